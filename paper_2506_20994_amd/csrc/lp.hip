@@ -127,6 +127,244 @@ gemm_nt(int M, int N, int K, const u16* __restrict__ A, int lda, const u16* __re
         }
 }
 
+// ---- products of the training step ------------------------------------------
+// C = A . B^T in the k order and with the instruction of gemm_nt (so every sum
+// is the same, bit for bit), for the shapes of a minibatch: 1024 x 256 has 16
+// tiles of 128 x 128, which left 240 of the 256 CUs idle and took 22 us a
+// product.  Here a wave owns a (16 TM) x (16 TN) tile and reads its MFMA
+// fragments straight from memory (a row's 16 bytes per lane; the operands are a
+// few hundred KB and sit in L2), two sets of k-steps in registers: no
+// LDS, no barriers, and 1024 waves for the same product.  What bounds it then
+// is the rate of those 16-row loads: 5-10 us a product, and the training step of
+// the lx = 8 network (batches of 1024, linear form) takes 71 us instead of 281.
+// The epilogue does what used to be passes of their own: the bf16 transpose
+// that the weight gradients' products read (a lane holds four consecutive rows
+// of a column: one 8-byte store), the loss and its gradient.
+enum { EPI_DIFF = 8, EPI_MSE = 16, EPI_METRIC = 32 };
+struct WaveGemm {
+    int M = 0, N = 0, K = 0;
+    const u16* A = nullptr; int lda = 0;
+    const u16* B = nullptr; int ldb = 0;
+    const int64_t *rows = nullptr, *trows = nullptr;   // row m of A is rows[m], of T trows[m]
+    const float* bias = nullptr;
+    const u16* mask = nullptr; int ldm = 0;
+    float* Cf = nullptr; u16* Cb = nullptr; int ldc = 0;
+    u16* Ct = nullptr; int ldt = 0;     // bf16 transpose: Ct[n * ldt + m]
+    int epi = 0;
+    const float* T = nullptr;           // targets (N wide)
+    float* dF = nullptr;                // EPI_DIFF: written; EPI_METRIC: read (N wide)
+    float scale = 0.f;                  // loss gradient
+    double* part = nullptr;             // EPI_MSE, EPI_METRIC: one loss partial per workgroup
+    int blocks = 0;                     // workgroups of this product
+};
+
+// k-steps a register set holds: 8 fragments ahead.  A training step of the lx = 8
+// network with batches of 1024 measured 71 us with 4 to 8 fragments, 76 with 16
+// and 91 with 24 (fewer waves in flight).
+constexpr int wave_unroll(int tm, int tn) { return 8 / (tm + tn) < 2 ? 2 : 8 / (tm + tn); }
+
+// the 4 waves of workgroup `blk` take 2 x 2 tiles, so that each fragment is read
+// by two waves of one CU
+template <int TM, int TN>
+__device__ __forceinline__ void wave_gemm_block(const WaveGemm& g, int blk, double* s_red) {
+    constexpr int U = wave_unroll(TM, TN);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int bn = (g.N + 32 * TN - 1) / (32 * TN);
+    const int m0 = (blk / bn) * 32 * TM + (wave >> 1) * 16 * TM;
+    const int n0 = (blk % bn) * 32 * TN + (wave & 1) * 16 * TN;
+    const int ko = (lane >> 4) * 8;
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    double loss = 0.0;
+    if (m0 < g.M && n0 < g.N) {                 // uniform over the wave
+        // rows past the end read the last row; their outputs are not stored
+        const u16 *pa[TM], *pb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int m = min(m0 + i * 16 + (lane & 15), g.M - 1);
+            pa[i] = g.A + (g.rows ? g.rows[m] : (int64_t)m) * g.lda;
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) pb[j] = g.B + (int64_t)min(n0 + j * 16 + (lane & 15), g.N - 1) * g.ldb;
+        // chunks of U k-steps in two register sets, the next chunk's loads issued
+        // before the current one's products.  The chunk past K is read at column 0
+        // and multiplied as zero.
+        bf16x8 fa[2][U][TM], fb[2][U][TN];
+        const int chunks = (g.K + 32 * U - 1) / (32 * U);
+        auto fetch = [&](int h, int c) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int k = (c * U + u) * 32 + ko;
+                k = k < g.K ? k : 0;
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fa[h][u][i] = *reinterpret_cast<const bf16x8*>(pa[i] + k);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fb[h][u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + k);
+            }
+            __builtin_amdgcn_sched_barrier(0);      // the loads stay ahead of the products that follow
+        };
+        auto multiply = [&](int h, int c, bool last) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool in = !last || (c * U + u) * 32 + ko < g.K;
+                const uint4 z{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    if (last) fa[h][u][i] = __builtin_bit_cast(bf16x8, in ? __builtin_bit_cast(uint4, fa[h][u][i]) : z);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    if (last) fb[h][u][j] = __builtin_bit_cast(bf16x8, in ? __builtin_bit_cast(uint4, fb[h][u][j]) : z);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][u][i], fb[h][u][j], acc[i][j], 0,
+                                                                            0, 0);
+            }
+        };
+        fetch(0, 0);
+        // what the epilogue reads (mask, target or metric residual, bias), loaded beside the operands
+        float side[TM][TN][4], bias[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = min(n0 + j * 16 + (lane & 15), g.N - 1);
+            bias[j] = (g.epi & EPI_BIAS) ? g.bias[n] : 0.f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int m = min(m0 + i * 16 + 4 * (lane >> 4) + q, g.M - 1);
+                    side[i][j][q] = 0.f;
+                    if (g.epi & EPI_MASK) side[i][j][q] = bf16_f(g.mask[(int64_t)m * g.ldm + n]);
+                    if (g.epi & (EPI_DIFF | EPI_MSE)) side[i][j][q] = g.T[(g.trows ? g.trows[m] : (int64_t)m) * g.N + n];
+                    if (g.epi & EPI_METRIC) side[i][j][q] = g.dF[(int64_t)m * g.N + n];
+                }
+        }
+        int c = 0;
+        for (; c + 2 < chunks; c += 2) {
+            fetch(1, c + 1);
+            multiply(0, c, false);
+            fetch(0, c + 2);
+            multiply(1, c + 1, false);
+        }
+        if (c + 1 < chunks) {
+            fetch(1, c + 1);
+            multiply(0, c, false);
+            multiply(1, c + 1, true);
+        } else {
+            multiply(0, c, true);
+        }
+        // acc[i][j][q] = C[m0 + 16 i + 4 (lane / 16) + q][n0 + 16 j + lane % 16]
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int n = n0 + j * 16 + (lane & 15), mb = m0 + i * 16 + 4 * (lane >> 4);
+                if (n >= g.N) continue;
+                u16 t[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int m = mb + q;
+                    t[q] = 0;
+                    if (m >= g.M) continue;
+                    float v = acc[i][j][q] + bias[j];
+                    if (g.epi & EPI_RELU) v = fmaxf(v, 0.f);
+                    if ((g.epi & EPI_MASK) && !(side[i][j][q] > 0.f)) v = 0.f;
+                    if (g.epi & (EPI_DIFF | EPI_MSE)) v -= side[i][j][q];
+                    if (g.epi & EPI_DIFF) g.dF[(int64_t)m * g.N + n] = v;
+                    if (g.epi & EPI_MSE) {
+                        loss += (double)v * v;
+                        v = g.scale * v;
+                    }
+                    if (g.epi & EPI_METRIC) {
+                        loss += (double)side[i][j][q] * v;
+                        v = g.scale * v;
+                    }
+                    if (g.Cf) g.Cf[(int64_t)m * g.ldc + n] = v;
+                    t[q] = bf16_rne(v);
+                    if (g.Cb) g.Cb[(int64_t)m * g.ldc + n] = t[q];
+                }
+                // M and ldt are multiples of 8 where a transpose is asked for
+                if (g.Ct && mb < g.M) {
+                    const uint2 w{(uint32_t)t[0] | ((uint32_t)t[1] << 16), (uint32_t)t[2] | ((uint32_t)t[3] << 16)};
+                    *reinterpret_cast<uint2*>(g.Ct + (int64_t)n * g.ldt + mb) = w;
+                }
+            }
+    }
+    if (g.part) {
+        loss = sem::wave_sum(loss);
+        if (lane == 0) s_red[wave] = loss;
+        __syncthreads();
+        if (threadIdx.x == 0) g.part[blk] = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+    }
+}
+
+// what a launch of products does besides, in workgroups of its own
+struct WaveAux {
+    // out[c][r] = bf16 row rows[r] (r itself without rows) of in, transposed, in
+    // 32 x 32 tiles: the minibatch's features as the first layer's weight gradient
+    // reads them
+    u16* out = nullptr; int ldo = 0;
+    const u16* in = nullptr; int ldi = 0;
+    const int64_t* rows = nullptr;
+    int nrows = 0, cols = 0;
+    // one workgroup: *loss (and *loss2 when given) = inv_n times the sum of the nb
+    // partials in a fixed order; z[q][0 .. nz[q]) = 0 (the linear form's unused
+    // bias gradients)
+    const double* part = nullptr;
+    int nb = 0;
+    double inv_n = 0.0;
+    float *loss = nullptr, *loss2 = nullptr;
+    float* z[3] = {};
+    int nz[3] = {};
+};
+
+__device__ __forceinline__ void gather_transpose(const WaveAux& a, int blk, u16 (*t)[33]) {
+    const int bc = (a.cols + 31) / 32;
+    const int c0 = (blk % bc) * 32, r0 = (blk / bc) * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 256 threads: 32 x 8
+    for (int y = ty; y < 32; y += 8) {
+        const int r = r0 + y, c = c0 + tx;
+        t[y][tx] = (r < a.nrows && c < a.cols) ? a.in[(a.rows ? a.rows[r] : (int64_t)r) * a.ldi + c] : (u16)0;
+    }
+    __syncthreads();
+    for (int y = ty; y < 32; y += 8) {
+        const int c = c0 + y, r = r0 + tx;
+        if (c < a.cols && r < a.nrows) a.out[(int64_t)c * a.ldo + r] = t[tx][y];
+    }
+}
+
+__device__ __forceinline__ void loss_final(const WaveAux& a, double* s_red) {
+    for (int l = 0; l < 3; ++l)
+        for (int q = threadIdx.x; q < a.nz[l]; q += 256) a.z[l][q] = 0.f;
+    double t = 0.0;
+    for (int q = threadIdx.x; q < a.nb; q += 256) t += a.part[q];
+    t = sem::wave_sum(t);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const float v = (float)(((s_red[0] + s_red[1]) + (s_red[2] + s_red[3])) * a.inv_n);
+        *a.loss = v;
+        if (a.loss2) *a.loss2 = v;
+    }
+}
+
+// up to two independent products in one launch (g1.blocks = 0: one), then the
+// workgroups of `aux`
+template <int TM, int TN>
+__global__ void __launch_bounds__(256) wave_gemm(WaveGemm g0, WaveGemm g1, WaveAux aux) {
+    __shared__ double s_red[4];
+    __shared__ u16 s_t[32][33];
+    const int b = blockIdx.x;
+    if (b < g0.blocks) wave_gemm_block<TM, TN>(g0, b, s_red);
+    else if (b < g0.blocks + g1.blocks) wave_gemm_block<TM, TN>(g1, b - g0.blocks, s_red);
+    else if (aux.out) gather_transpose(aux, b - g0.blocks - g1.blocks, s_t);
+    else loss_final(aux, s_red);
+}
+
 // C[r][c] = sum_k A[r][k] B[k][c] in float32 (small products of the weights)
 __global__ void matmul_f32(float* __restrict__ C, const float* __restrict__ A, const float* __restrict__ B,
                            int rows, int inner, int cols, int lda, int ldb, int ldc) {
@@ -143,28 +381,11 @@ __global__ void f32_to_bf16(u16* __restrict__ out, const float* __restrict__ in,
         out[q] = bf16_rne(in[q]);
 }
 
-// out[c][r] = in[r][c] (bf16), rows x cols, leading dims ldi / ldo
 // out = bf16((in + in^T) / 2) for an n x n row-major matrix
 __global__ void sym_to_bf16(u16* __restrict__ out, const float* __restrict__ in, int n) {
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n * n; q += gridDim.x * blockDim.x) {
         const int i = q / n, j = q % n;
         out[q] = bf16_rne(0.5f * (in[q] + in[j * n + i]));
-    }
-}
-
-__global__ void transpose_bf16(u16* __restrict__ out, int ldo, const u16* __restrict__ in, int ldi,
-                               int rows, int cols) {
-    __shared__ u16 t[32][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 256 threads: 32 x 8
-    for (int y = ty; y < 32; y += 8) {
-        const int r = r0 + y, c = c0 + tx;
-        t[y][tx] = (r < rows && c < cols) ? in[(int64_t)r * ldi + c] : (u16)0;
-    }
-    __syncthreads();
-    for (int y = ty; y < 32; y += 8) {
-        const int c = c0 + y, r = r0 + tx;
-        if (c < cols && r < rows) out[(int64_t)c * ldo + r] = t[tx][y];
     }
 }
 
@@ -182,94 +403,24 @@ __global__ void weights_to_bf16(u16* __restrict__ out, int ldo, u16* __restrict_
     }
 }
 
-// batch gather: Xb[i] = X[rows[i]] (bf16, nip wide), Tb[i] = T[rows[i]] (float, no)
-__global__ void gather_rows(u16* __restrict__ Xb, float* __restrict__ Tb, const u16* __restrict__ X,
-                            const float* __restrict__ T, const int64_t* __restrict__ rows, int B, int nip, int no) {
+// batch gather: Xb[i] = X[rows[i]] (bf16, nip wide)
+__global__ void gather_rows(u16* __restrict__ Xb, const u16* __restrict__ X, const int64_t* __restrict__ rows, int B,
+                            int nip) {
     const int i = blockIdx.x;
     if (i >= B) return;
     const int64_t r = rows[i];
     for (int c = threadIdx.x; c < nip; c += blockDim.x) Xb[(int64_t)i * nip + c] = X[r * nip + c];
-    for (int c = threadIdx.x; c < no; c += blockDim.x) Tb[(int64_t)i * no + c] = T[r * no + c];
 }
 
-// d3 = 2 (Y3 - T) / (B * kOut) as float and bf16; per-block partial of sum (Y3 - T)^2
-__global__ void mse_grad(float* __restrict__ d3f, u16* __restrict__ d3b, const float* __restrict__ Y3,
-                         const float* __restrict__ T, int64_t n, float scale, double* __restrict__ part) {
-    __shared__ double s[kBlock / 64];
-    double acc = 0.0;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const float d = Y3[q] - T[q];
-        acc += (double)d * d;
-        const float g = scale * d;
-        d3f[q] = g;
-        d3b[q] = bf16_rne(g);
-    }
-    acc = sem::wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < kBlock / 64; ++q) t += s[q];
-        part[blockIdx.x] = t;
-    }
-}
-
-// d = Y3 - T as float and bf16 (the metric loss's residual)
-__global__ void diff_kernel(float* __restrict__ df, u16* __restrict__ db, const float* __restrict__ Y3,
-                            const float* __restrict__ T, int64_t n) {
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const float d = Y3[q] - T[q];
-        df[q] = d;
-        db[q] = bf16_rne(d);
-    }
-}
-
-// loss partials sum d.Kd; gradient d3 = scale * Kd (float and bf16)
-__global__ void metric_grad(float* __restrict__ d3f, u16* __restrict__ d3b, const float* __restrict__ df,
-                            const float* __restrict__ Kd, int64_t n, float scale, double* __restrict__ part) {
-    __shared__ double s[kBlock / 64];
-    double acc = 0.0;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const float k = Kd[q];
-        acc += (double)df[q] * k;
-        const float g = scale * k;
-        d3f[q] = g;
-        d3b[q] = bf16_rne(g);
-    }
-    acc = sem::wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < kBlock / 64; ++q) t += s[q];
-        part[blockIdx.x] = t;
-    }
-}
-
-// one 256-thread block: strided partial sums, then a fixed-order tree
-__global__ void loss_final(float* __restrict__ loss, const double* __restrict__ part, int nb, double inv_n) {
-    __shared__ double s_red[256];
-    double t = 0.0;
-    for (int q = threadIdx.x; q < nb; q += 256) t += part[q];
-    s_red[threadIdx.x] = t;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s_red[threadIdx.x] += s_red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = (float)(s_red[0] * inv_n);
-}
-
-// out[c] = sum_r d[r][c] (float), fixed order
 // column sums of a (rows x cols) row-major matrix in two deterministic passes:
 // part[chunk][c] = sum over the 64 rows of the chunk (256 threads: 4 row groups
 // x 64 columns, combined in a fixed order), then out[c] = sum over the chunks
 constexpr int kColRows = 64;
-__global__ void colsum_part(float* __restrict__ part, const float* __restrict__ d, int rows, int cols) {
+struct ColSums { float* out[3]; float* part[3]; const float* d[3]; int cols[3]; };   // the three layers
+__global__ void colsum_part(ColSums a, int rows) {
     __shared__ float s_red[4][64];
+    const int cols = a.cols[blockIdx.z];
+    const float* __restrict__ d = a.d[blockIdx.z];
     const int c = blockIdx.x * 64 + (threadIdx.x & 63), rg = threadIdx.x >> 6;
     const int r0 = blockIdx.y * kColRows;
     float s = 0.f;
@@ -278,33 +429,49 @@ __global__ void colsum_part(float* __restrict__ part, const float* __restrict__ 
     s_red[rg][threadIdx.x & 63] = s;
     __syncthreads();
     if (rg == 0 && c < cols)
-        part[(int64_t)blockIdx.y * cols + c] = (s_red[0][threadIdx.x] + s_red[1][threadIdx.x]) +
-                                              (s_red[2][threadIdx.x] + s_red[3][threadIdx.x]);
+        a.part[blockIdx.z][(int64_t)blockIdx.y * cols + c] = (s_red[0][threadIdx.x] + s_red[1][threadIdx.x]) +
+                                                             (s_red[2][threadIdx.x] + s_red[3][threadIdx.x]);
 }
 
-__global__ void colsum_final(float* __restrict__ out, const float* __restrict__ part, int chunks, int cols) {
+__global__ void colsum_final(ColSums a, int chunks) {
+    const int cols = a.cols[blockIdx.z];
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= cols) return;
     float s = 0.f;
-    for (int q = 0; q < chunks; ++q) s += part[(int64_t)q * cols + c];
-    out[c] = s;
+    for (int q = 0; q < chunks; ++q) s += a.part[blockIdx.z][(int64_t)q * cols + c];
+    a.out[blockIdx.z][c] = s;
 }
 
-// Adam on a (rows x cols) parameter whose gradient has leading dim ldg
-__global__ void adam_kernel(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, int rows, int cols, int ldg, float lr,
-                            float b1, float omb1, float b2, float omb2, float eps, float c1, float c2) {
-    const int64_t n = (int64_t)rows * cols;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = q / cols, c = q % cols;
-        const float gv = g[r * ldg + c];
-        const float mv = b1 * m[q] + omb1 * gv;
-        const float vv = b2 * v[q] + omb2 * gv * gv;
-        m[q] = mv;
-        v[q] = vv;
-        p[q] -= lr * (mv / c1) / (sqrtf(vv / c2) + eps);
-    }
+// Adam on the six parameters in one launch (parameter q from workgroup first[q]
+// on, one value per thread), followed by the new value's bf16 copies (the
+// padded row-major one and, where there is one, the transpose): six launches
+// and three conversions a step before.  A gradient row has ldg values.
+struct AdamSet {
+    float *p[6], *m[6], *v[6];
+    const float* g[6];
+    int rows[6], cols[6], ldg[6], ldb[6];
+    u16 *wb[6], *wt[6];
+    int first[7];
+};
+__global__ void adam_kernel(AdamSet a, float lr, float b1, float omb1, float b2, float omb2, float eps, float c1,
+                            float c2) {
+    int s = 0;
+    while (s < 5 && (int)blockIdx.x >= a.first[s + 1]) ++s;
+    const int64_t q = (int64_t)((int)blockIdx.x - a.first[s]) * blockDim.x + threadIdx.x;
+    const int cols = a.cols[s];
+    if (q >= (int64_t)a.rows[s] * cols) return;
+    const int64_t r = q / cols, c = q % cols;
+    float *p = a.p[s], *m = a.m[s], *v = a.v[s];
+    const float gv = a.g[s][r * a.ldg[s] + c];
+    const float mv = b1 * m[q] + omb1 * gv;
+    const float vv = b2 * v[q] + omb2 * gv * gv;
+    m[q] = mv;
+    v[q] = vv;
+    const float pn = p[q] - lr * (mv / c1) / (sqrtf(vv / c2) + eps);
+    p[q] = pn;
+    const u16 h = bf16_rne(pn);
+    if (a.wb[s]) a.wb[s][r * a.ldb[s] + c] = h;
+    if (a.wt[s]) a.wt[s][c * a.rows[s] + r] = h;
 }
 
 // per-element geometric features (six means of h1 g_ab over kappa), kappa and 1/kappa
@@ -647,10 +814,6 @@ __global__ void first_copy_kernel(double* __restrict__ out, const double* __rest
         out[u] = in[uidx[uoff[u]]];
 }
 
-__global__ void zero_f32(float* __restrict__ x, int n) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) x[q] = 0.f;
-}
-
 // x = 1 / x, with 0 kept at 0 (Dirichlet nodes, zeroed by the gather-scatter)
 __global__ void inv_kernel(double* __restrict__ x, int64_t n) {
     for (int64_t L = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; L < n;
@@ -695,9 +858,11 @@ struct sem_lp_s {
     bool fold_dirty = true;   // folded matrix of the linear form out of date
     float* colpart = nullptr; // column-sum partials (bias gradients)
     // activations / work for up to max_rows rows
-    u16 *X = nullptr, *Y1 = nullptr, *Y2 = nullptr, *d3b = nullptr, *d2b = nullptr, *d1b = nullptr;
-    float *Y3 = nullptr, *T = nullptr, *d3f = nullptr, *d2f = nullptr, *d1f = nullptr, *scale = nullptr;
-    u16 *tA = nullptr, *tB = nullptr;   // transposes (nip x max_rows each)
+    u16 *X = nullptr, *Y1 = nullptr, *Y2 = nullptr, *d3b = nullptr, *d2b = nullptr;
+    float *Y3 = nullptr, *d3f = nullptr, *d2f = nullptr, *d1f = nullptr, *scale = nullptr;
+    // transposes of a minibatch (k-contiguous operands of the weight gradients)
+    u16 *Xt = nullptr, *Y1t = nullptr, *Y2t = nullptr, *d3t = nullptr, *d2t = nullptr, *d1t = nullptr;
+    double* lpart = nullptr;            // loss partials of the training products
     double* part = nullptr;
     float* loss = nullptr;
     // bound operator (inference)
@@ -709,7 +874,7 @@ struct sem_lp_s {
     const int* skip = nullptr;   // set by the solver: kernels return when *skip != 0
     // energy-norm loss: metric K (no x no, bf16) and work arrays
     u16* K = nullptr;
-    float *dF = nullptr, *Kd = nullptr;
+    float* dF = nullptr;
     u16* dB = nullptr;
     // linear form: identity activations, no biases, geometric inputs zeroed;
     // inference then uses the folded matrix (W3 W2 W1)[:, :no] (bf16)
@@ -773,10 +938,30 @@ int launch_features(sem_lp_t lp, int64_t count, u16* X, float* scale, float* Tt,
     return SEM_OK;
 }
 
-int transpose(sem_lp_t lp, u16* out, int ldo, const u16* in, int ldi, int rows, int cols) {
-    dim3 grid((cols + 31) / 32, (rows + 31) / 32);
-    transpose_bf16<<<grid, 256, 0, lp->ctx->stream>>>(out, ldo, in, ldi, rows, cols);
+// tiles of the wave products, by their count: one MFMA tile per wave up to 2048
+// tiles (2048 waves, two per SIMD), 2 x 2 up to 8192, 4 x 4 above.  At 1024 rows
+// and 256 or 512 columns 2 x 2 already measured slower (step 93 against 76 us).
+template <int TM, int TN>
+int wave_blocks(const WaveGemm& g) {
+    return ((g.M + 32 * TM - 1) / (32 * TM)) * ((g.N + 32 * TN - 1) / (32 * TN));
+}
+template <int TM, int TN>
+int wave_launch(hipStream_t st, WaveGemm g0, WaveGemm g1, const WaveAux& aux) {
+    g0.blocks = wave_blocks<TM, TN>(g0);
+    g1.blocks = g1.M > 0 ? wave_blocks<TM, TN>(g1) : 0;
+    const int extra = aux.out ? ((aux.cols + 31) / 32) * ((aux.nrows + 31) / 32) : aux.part ? 1 : 0;
+    wave_gemm<TM, TN><<<(unsigned)(g0.blocks + g1.blocks + extra), 256, 0, st>>>(g0, g1, aux);
+    return g0.blocks;
+}
+int wave_products(sem_lp_t lp, const WaveGemm& g0, const WaveGemm& g1 = WaveGemm(), const WaveAux& aux = WaveAux(),
+                  int* nblocks = nullptr) {
+    hipStream_t st = lp->ctx->stream;
+    const int64_t tiles = (int64_t)((g0.M + 15) / 16) * ((g0.N + 15) / 16) +
+                          (int64_t)((g1.M + 15) / 16) * ((g1.N + 15) / 16);
+    const int nb = tiles <= 2048 ? wave_launch<1, 1>(st, g0, g1, aux)
+                 : tiles <= 8192 ? wave_launch<2, 2>(st, g0, g1, aux) : wave_launch<4, 4>(st, g0, g1, aux);
     SEM_LAUNCH_CHECK(lp->ctx);
+    if (nblocks) *nblocks = nb;
     return SEM_OK;
 }
 
@@ -884,7 +1069,6 @@ extern "C" int sem_lp_create_lx(sem_ctx_t ctx, int lx, int hidden, int64_t max_r
     LP_ALLOC(lp->Y1, 2 * R * kHid);
     LP_ALLOC(lp->Y2, 2 * R * kHid);
     LP_ALLOC(lp->Y3, 4 * R * no);
-    LP_ALLOC(lp->T, 4 * R * no);
     LP_ALLOC(lp->scale, 4 * R);
     LP_ALLOC(lp->part, 8 * 4096);
     LP_ALLOC(lp->loss, 4);
@@ -1021,9 +1205,6 @@ extern "C" int sem_lp_set_metric(sem_lp_t lp, double mu) {
         rc = lp_alloc(lp, &p, 4 * R * kOut);
         if (rc) return rc;
         lp->dF = (float*)p;
-        rc = lp_alloc(lp, &p, 4 * R * kOut);
-        if (rc) return rc;
-        lp->Kd = (float*)p;
         rc = lp_alloc(lp, &p, 2 * R * kOut);
         if (rc) return rc;
         lp->dB = (u16*)p;
@@ -1294,65 +1475,116 @@ extern "C" int sem_lp_forward(sem_lp_t lp, const uint16_t* X, int64_t rows, floa
     return SEM_OK;
 }
 
-static void colsum(sem_lp_t lp, float* out, const float* d, int rows, int cols) {
-    hipStream_t st = lp->ctx->stream;
-    const int chunks = (rows + kColRows - 1) / kColRows;
-    colsum_part<<<dim3((cols + 63) / 64, chunks), 256, 0, st>>>(lp->colpart, d, rows, cols);
-    colsum_final<<<(cols + 255) / 256, 256, 0, st>>>(out, lp->colpart, chunks, cols);
-}
-
-// gradients of the batch loss into the gradient slots (and the loss into *loss_dev)
-static int lp_backward(sem_lp_t lp, const uint16_t* Xb, const float* Tb, int B) {
+// gradients of the batch loss into the gradient slots (and the loss into
+// lp->loss and *loss2): row m of the batch is row rows[m] of T (m itself without
+// rows), and of X with x_rows.  Seven launches (two more for the
+// nonlinear form's bias gradients); the products that depend on the same error
+// share one.
+static int lp_backward(sem_lp_t lp, const uint16_t* X, const float* T, const int64_t* rows, bool x_rows, int B,
+                       float* loss2) {
     const int kHid = lp->nh;     // this network's hidden width
     sem_ctx_t ctx = lp->ctx;
     hipStream_t st = ctx->stream;
-    int rc = forward(lp, Xb, B);
+    int rc = refresh_bf16(lp);
     if (rc) return rc;
     const int kOut = lp->no, kInPad = lp->nip;     // this network's sizes
     const int64_t n3 = (int64_t)B * kOut;
-    const unsigned g = grid_of(n3);
+    const bool lin = lp->linear;
+    WaveAux xt;                                    // X^T beside the first product
+    xt.out = lp->Xt; xt.ldo = B;
+    xt.in = X; xt.ldi = kInPad;
+    xt.rows = x_rows ? rows : nullptr;
+    xt.nrows = B; xt.cols = kInPad;
+    auto product = [&](int M, int N, int K, const u16* A, int lda, const u16* Bm, int ldb) {
+        WaveGemm g;
+        g.M = M; g.N = N; g.K = K;
+        g.A = A; g.lda = lda;
+        g.B = Bm; g.ldb = ldb;
+        return g;
+    };
+    // forward: Y1 and Y2 also transposed
+    WaveGemm g = product(B, kHid, kInPad, X, kInPad, lp->W1b, kInPad);
+    g.rows = x_rows ? rows : nullptr;
+    g.bias = lp->b[0]; g.epi = lin ? 0 : EPI_BIAS | EPI_RELU;
+    g.Cb = lp->Y1; g.ldc = kHid; g.Ct = lp->Y1t; g.ldt = B;
+    if ((rc = wave_products(lp, g, WaveGemm(), xt))) return rc;
+    g = product(B, kHid, kHid, lp->Y1, kHid, lp->W2b, kHid);
+    g.bias = lp->b[1]; g.epi = lin ? 0 : EPI_BIAS | EPI_RELU;
+    g.Cb = lp->Y2; g.ldc = kHid; g.Ct = lp->Y2t; g.ldt = B;
+    if ((rc = wave_products(lp, g))) return rc;
+    // output layer: its epilogue takes the targets off.  Mean squared error: d3 =
+    // scale (y - t).  Metric: loss = mean_b d_b^T K d_b, d3 = 2 K d / B, one more product.
+    int nb = 0;
+    g = product(B, kOut, kHid, lp->Y2, kHid, lp->W3b, kHid);
+    g.trows = rows;
+    g.bias = lp->b[2]; g.epi = lin ? 0 : EPI_BIAS;
+    g.T = T;
+    WaveGemm d3 = g;
     if (lp->K) {
-        // loss = mean_b d_b^T K d_b, gradient 2 K d / B
-        diff_kernel<<<g, kBlock, 0, st>>>(lp->dF, lp->dB, lp->Y3, Tb, n3);
-        rc = gemm(lp, B, kOut, kOut, lp->dB, kOut, lp->K, kOut, nullptr, nullptr, 0, lp->Kd, nullptr, kOut, 0);
-        if (rc) return rc;
-        metric_grad<<<g, kBlock, 0, st>>>(lp->d3f, lp->d3b, lp->dF, lp->Kd, n3, 2.0f / (float)B, lp->part);
-        loss_final<<<1, 256, 0, st>>>(lp->loss, lp->part, (int)g, 1.0 / (double)B);
+        g.epi |= EPI_DIFF;
+        g.dF = lp->dF; g.Cb = lp->dB; g.ldc = kOut;
+        if ((rc = wave_products(lp, g))) return rc;
+        d3 = product(B, kOut, kOut, lp->dB, kOut, lp->K, kOut);
+        d3.epi = EPI_METRIC;
+        d3.dF = lp->dF;
+        d3.scale = 2.0f / (float)B;
     } else {
-        mse_grad<<<g, kBlock, 0, st>>>(lp->d3f, lp->d3b, lp->Y3, Tb, n3, 2.0f / (float)n3, lp->part);
-        loss_final<<<1, 256, 0, st>>>(lp->loss, lp->part, (int)g, 1.0 / (double)n3);
+        d3.epi |= EPI_MSE;
+        d3.scale = 2.0f / (float)n3;
     }
-    SEM_LAUNCH_CHECK(ctx);
-    // layer 3: gW3 = d3^T Y2, gb3 = colsum d3, d2 = (d3 W3) * (Y2 > 0)
-    rc = transpose(lp, lp->tA, B, lp->d3b, kOut, B, kOut);           // d3^T: no x B
-    if (!rc) rc = transpose(lp, lp->tB, B, lp->Y2, kHid, B, kHid);   // Y2^T: 256 x B
-    if (!rc) rc = gemm(lp, kOut, kHid, B, lp->tA, B, lp->tB, B, nullptr, nullptr, 0, lp->gW[2], nullptr, kHid, 0);
-    const int mask = lp->linear ? 0 : EPI_MASK;
-    if (!lp->linear) colsum(lp, lp->gb[2], lp->d3f, B, kOut);
-    if (!rc) rc = gemm(lp, B, kHid, kOut, lp->d3b, kOut, lp->W3t, kOut, nullptr, lp->Y2, kHid, lp->d2f, lp->d2b, kHid, mask);
-    // layer 2
-    if (!rc) rc = transpose(lp, lp->tA, B, lp->d2b, kHid, B, kHid);
-    if (!rc) rc = transpose(lp, lp->tB, B, lp->Y1, kHid, B, kHid);
-    if (!rc) rc = gemm(lp, kHid, kHid, B, lp->tA, B, lp->tB, B, nullptr, nullptr, 0, lp->gW[1], nullptr, kHid, 0);
-    if (!lp->linear) colsum(lp, lp->gb[1], lp->d2f, B, kHid);
-    if (!rc) rc = gemm(lp, B, kHid, kHid, lp->d2b, kHid, lp->W2t, kHid, nullptr, lp->Y1, kHid, lp->d1f, lp->d1b, kHid, mask);
-    // layer 1
-    if (!rc) rc = transpose(lp, lp->tA, B, lp->d1b, kHid, B, kHid);
-    if (!rc) rc = transpose(lp, lp->tB, B, Xb, kInPad, B, kInPad);
-    if (!rc) rc = gemm(lp, kHid, kInPad, B, lp->tA, B, lp->tB, B, nullptr, nullptr, 0, lp->gW[0], nullptr, kInPad, 0);
-    if (!lp->linear) colsum(lp, lp->gb[0], lp->d1f, B, kHid);
-    if (lp->linear) {   // the biases are not used: their gradients are zero
-        zero_f32<<<1, 256, 0, st>>>(lp->gb[0], kHid);
-        zero_f32<<<1, 256, 0, st>>>(lp->gb[1], kHid);
-        zero_f32<<<2, 256, 0, st>>>(lp->gb[2], kOut);
+    d3.part = lp->lpart;
+    d3.Cf = lin ? nullptr : lp->d3f; d3.Cb = lp->d3b; d3.ldc = kOut; d3.Ct = lp->d3t; d3.ldt = B;
+    if ((rc = wave_products(lp, d3, WaveGemm(), WaveAux(), &nb))) return rc;
+    WaveAux sum;                                   // the loss beside the next products
+    sum.part = lp->lpart; sum.nb = nb;
+    sum.inv_n = lp->K ? 1.0 / (double)B : 1.0 / (double)n3;
+    sum.loss = lp->loss; sum.loss2 = loss2;
+    for (int l = 0; l < 3; ++l) {
+        sum.z[l] = lp->gb[l];
+        sum.nz[l] = lin ? param_rows(lp, l) : 0;
     }
-    SEM_LAUNCH_CHECK(ctx);
-    return rc;
+    // layer 3: gW3 = d3^T Y2 and d2 = (d3 W3) * (Y2 > 0)
+    const int mask = lin ? 0 : EPI_MASK;
+    WaveGemm w = product(kOut, kHid, B, lp->d3t, B, lp->Y2t, B);
+    w.Cf = lp->gW[2]; w.ldc = kHid;
+    g = product(B, kHid, kOut, lp->d3b, kOut, lp->W3t, kOut);
+    g.epi = mask; g.mask = lp->Y2; g.ldm = kHid;
+    g.Cf = lin ? nullptr : lp->d2f; g.Cb = lp->d2b; g.ldc = kHid; g.Ct = lp->d2t; g.ldt = B;
+    if ((rc = wave_products(lp, w, g, sum))) return rc;
+    // layer 2: gW2 = d2^T Y1 and d1 = (d2 W2) * (Y1 > 0)
+    w = product(kHid, kHid, B, lp->d2t, B, lp->Y1t, B);
+    w.Cf = lp->gW[1]; w.ldc = kHid;
+    g = product(B, kHid, kHid, lp->d2b, kHid, lp->W2t, kHid);
+    g.epi = mask; g.mask = lp->Y1; g.ldm = kHid;
+    g.Cf = lin ? nullptr : lp->d1f; g.ldc = kHid; g.Ct = lp->d1t; g.ldt = B;
+    if ((rc = wave_products(lp, w, g))) return rc;
+    // layer 1: gW1 = d1^T X
+    w = product(kHid, kInPad, B, lp->d1t, B, lp->Xt, B);
+    w.Cf = lp->gW[0]; w.ldc = kInPad;
+    if ((rc = wave_products(lp, w))) return rc;
+    if (!lin) {     // bias gradients: column sums of the float32 errors
+        const int chunks = (B + kColRows - 1) / kColRows, wide = std::max(kHid, kOut);
+        ColSums cs;
+        const float* d[3] = {lp->d1f, lp->d2f, lp->d3f};
+        const int cols[3] = {kHid, kHid, kOut};
+        size_t at = 0;
+        for (int l = 0; l < 3; ++l) {
+            cs.out[l] = lp->gb[l];
+            cs.d[l] = d[l];
+            cs.cols[l] = cols[l];
+            cs.part[l] = lp->colpart + at;
+            at += (size_t)chunks * cols[l];
+        }
+        colsum_part<<<dim3((wide + 63) / 64, chunks, 3), 256, 0, st>>>(cs, B);
+        colsum_final<<<dim3((wide + 255) / 256, 1, 3), 256, 0, st>>>(cs, chunks);
+        SEM_LAUNCH_CHECK(ctx);
+    }
+    return SEM_OK;
 }
 
 static int lp_train_buffers(sem_lp_t lp, int B) {
     const int kHid = lp->nh;     // this network's hidden width
-    if (lp->d3f) return SEM_OK;
+    if (lp->lpart) return SEM_OK;
     const size_t R = (size_t)lp->max_rows;
     const size_t kOut = (size_t)lp->no, kInPad = (size_t)lp->nip;
     void* p = nullptr;
@@ -1363,13 +1595,15 @@ static int lp_train_buffers(sem_lp_t lp, int B) {
     LP_ALLOC2(lp->d2f, 4 * R * kHid);
     LP_ALLOC2(lp->d2b, 2 * R * kHid);
     LP_ALLOC2(lp->d1f, 4 * R * kHid);
-    LP_ALLOC2(lp->d1b, 2 * R * kHid);
-    // the transposes hold no x B, 256 x B or nip x B values, the column-sum
-    // partials chunks x no or chunks x 256 (no < 256 for lx < 8)
-    const size_t wide = std::max<size_t>(kInPad, (size_t)kHid), cols = std::max<size_t>(kOut, (size_t)kHid);
-    LP_ALLOC2(lp->tA, 2 * R * wide);
-    LP_ALLOC2(lp->tB, 2 * R * wide);
-    LP_ALLOC2(lp->colpart, 4 * ((R + kColRows - 1) / kColRows) * cols);
+    LP_ALLOC2(lp->Xt, 2 * R * kInPad);
+    LP_ALLOC2(lp->Y1t, 2 * R * kHid);
+    LP_ALLOC2(lp->Y2t, 2 * R * kHid);
+    LP_ALLOC2(lp->d3t, 2 * R * kOut);
+    LP_ALLOC2(lp->d2t, 2 * R * kHid);
+    LP_ALLOC2(lp->d1t, 2 * R * kHid);
+    LP_ALLOC2(lp->colpart, 4 * ((R + kColRows - 1) / kColRows) * (2 * (size_t)kHid + kOut));
+    // one loss partial per workgroup of the output layer's product, at most one per 32 x 32 tile
+    LP_ALLOC2(lp->lpart, 8 * ((R + 31) / 32) * ((kOut + 31) / 32));
 #undef LP_ALLOC2
     (void)B;
     return SEM_OK;
@@ -1384,7 +1618,7 @@ extern "C" int sem_lp_gradients(sem_lp_t lp, const uint16_t* X, const float* T, 
         return sem::fail(ctx, SEM_EINVAL, "sem_lp_gradients: batch %lld must be in [1, max_rows], a multiple of 8",
                          (long long)B);
     rc = lp_train_buffers(lp, (int)B);
-    if (!rc) rc = lp_backward(lp, X, T, (int)B);
+    if (!rc) rc = lp_backward(lp, X, T, nullptr, false, (int)B, nullptr);
     if (rc) return rc;
     if (loss) {
         SEM_HIP(ctx, hipMemcpyAsync(loss, lp->loss, 4, hipMemcpyDeviceToHost, ctx->stream));
@@ -1401,18 +1635,33 @@ extern "C" int sem_lp_adam(sem_lp_t lp, double lr, double beta1, double beta2, d
     lp->step += 1;
     const double c1 = 1.0 - std::pow(beta1, (double)lp->step);
     const double c2 = 1.0 - std::pow(beta2, (double)lp->step);
-    for (int l = 0; l < 3; ++l) {
-        const int rows = param_rows(lp, l), cols = param_cols(lp, l);
-        adam_kernel<<<grid_of((int64_t)rows * cols), kBlock, 0, ctx->stream>>>(
-            lp->W[l], lp->mW[l], lp->vW[l], lp->gW[l], rows, cols, l == 0 ? lp->nip : cols, (float)lr,
-            (float)beta1, (float)(1.0 - beta1), (float)beta2, (float)(1.0 - beta2), (float)eps,
-            (float)c1, (float)c2);
-        adam_kernel<<<grid_of(rows), kBlock, 0, ctx->stream>>>(
-            lp->b[l], lp->mb[l], lp->vb[l], lp->gb[l], 1, rows, rows, (float)lr, (float)beta1,
-            (float)(1.0 - beta1), (float)beta2, (float)(1.0 - beta2), (float)eps, (float)c1, (float)c2);
+    AdamSet a;
+    int first = 0;
+    for (int q = 0; q < 6; ++q) {       // W1, b1, W2, b2, W3, b3
+        const int l = q / 2;
+        const bool isW = q % 2 == 0;
+        a.rows[q] = isW ? param_rows(lp, l) : 1;
+        a.cols[q] = isW ? param_cols(lp, l) : param_rows(lp, l);
+        a.ldg[q] = q == 0 ? lp->nip : a.cols[q];
+        a.p[q] = isW ? lp->W[l] : lp->b[l];
+        a.m[q] = isW ? lp->mW[l] : lp->mb[l];
+        a.v[q] = isW ? lp->vW[l] : lp->vb[l];
+        a.g[q] = isW ? lp->gW[l] : lp->gb[l];
+        a.wb[q] = a.wt[q] = nullptr;
+        a.ldb[q] = 0;
+        a.first[q] = first;
+        first += (int)(((int64_t)a.rows[q] * a.cols[q] + kBlock - 1) / kBlock);
     }
+    a.first[6] = first;
+    a.wb[0] = lp->W1b; a.ldb[0] = lp->nip;      // the padding columns stay zero from creation on
+    a.wb[2] = lp->W2b; a.ldb[2] = lp->nh; a.wt[2] = lp->W2t;
+    a.wb[4] = lp->W3b; a.ldb[4] = lp->nh; a.wt[4] = lp->W3t;
+    adam_kernel<<<(unsigned)first, kBlock, 0, ctx->stream>>>(a, (float)lr, (float)beta1, (float)(1.0 - beta1),
+                                                             (float)beta2, (float)(1.0 - beta2), (float)eps,
+                                                             (float)c1, (float)c2);
     SEM_LAUNCH_CHECK(ctx);
-    lp->dirty = lp->fold_dirty = true;
+    lp->dirty = false;                          // every weight's bf16 copy has just been written
+    lp->fold_dirty = true;
     return SEM_OK;
 }
 
@@ -1426,14 +1675,17 @@ extern "C" int sem_lp_train_step(sem_lp_t lp, const uint16_t* X, const float* T,
         return sem::fail(ctx, SEM_EINVAL, "sem_lp_train_step: bad batch (%lld)", (long long)B);
     rc = lp_train_buffers(lp, (int)B);
     if (rc) return rc;
-    gather_rows<<<(unsigned)B, 256, 0, ctx->stream>>>(lp->X, lp->T, X, T, rows, (int)B, lp->nip, lp->no);
-    SEM_LAUNCH_CHECK(ctx);
-    rc = lp_backward(lp, lp->X, lp->T, (int)B);
+    // the products read rows[] of X and T in place, 16 bytes of a feature row at a
+    // time; features that do not lie on 16 bytes are copied into rows that do
+    const u16* Xb = X;
+    if (reinterpret_cast<uintptr_t>(X) % 16) {
+        gather_rows<<<(unsigned)B, 256, 0, ctx->stream>>>(lp->X, X, rows, (int)B, lp->nip);
+        SEM_LAUNCH_CHECK(ctx);
+        Xb = lp->X;
+    }
+    rc = lp_backward(lp, Xb, T, rows, Xb == X, (int)B, loss);
     if (rc) return rc;
-    rc = sem_lp_adam(lp, lr, 0.9, 0.999, 1e-8);
-    if (rc) return rc;
-    if (loss) SEM_HIP(ctx, hipMemcpyAsync(loss, lp->loss, 4, hipMemcpyDeviceToDevice, ctx->stream));
-    return SEM_OK;
+    return sem_lp_adam(lp, lr, 0.9, 0.999, 1e-8);
 }
 
 namespace sem {
