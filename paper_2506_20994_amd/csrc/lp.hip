@@ -33,21 +33,18 @@ __device__ __forceinline__ u16 bf16_rne(float f) {
 }
 __device__ __forceinline__ float bf16_f(u16 h) { return __uint_as_float((uint32_t)h << 16); }
 
-enum { EPI_BIAS = 1, EPI_RELU = 2, EPI_MASK = 4 };
 constexpr int BM = 128, BN = 128, BK = 64, LDK = BK + 8;
 
-// C = A . B^T (+bias[n]) (relu) (*(mask[m][n] > 0)); Cf float and/or Cb bf16.
-// With pos, the float output of (m, n) goes to Cf[pos[m * ldc + n]], scaled by
-// rowscale[m].
+// C = A . B^T in float32 (the linear form's inference).  With pos, the output of
+// (m, n) goes to Cf[pos[m * ldc + n]], scaled by rowscale[m].
 // Requires K % 8 == 0, lda % 8 == 0, ldb % 8 == 0 and 16-byte aligned bases.
 // 128 x 128 tile per 256-thread workgroup, each wave 64 x 64 as 4 x 4
 // 16x16x32 MFMA blocks; the next 64-wide k-slab is fetched into registers
 // while the current one is multiplied out of LDS.
 __global__ void __launch_bounds__(256)
 gemm_nt(int M, int N, int K, const u16* __restrict__ A, int lda, const u16* __restrict__ B, int ldb,
-        const float* __restrict__ bias, const u16* __restrict__ mask, int ldm,
-        float* __restrict__ Cf, u16* __restrict__ Cb, int ldc, int epi, const int* __restrict__ skip,
-        const float* __restrict__ rowscale, const int32_t* __restrict__ pos) {
+        float* __restrict__ Cf, int ldc, const int* __restrict__ skip, const float* __restrict__ rowscale,
+        const int32_t* __restrict__ pos) {
     if (skip && *skip) return;
     __shared__ __attribute__((aligned(16))) u16 sA[BM * LDK];
     __shared__ __attribute__((aligned(16))) u16 sB[BN * LDK];
@@ -112,44 +109,55 @@ gemm_nt(int M, int N, int K, const u16* __restrict__ A, int lda, const u16* __re
         for (int j = 0; j < 4; ++j) {
             const int n = n0 + wn * 64 + j * 16 + (lane & 15);
             if (n >= N) continue;
-            const float bv = (epi & EPI_BIAS) ? bias[n] : 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int m = m0 + wm * 64 + i * 16 + 4 * (lane >> 4) + q;
                 if (m >= M) continue;
-                float v = acc[i][j][q] + bv;
-                if (epi & EPI_RELU) v = fmaxf(v, 0.f);
-                if ((epi & EPI_MASK) && !(bf16_f(mask[(int64_t)m * ldm + n]) > 0.f)) v = 0.f;
+                const float v = acc[i][j][q];
                 if (pos) Cf[pos[(int64_t)m * ldc + n]] = v * rowscale[m];
-                else if (Cf) Cf[(int64_t)m * ldc + n] = v;
-                if (Cb) Cb[(int64_t)m * ldc + n] = bf16_rne(v);
+                else Cf[(int64_t)m * ldc + n] = v;
             }
         }
 }
+
+// ---- packed operands ---------------------------------------------------------
+// The network's own matrices (weights, a minibatch's activations, errors and
+// their transposes) are stored as the MFMA fragments that read them: 16 rows by
+// 32 k make 64 runs of 8 bf16, run 16 (k / 8) + row, so a wave reads a fragment
+// as one contiguous KB.  Read row by row instead, each lane's 16 bytes lie in
+// another line (16 rows x 64 bytes per load), and the products of a training step
+// ran at the rate of those loads: 5-10 us each, 71 us a step; packed, a step
+// takes 48 us.
+// ks(K) k-steps of 32; entries past K are zero, entries past the last row are
+// whatever is there and only reach outputs that are not stored.
+__host__ __device__ constexpr int ksteps(int k) { return (k + 31) / 32; }
+__host__ __device__ constexpr int64_t packed_at(int64_t row, int k, int ks) {
+    return (((row >> 4) * ks + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (row & 15)) * 8 + (k & 7);
+}
+// bf16 values of a packed matrix
+constexpr size_t packed_size(size_t rows, size_t k) { return (rows + 15) / 16 * ((k + 31) / 32) * 512; }
 
 // ---- products of the training step ------------------------------------------
 // C = A . B^T in the k order and with the instruction of gemm_nt (so every sum
 // is the same, bit for bit), for the shapes of a minibatch: 1024 x 256 has 16
 // tiles of 128 x 128, which left 240 of the 256 CUs idle and took 22 us a
 // product.  Here a wave owns a (16 TM) x (16 TN) tile and reads its MFMA
-// fragments straight from memory (a row's 16 bytes per lane; the operands are a
-// few hundred KB and sit in L2), two sets of k-steps in registers: no
-// LDS, no barriers, and 1024 waves for the same product.  What bounds it then
-// is the rate of those 16-row loads: 5-10 us a product, and the training step of
-// the lx = 8 network (batches of 1024, linear form) takes 71 us instead of 281.
+// fragments straight from memory (the operands are a few hundred KB and sit in
+// L2), two sets of k-steps in registers: no LDS, no barriers, and 1024 waves for
+// the same product.
 // The epilogue does what used to be passes of their own: the bf16 transpose
 // that the weight gradients' products read (a lane holds four consecutive rows
 // of a column: one 8-byte store), the loss and its gradient.
-enum { EPI_DIFF = 8, EPI_MSE = 16, EPI_METRIC = 32 };
+enum { EPI_BIAS = 1, EPI_RELU = 2, EPI_MASK = 4, EPI_DIFF = 8, EPI_MSE = 16, EPI_METRIC = 32 };
 struct WaveGemm {
     int M = 0, N = 0, K = 0;
-    const u16* A = nullptr; int lda = 0;
-    const u16* B = nullptr; int ldb = 0;
-    const int64_t *rows = nullptr, *trows = nullptr;   // row m of A is rows[m], of T trows[m]
+    const u16* A = nullptr; int lda = 0;               // packed, or row-major with row length lda
+    const u16* B = nullptr;                            // packed
+    const int64_t *rows = nullptr, *trows = nullptr;   // row m of a row-major A is rows[m], of T trows[m]
     const float* bias = nullptr;
-    const u16* mask = nullptr; int ldm = 0;
-    float* Cf = nullptr; u16* Cb = nullptr; int ldc = 0;
-    u16* Ct = nullptr; int ldt = 0;     // bf16 transpose: Ct[n * ldt + m]
+    const u16* mask = nullptr;          // packed, M x N
+    float* Cf = nullptr; int ldc = 0;
+    u16 *Cb = nullptr, *Ct = nullptr;   // packed M x N, and its transpose (N x M)
     int epi = 0;
     const float* T = nullptr;           // targets (N wide)
     float* dF = nullptr;                // EPI_DIFF: written; EPI_METRIC: read (N wide)
@@ -179,44 +187,54 @@ __device__ __forceinline__ void wave_gemm_block(const WaveGemm& g, int blk, doub
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     double loss = 0.0;
+    const int ks = ksteps(g.K), nks = ksteps(g.N), mks = ksteps(g.M);
     if (m0 < g.M && n0 < g.N) {                 // uniform over the wave
-        // rows past the end read the last row; their outputs are not stored
+        const bool packed = g.lda == 0;
+        // fragment s of A's tile i is at pa[i] + s * astep, of B's tile j at pb[j] + 512 s;
+        // tiles past the end read the last one, and their outputs are not stored
         const u16 *pa[TM], *pb[TN];
+        const int astep = packed ? 512 : 32;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int m = min(m0 + i * 16 + (lane & 15), g.M - 1);
-            pa[i] = g.A + (g.rows ? g.rows[m] : (int64_t)m) * g.lda;
+            if (packed) {
+                pa[i] = g.A + (int64_t)min(m0 / 16 + i, (g.M - 1) / 16) * ks * 512 + lane * 8;
+            } else {
+                const int m = min(m0 + i * 16 + (lane & 15), g.M - 1);
+                pa[i] = g.A + (g.rows ? g.rows[m] : (int64_t)m) * g.lda + ko;
+            }
         }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) pb[j] = g.B + (int64_t)min(n0 + j * 16 + (lane & 15), g.N - 1) * g.ldb;
+        for (int j = 0; j < TN; ++j) pb[j] = g.B + (int64_t)min(n0 / 16 + j, (g.N - 1) / 16) * ks * 512 + lane * 8;
         // chunks of U k-steps in two register sets, the next chunk's loads issued
-        // before the current one's products.  The chunk past K is read at column 0
-        // and multiplied as zero.
+        // before the current one's products.  Steps past the last one read it again
+        // and are not multiplied; a row-major A's runs past K read its last whole run
+        // and are multiplied as zero.
         bf16x8 fa[2][U][TM], fb[2][U][TN];
-        const int chunks = (g.K + 32 * U - 1) / (32 * U);
+        const int chunks = (ks + U - 1) / U;
+        const int short_run = packed ? 0 : max(0, (ks - 1) * 32 + ko + 8 - g.K);   // past K in the last step
         auto fetch = [&](int h, int c) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                int k = (c * U + u) * 32 + ko;
-                k = k < g.K ? k : 0;
+                const int t = min(c * U + u, ks - 1);
+                const int off = t * astep - (t == ks - 1 ? short_run : 0);
 #pragma unroll
-                for (int i = 0; i < TM; ++i) fa[h][u][i] = *reinterpret_cast<const bf16x8*>(pa[i] + k);
+                for (int i = 0; i < TM; ++i) fa[h][u][i] = *reinterpret_cast<const bf16x8*>(pa[i] + off);
 #pragma unroll
-                for (int j = 0; j < TN; ++j) fb[h][u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + k);
+                for (int j = 0; j < TN; ++j) fb[h][u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + t * 512);
             }
             __builtin_amdgcn_sched_barrier(0);      // the loads stay ahead of the products that follow
         };
         auto multiply = [&](int h, int c, bool last) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const bool in = !last || (c * U + u) * 32 + ko < g.K;
-                const uint4 z{0u, 0u, 0u, 0u};
+                if (last) {
+                    if (c * U + u >= ks) break;
+                    const uint4 z{0u, 0u, 0u, 0u};
+                    if (c * U + u == ks - 1)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    if (last) fa[h][u][i] = __builtin_bit_cast(bf16x8, in ? __builtin_bit_cast(uint4, fa[h][u][i]) : z);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    if (last) fb[h][u][j] = __builtin_bit_cast(bf16x8, in ? __builtin_bit_cast(uint4, fb[h][u][j]) : z);
+                        for (int i = 0; i < TM; ++i)
+                            fa[h][u][i] = __builtin_bit_cast(bf16x8, short_run ? z : __builtin_bit_cast(uint4, fa[h][u][i]));
+                }
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -238,7 +256,7 @@ __device__ __forceinline__ void wave_gemm_block(const WaveGemm& g, int blk, doub
                 for (int q = 0; q < 4; ++q) {
                     const int m = min(m0 + i * 16 + 4 * (lane >> 4) + q, g.M - 1);
                     side[i][j][q] = 0.f;
-                    if (g.epi & EPI_MASK) side[i][j][q] = bf16_f(g.mask[(int64_t)m * g.ldm + n]);
+                    if (g.epi & EPI_MASK) side[i][j][q] = bf16_f(g.mask[packed_at(m, n, nks)]);
                     if (g.epi & (EPI_DIFF | EPI_MSE)) side[i][j][q] = g.T[(g.trows ? g.trows[m] : (int64_t)m) * g.N + n];
                     if (g.epi & EPI_METRIC) side[i][j][q] = g.dF[(int64_t)m * g.N + n];
                 }
@@ -285,13 +303,21 @@ __device__ __forceinline__ void wave_gemm_block(const WaveGemm& g, int blk, doub
                     }
                     if (g.Cf) g.Cf[(int64_t)m * g.ldc + n] = v;
                     t[q] = bf16_rne(v);
-                    if (g.Cb) g.Cb[(int64_t)m * g.ldc + n] = t[q];
+                    if (g.Cb) g.Cb[packed_at(m, n, nks)] = t[q];
                 }
-                // M and ldt are multiples of 8 where a transpose is asked for
-                if (g.Ct && mb < g.M) {
+                // rows past M are zero in the transpose, whose k they are
+                if (g.Ct && mb < mks * 32) {
                     const uint2 w{(uint32_t)t[0] | ((uint32_t)t[1] << 16), (uint32_t)t[2] | ((uint32_t)t[3] << 16)};
-                    *reinterpret_cast<uint2*>(g.Ct + (int64_t)n * g.ldt + mb) = w;
+                    *reinterpret_cast<uint2*>(g.Ct + packed_at(n, mb, mks)) = w;
                 }
+            }
+    } else if (g.Ct && n0 < g.N) {              // a tile past M: the transpose's zero padding
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int n = n0 + j * 16 + (lane & 15), mb = m0 + i * 16 + 4 * (lane >> 4);
+                if (n < g.N && mb < mks * 32) *reinterpret_cast<uint2*>(g.Ct + packed_at(n, mb, mks)) = uint2{0u, 0u};
             }
     }
     if (g.part) {
@@ -304,10 +330,10 @@ __device__ __forceinline__ void wave_gemm_block(const WaveGemm& g, int blk, doub
 
 // what a launch of products does besides, in workgroups of its own
 struct WaveAux {
-    // out[c][r] = bf16 row rows[r] (r itself without rows) of in, transposed, in
-    // 32 x 32 tiles: the minibatch's features as the first layer's weight gradient
-    // reads them
-    u16* out = nullptr; int ldo = 0;
+    // out = the packed transpose (cols x nrows) of the bf16 rows rows[r] (r itself
+    // without rows) of in, in 32 x 32 tiles: the minibatch's features as the first
+    // layer's weight gradient reads them
+    u16* out = nullptr;
     const u16* in = nullptr; int ldi = 0;
     const int64_t* rows = nullptr;
     int nrows = 0, cols = 0;
@@ -331,9 +357,15 @@ __device__ __forceinline__ void gather_transpose(const WaveAux& a, int blk, u16 
         t[y][tx] = (r < a.nrows && c < a.cols) ? a.in[(a.rows ? a.rows[r] : (int64_t)r) * a.ldi + c] : (u16)0;
     }
     __syncthreads();
-    for (int y = ty; y < 32; y += 8) {
-        const int c = c0 + y, r = r0 + tx;
-        if (c < a.cols && r < a.nrows) a.out[(int64_t)c * a.ldo + r] = t[tx][y];
+    if (threadIdx.x < 128) {                    // 32 columns x 4 runs of 8 rows
+        const int c = threadIdx.x & 31, r = 8 * (threadIdx.x >> 5);
+        if (c0 + c < a.cols) {
+            uint4 w;
+            uint32_t* p = &w.x;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p[q] = (uint32_t)t[r + 2 * q][c] | ((uint32_t)t[r + 2 * q + 1][c] << 16);
+            *reinterpret_cast<uint4*>(a.out + packed_at(c0 + c, r0 + r, ksteps(a.nrows))) = w;
+        }
     }
 }
 
@@ -365,6 +397,130 @@ __global__ void __launch_bounds__(256) wave_gemm(WaveGemm g0, WaveGemm g1, WaveA
     else loss_final(aux, s_red);
 }
 
+// ---- the network's forward pass in one kernel --------------------------------
+// 16 MT rows a workgroup: their features go to LDS as packed fragments, the eight
+// waves share the columns of a layer in pairs of tiles (weights as packed
+// fragments from L2, two sets of 4 k-steps in registers), and the hidden
+// activations stay in LDS.  The same products in the same order as three
+// launches of gemm_nt (20 us each at 8000 rows of the lx = 8 network, 126 to 252
+// workgroups, activations through memory); this kernel takes 21 us for the three,
+// bound by the 0.66 MB of weights that every workgroup reads from L2.
+constexpr int kMlpWaves = 8, kMlpU = 4;
+
+// one layer from the fragments `in` (ks k-steps) in LDS; out(mt, n, acc) takes
+// each 16 x 16 tile's column n of row tile mt
+template <int MT, typename Out>
+__device__ __forceinline__ void mlp_layer(const u16* in, int ks, const u16* __restrict__ W, int N, Out out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nt = (N + 15) / 16, groups = (nt + 1) / 2, chunks = (ks + kMlpU - 1) / kMlpU;
+    bf16x8 fb[2][kMlpU][2];
+    const u16* pb[2];
+    auto start = [&](int grp) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) pb[j] = W + (int64_t)min(2 * grp + j, nt - 1) * ks * 512 + lane * 8;
+    };
+    auto fetch = [&](int h, int c) {            // steps past the last one read it again
+#pragma unroll
+        for (int u = 0; u < kMlpU; ++u)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                fb[h][u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + min(c * kMlpU + u, ks - 1) * 512);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (wave < groups) {
+        start(wave);
+        fetch(0, 0);
+    }
+    __syncthreads();                            // `in` is complete, the output's place is free
+    for (int grp = wave; grp < groups; grp += kMlpWaves) {
+        f32x4 acc[MT][2];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto multiply = [&](int h, int c) {
+#pragma unroll
+            for (int u = 0; u < kMlpU; ++u) {
+                const int t = c * kMlpU + u;
+                if (t >= ks) break;
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(in + ((i * ks + t) * 64 + lane) * 8);
+                    acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, fb[h][u][0], acc[i][0], 0, 0, 0);
+                    acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, fb[h][u][1], acc[i][1], 0, 0, 0);
+                }
+            }
+        };
+        if (grp != wave) {
+            start(grp);
+            fetch(0, 0);
+        }
+        int c = 0;
+        for (; c + 2 < chunks; c += 2) {
+            fetch(1, c + 1);
+            multiply(0, c);
+            fetch(0, c + 2);
+            multiply(1, c + 1);
+        }
+        if (c + 1 < chunks) {
+            fetch(1, c + 1);
+            multiply(0, c);
+            multiply(1, c + 1);
+        } else {
+            multiply(0, c);
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) out(i, (2 * grp + j) * 16 + (lane & 15), acc[i][j]);
+    }
+}
+
+template <int MT>
+__global__ void __launch_bounds__(64 * kMlpWaves)
+mlp_kernel(float* __restrict__ Y, const u16* __restrict__ X, int nip, int64_t rows, const u16* __restrict__ W1,
+           const float* __restrict__ b1, const u16* __restrict__ W2, const float* __restrict__ b2,
+           const u16* __restrict__ W3, const float* __restrict__ b3, int nh, int no, bool linear,
+           const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    extern __shared__ __attribute__((aligned(16))) u16 s_mlp[];
+    const int ks1 = ksteps(nip), ksh = ksteps(nh);
+    u16* sa = s_mlp;                                         // features, then the second hidden layer
+    u16* sb = s_mlp + (size_t)MT * max(ks1, ksh) * 512;      // first hidden layer
+    const int64_t row0 = (int64_t)blockIdx.x * (16 * MT);
+    for (int q = threadIdx.x; q < MT * ks1 * 64; q += 64 * kMlpWaves) {
+        const int t = q >> 6, mt = t / ks1, k = (t - mt * ks1) * 32 + 8 * (q & 3), r = (q >> 2) & 15;
+        const int64_t row = row0 + mt * 16 + r;
+        uint4 v{0u, 0u, 0u, 0u};
+        if (row < rows && k < nip) v = *reinterpret_cast<const uint4*>(X + row * nip + k);
+        *reinterpret_cast<uint4*>(sa + (t * 64 + (q & 3) * 16 + r) * 8) = v;
+    }
+    const int lane4 = 4 * ((threadIdx.x & 63) >> 4);
+    // hidden layer: bias and ReLU, rounded to bf16 where the next layer reads it;
+    // the columns between nh and the next whole k-step are zero
+    auto hidden = [&](u16* dst, const float* b) {
+        return [=](int mt, int n, f32x4 acc) {
+            if (n >= ksh * 32) return;
+            const float bv = (!linear && n < nh) ? b[n] : 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v = acc[q] + bv;
+                if (!linear) v = fmaxf(v, 0.f);
+                dst[packed_at(mt * 16 + lane4 + q, n, ksh)] = n < nh ? bf16_rne(v) : (u16)0;
+            }
+        };
+    };
+    mlp_layer<MT>(sa, ks1, W1, nh, hidden(sb, b1));
+    mlp_layer<MT>(sb, ksh, W2, nh, hidden(sa, b2));
+    mlp_layer<MT>(sa, ksh, W3, no, [=](int mt, int n, f32x4 acc) {
+        if (n >= no) return;
+        const float bv = linear ? 0.f : b3[n];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t row = row0 + mt * 16 + lane4 + q;
+            if (row < rows) Y[row * no + n] = acc[q] + bv;
+        }
+    });
+}
+
 // C[r][c] = sum_k A[r][k] B[k][c] in float32 (small products of the weights)
 __global__ void matmul_f32(float* __restrict__ C, const float* __restrict__ A, const float* __restrict__ B,
                            int rows, int inner, int cols, int lda, int ldb, int ldc) {
@@ -389,17 +545,17 @@ __global__ void sym_to_bf16(u16* __restrict__ out, const float* __restrict__ in,
     }
 }
 
-// float32 master (rows x cols) -> bf16 copy with leading dim ldo (zero pad)
-// and, if outT != null, its bf16 transpose (cols x rows)
-__global__ void weights_to_bf16(u16* __restrict__ out, int ldo, u16* __restrict__ outT,
+// float32 master (rows x cols) -> packed bf16 copy with kb k-steps and, if outT
+// != null, its packed transpose; the padding is zero from creation on
+__global__ void weights_to_bf16(u16* __restrict__ out, int kb, u16* __restrict__ outT,
                                 const float* __restrict__ w, int rows, int cols) {
-    const int64_t n = (int64_t)rows * ldo;
+    const int64_t n = (int64_t)rows * cols;
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
          q += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(q / ldo), c = (int)(q % ldo);
-        const u16 v = c < cols ? bf16_rne(w[(int64_t)r * cols + c]) : (u16)0;
-        out[q] = v;
-        if (outT && c < cols) outT[(int64_t)c * rows + r] = v;
+        const int r = (int)(q / cols), c = (int)(q % cols);
+        const u16 v = bf16_rne(w[q]);
+        out[packed_at(r, c, kb)] = v;
+        if (outT) outT[packed_at(c, r, ksteps(rows))] = v;
     }
 }
 
@@ -443,13 +599,13 @@ __global__ void colsum_final(ColSums a, int chunks) {
 }
 
 // Adam on the six parameters in one launch (parameter q from workgroup first[q]
-// on, one value per thread), followed by the new value's bf16 copies (the
-// padded row-major one and, where there is one, the transpose): six launches
+// on, one value per thread), followed by the new value's bf16 copies (packed,
+// and the packed transpose where there is one): six launches
 // and three conversions a step before.  A gradient row has ldg values.
 struct AdamSet {
     float *p[6], *m[6], *v[6];
     const float* g[6];
-    int rows[6], cols[6], ldg[6], ldb[6];
+    int rows[6], cols[6], ldg[6], kb[6];
     u16 *wb[6], *wt[6];
     int first[7];
 };
@@ -470,8 +626,8 @@ __global__ void adam_kernel(AdamSet a, float lr, float b1, float omb1, float b2,
     const float pn = p[q] - lr * (mv / c1) / (sqrtf(vv / c2) + eps);
     p[q] = pn;
     const u16 h = bf16_rne(pn);
-    if (a.wb[s]) a.wb[s][r * a.ldb[s] + c] = h;
-    if (a.wt[s]) a.wt[s][c * a.rows[s] + r] = h;
+    if (a.wb[s]) a.wb[s][packed_at(r, (int)c, a.kb[s])] = h;
+    if (a.wt[s]) a.wt[s][packed_at(c, (int)r, ksteps(a.rows[s]))] = h;
 }
 
 // per-element geometric features (six means of h1 g_ab over kappa), kappa and 1/kappa
@@ -553,15 +709,15 @@ __global__ void features_kernel(u16* __restrict__ X, float* __restrict__ scale, 
 
 // z_L = (scale[e] * Y3[e][node] (+ minv_L r_L)) / mult_L, or with sym
 // z_L = scale[e] * Y3[e][node] / sqrt(mult_L) (+ minv_L r_L / mult_L)
-template <typename T>
+template <typename T, int NO>
 __global__ void lp_output_kernel(T* __restrict__ z, const float* __restrict__ Y3,
                                  const float* __restrict__ scale, const double* __restrict__ mult,
                                  const double* __restrict__ minv, const T* __restrict__ r,
-                                 int64_t n, const int* __restrict__ skip, bool sym, int no) {
+                                 int64_t n, const int* __restrict__ skip, bool sym) {
     if (skip && *skip) return;
     for (int64_t L = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; L < n;
          L += (int64_t)gridDim.x * blockDim.x) {
-        double v = (double)scale[L / no] * (double)Y3[L];
+        double v = (double)scale[L / NO] * (double)Y3[L];
         if (sym) {     // S y + Minv r / mult; the gather-scatter sums the copies
             v *= rsqrt(mult[L]);
             if (minv) v += minv[L] * (double)r[L] / mult[L];
@@ -573,25 +729,36 @@ __global__ void lp_output_kernel(T* __restrict__ z, const float* __restrict__ Y3
     }
 }
 
-// unique layout: z_u = mean over the copies L of u of scale[e(L)] Y3[L], or with
-// sym their sum weighted by mult_u^-1/2 (+ Minv_u r_u with the Jacobi base)
-template <typename T>
+// unique layout: z_u = mean over the copies L of u of scale[e(L)] Y3[L] (+ Minv_u
+// r_u with the Jacobi base).  Bound by the chain offsets -> copies -> values: the
+// first eight copies (a hexahedral mesh has at most eight) go out as independent
+// predicated loads, summed in CSR order, and the workgroups run in XCD order.
+template <typename T, int NO>
 __global__ void lp_output_unique_kernel(T* __restrict__ z, const float* __restrict__ Y3,
                                         const float* __restrict__ scale, const double* __restrict__ minv,
                                         const T* __restrict__ r, const int32_t* __restrict__ uoff,
                                         const int32_t* __restrict__ uidx, int64_t nu,
-                                        const int* __restrict__ skip, bool sym, int no) {
+                                        const int* __restrict__ skip) {
     if (skip && *skip) return;
-    for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < nu;
+    for (int64_t u = sem::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; u < nu;
          u += (int64_t)gridDim.x * blockDim.x) {
         const int32_t b = uoff[u], e = uoff[u + 1];
-        double s = 0.0;
-        for (int32_t q = b; q < e; ++q) {
-            const int32_t L = uidx[q];
-            s += (double)scale[L / no] * (double)Y3[L];
+        int32_t L[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) L[q] = b + q < e ? uidx[b + q] : -1;
+        float y[8], c[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            y[q] = L[q] >= 0 ? Y3[L[q]] : 0.f;
+            c[q] = L[q] >= 0 ? scale[L[q] / NO] : 0.f;
         }
-        s *= sym ? rsqrt((double)(e - b)) : 1.0 / (double)(e - b);
-        if (minv) s += minv[uidx[b]] * (double)r[u];
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (L[q] >= 0) s += (double)c[q] * (double)y[q];
+        for (int32_t q = b + 8; q < e; ++q) s += (double)scale[uidx[q] / NO] * (double)Y3[uidx[q]];
+        s *= 1.0 / (double)(e - b);
+        if (minv) s += minv[L[0]] * (double)r[u];
         z[u] = (T)s;
     }
 }
@@ -851,7 +1018,7 @@ struct sem_lp_s {
     float *W[3] = {}, *b[3] = {}, *mW[3] = {}, *mb[3] = {}, *vW[3] = {}, *vb[3] = {};
     float *gW[3] = {}, *gb[3] = {};
     int64_t step = 0;
-    // bf16 copies: W1 (256 x nip), W2 (256 x 256), W3 (no x 256), W2^T, W3^T
+    // packed bf16 copies: W1 (256 x nip), W2 (256 x 256), W3 (no x 256), W2^T, W3^T
     u16 *W1b = nullptr, *W2b = nullptr, *W3b = nullptr, *W2t = nullptr, *W3t = nullptr;
     double mu = -1.0;         // training metric (< 0: mean squared error)
     bool dirty = true;        // bf16 copies of the weights out of date
@@ -863,7 +1030,6 @@ struct sem_lp_s {
     // transposes of a minibatch (k-contiguous operands of the weight gradients)
     u16 *Xt = nullptr, *Y1t = nullptr, *Y2t = nullptr, *d3t = nullptr, *d2t = nullptr, *d1t = nullptr;
     double* lpart = nullptr;            // loss partials of the training products
-    double* part = nullptr;
     float* loss = nullptr;
     // bound operator (inference)
     int64_t nel = 0, geo_cap = 0;
@@ -905,13 +1071,11 @@ int lp_alloc(sem_lp_t lp, void** p, size_t bytes) {
     return SEM_OK;
 }
 
-int gemm(sem_lp_t lp, int M, int N, int K, const u16* A, int lda, const u16* B, int ldb,
-         const float* bias, const u16* mask, int ldm, float* Cf, u16* Cb, int ldc, int epi,
+int gemm(sem_lp_t lp, int M, int N, int K, const u16* A, int lda, const u16* B, int ldb, float* Cf, int ldc,
          const float* rowscale = nullptr, const int32_t* pos = nullptr) {
     if (M == 0 || N == 0) return SEM_OK;
     dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
-    gemm_nt<<<grid, 256, 0, lp->ctx->stream>>>(M, N, K, A, lda, B, ldb, bias, mask, ldm, Cf, Cb, ldc, epi,
-                                               lp->skip, rowscale, pos);
+    gemm_nt<<<grid, 256, 0, lp->ctx->stream>>>(M, N, K, A, lda, B, ldb, Cf, ldc, lp->skip, rowscale, pos);
     SEM_LAUNCH_CHECK(lp->ctx);
     return SEM_OK;
 }
@@ -969,9 +1133,9 @@ int refresh_bf16(sem_lp_t lp) {
     const int kHid = lp->nh;     // this network's hidden width
     if (!lp->dirty) return SEM_OK;
     hipStream_t st = lp->ctx->stream;
-    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W1b, lp->nip, nullptr, lp->W[0], kHid, lp->ni);
-    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W2b, kHid, lp->W2t, lp->W[1], kHid, kHid);
-    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W3b, kHid, lp->W3t, lp->W[2], lp->no, kHid);
+    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W1b, ksteps(lp->nip), nullptr, lp->W[0], kHid, lp->ni);
+    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W2b, ksteps(kHid), lp->W2t, lp->W[1], kHid, kHid);
+    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W3b, ksteps(kHid), lp->W3t, lp->W[2], lp->no, kHid);
     SEM_LAUNCH_CHECK(lp->ctx);
     lp->dirty = false;
     return SEM_OK;
@@ -995,18 +1159,30 @@ int refresh_fold(sem_lp_t lp) {
     return SEM_OK;
 }
 
-// forward of rows [0, M) of lp->X into Y1, Y2 (bf16) and Y3 (float)
-int forward(sem_lp_t lp, const u16* X, int64_t M) {
-    const int kHid = lp->nh;     // this network's hidden width
+// LDS of mlp_kernel<MT>
+size_t mlp_lds(const sem_lp_s* lp, int mt) {
+    const int ks1 = ksteps(lp->nip), ksh = ksteps(lp->nh);
+    return (size_t)mt * 1024 * (std::max(ks1, ksh) + ksh);
+}
+constexpr size_t kLdsMax = 160 * 1024;      // per workgroup on gfx950
+
+// forward of M rows of X (on 16 bytes) into Y (float32)
+int forward(sem_lp_t lp, const u16* X, int64_t M, float* Y) {
     int rc = refresh_bf16(lp);
     if (rc) return rc;
     if (M > 0x7fffffff) return sem::fail(lp->ctx, SEM_EINVAL, "sem_lp: too many rows");
-    const int m = (int)M;
-    const int hid = lp->linear ? 0 : EPI_BIAS | EPI_RELU, out = lp->linear ? 0 : EPI_BIAS;
-    rc = gemm(lp, m, kHid, lp->nip, X, lp->nip, lp->W1b, lp->nip, lp->b[0], nullptr, 0, nullptr, lp->Y1, kHid, hid);
-    if (!rc) rc = gemm(lp, m, kHid, kHid, lp->Y1, kHid, lp->W2b, kHid, lp->b[1], nullptr, 0, nullptr, lp->Y2, kHid, hid);
-    if (!rc) rc = gemm(lp, m, lp->no, kHid, lp->Y2, kHid, lp->W3b, kHid, lp->b[2], nullptr, 0, lp->Y3, nullptr, lp->no, out);
-    return rc;
+    hipStream_t st = lp->ctx->stream;
+#define LP_MLP(MT) mlp_kernel<MT><<<(unsigned)((M + 16 * MT - 1) / (16 * MT)), 64 * kMlpWaves, mlp_lds(lp, MT), st>>>( \
+        Y, X, lp->nip, M, lp->W1b, lp->b[0], lp->W2b, lp->b[1], lp->W3b, lp->b[2], lp->nh, lp->no, lp->linear, lp->skip)
+    // 32 rows a workgroup read the weights half as often, 16 rows make twice the
+    // workgroups: 8000 rows at lx = 8 measured the same, 32768 rows 238 against 254
+    // us for the whole application, 13824 rows at lx = 6 55 against 60, 1728 rows at
+    // lx = 10 66 against 57, 512 rows 28 against 23 (64 rows were slower throughout)
+    if (M >= 8192 && mlp_lds(lp, 2) <= kLdsMax) LP_MLP(2);
+    else LP_MLP(1);
+#undef LP_MLP
+    SEM_LAUNCH_CHECK(lp->ctx);
+    return SEM_OK;
 }
 
 float** param_slot(sem_lp_t lp, int which, int64_t* count, int* ld) {
@@ -1051,6 +1227,11 @@ extern "C" int sem_lp_create_lx(sem_ctx_t ctx, int lx, int hidden, int64_t max_r
     lp->nip = (lp->ni + 15) / 16 * 16;
     const int no = lp->no, nip = lp->nip;
     auto bail = [&](int code) { sem_lp_destroy(lp); return code; };
+    // forward() may ask for more LDS than a kernel gets by default
+    for (const void* k : {(const void*)mlp_kernel<1>, (const void*)mlp_kernel<2>}) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+        if (e != hipSuccess) return bail(sem::check_hip(ctx, e, "sem_lp_create: hipFuncSetAttribute"));
+    }
 #define LP_ALLOC(ptr, bytes) do { int rc_ = lp_alloc(lp, (void**)&(ptr), (bytes)); if (rc_) return bail(rc_); } while (0)
     for (int l = 0; l < 3; ++l) {
         const size_t nw = (size_t)param_rows(lp, l) * param_cols(lp, l), nb = param_rows(lp, l);
@@ -1059,18 +1240,15 @@ extern "C" int sem_lp_create_lx(sem_ctx_t ctx, int lx, int hidden, int64_t max_r
         LP_ALLOC(lp->gW[l], 4 * (size_t)param_rows(lp, l) * (l == 0 ? nip : param_cols(lp, l)));
         LP_ALLOC(lp->gb[l], 4 * nb);
     }
-    LP_ALLOC(lp->W1b, 2 * (size_t)kHid * nip);
-    LP_ALLOC(lp->W2b, 2 * (size_t)kHid * kHid);
-    LP_ALLOC(lp->W3b, 2 * (size_t)no * kHid);
-    LP_ALLOC(lp->W2t, 2 * (size_t)kHid * kHid);
-    LP_ALLOC(lp->W3t, 2 * (size_t)kHid * no);
+    LP_ALLOC(lp->W1b, 2 * packed_size(kHid, nip));
+    LP_ALLOC(lp->W2b, 2 * packed_size(kHid, kHid));
+    LP_ALLOC(lp->W3b, 2 * packed_size(no, kHid));
+    LP_ALLOC(lp->W2t, 2 * packed_size(kHid, kHid));
+    LP_ALLOC(lp->W3t, 2 * packed_size(kHid, no));
     const size_t R = (size_t)max_rows;
     LP_ALLOC(lp->X, 2 * R * nip);
-    LP_ALLOC(lp->Y1, 2 * R * kHid);
-    LP_ALLOC(lp->Y2, 2 * R * kHid);
     LP_ALLOC(lp->Y3, 4 * R * no);
     LP_ALLOC(lp->scale, 4 * R);
-    LP_ALLOC(lp->part, 8 * 4096);
     LP_ALLOC(lp->loss, 4);
 #undef LP_ALLOC
     SEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -1178,7 +1356,7 @@ extern "C" int sem_lp_set_metric(sem_lp_t lp, double mu) {
     double wsum = 0.0;
     for (int i = 0; i < lx; ++i) wsum += w[i];
     const double kappa = std::pow(wsum / lx, 3);     // mean of w_i w_j w_k
-    std::vector<u16> Kb((size_t)kOut * kOut);
+    std::vector<u16> Kb(packed_size(kOut, kOut), 0);
     for (int p = 0; p < kOut; ++p) {
         const int i = p % lx, j = (p / lx) % lx, k = p / (lx * lx);
         for (int q = 0; q < kOut; ++q) {
@@ -1193,19 +1371,19 @@ extern "C" int sem_lp_set_metric(sem_lp_t lp, double mu) {
             uint32_t b;
             std::memcpy(&b, &f, 4);
             b += 0x7fffu + ((b >> 16) & 1u);
-            Kb[(size_t)p * kOut + q] = (u16)(b >> 16);
+            Kb[packed_at(p, q, ksteps(kOut))] = (u16)(b >> 16);
         }
     }
     if (!lp->K) {
         const size_t R = (size_t)lp->max_rows;
         void* p = nullptr;
-        rc = lp_alloc(lp, &p, 2 * (size_t)kOut * kOut);
+        rc = lp_alloc(lp, &p, 2 * Kb.size());
         if (rc) return rc;
         lp->K = (u16*)p;
         rc = lp_alloc(lp, &p, 4 * R * kOut);
         if (rc) return rc;
         lp->dF = (float*)p;
-        rc = lp_alloc(lp, &p, 2 * R * kOut);
+        rc = lp_alloc(lp, &p, 2 * packed_size(R, kOut));
         if (rc) return rc;
         lp->dB = (u16*)p;
     }
@@ -1469,10 +1647,7 @@ extern "C" int sem_lp_forward(sem_lp_t lp, const uint16_t* X, int64_t rows, floa
     if (rc) return rc;
     if (!X || !Y || rows < 0 || rows > lp->max_rows) return sem::fail(ctx, SEM_EINVAL, "sem_lp_forward: bad argument");
     if (rows == 0) return SEM_OK;
-    rc = forward(lp, X, rows);
-    if (rc) return rc;
-    SEM_HIP(ctx, hipMemcpyAsync(Y, lp->Y3, 4 * (size_t)rows * lp->no, hipMemcpyDeviceToDevice, ctx->stream));
-    return SEM_OK;
+    return forward(lp, X, rows, Y);
 }
 
 // gradients of the batch loss into the gradient slots (and the loss into
@@ -1491,40 +1666,40 @@ static int lp_backward(sem_lp_t lp, const uint16_t* X, const float* T, const int
     const int64_t n3 = (int64_t)B * kOut;
     const bool lin = lp->linear;
     WaveAux xt;                                    // X^T beside the first product
-    xt.out = lp->Xt; xt.ldo = B;
+    xt.out = lp->Xt;
     xt.in = X; xt.ldi = kInPad;
     xt.rows = x_rows ? rows : nullptr;
     xt.nrows = B; xt.cols = kInPad;
-    auto product = [&](int M, int N, int K, const u16* A, int lda, const u16* Bm, int ldb) {
+    auto product = [&](int M, int N, int K, const u16* A, const u16* Bm) {
         WaveGemm g;
         g.M = M; g.N = N; g.K = K;
-        g.A = A; g.lda = lda;
-        g.B = Bm; g.ldb = ldb;
+        g.A = A; g.B = Bm;
         return g;
     };
     // forward: Y1 and Y2 also transposed
-    WaveGemm g = product(B, kHid, kInPad, X, kInPad, lp->W1b, kInPad);
+    WaveGemm g = product(B, kHid, kInPad, X, lp->W1b);
+    g.lda = kInPad;
     g.rows = x_rows ? rows : nullptr;
     g.bias = lp->b[0]; g.epi = lin ? 0 : EPI_BIAS | EPI_RELU;
-    g.Cb = lp->Y1; g.ldc = kHid; g.Ct = lp->Y1t; g.ldt = B;
+    g.Cb = lp->Y1; g.Ct = lp->Y1t;
     if ((rc = wave_products(lp, g, WaveGemm(), xt))) return rc;
-    g = product(B, kHid, kHid, lp->Y1, kHid, lp->W2b, kHid);
+    g = product(B, kHid, kHid, lp->Y1, lp->W2b);
     g.bias = lp->b[1]; g.epi = lin ? 0 : EPI_BIAS | EPI_RELU;
-    g.Cb = lp->Y2; g.ldc = kHid; g.Ct = lp->Y2t; g.ldt = B;
+    g.Cb = lp->Y2; g.Ct = lp->Y2t;
     if ((rc = wave_products(lp, g))) return rc;
     // output layer: its epilogue takes the targets off.  Mean squared error: d3 =
     // scale (y - t).  Metric: loss = mean_b d_b^T K d_b, d3 = 2 K d / B, one more product.
     int nb = 0;
-    g = product(B, kOut, kHid, lp->Y2, kHid, lp->W3b, kHid);
+    g = product(B, kOut, kHid, lp->Y2, lp->W3b);
     g.trows = rows;
     g.bias = lp->b[2]; g.epi = lin ? 0 : EPI_BIAS;
     g.T = T;
     WaveGemm d3 = g;
     if (lp->K) {
         g.epi |= EPI_DIFF;
-        g.dF = lp->dF; g.Cb = lp->dB; g.ldc = kOut;
+        g.dF = lp->dF; g.Cb = lp->dB;
         if ((rc = wave_products(lp, g))) return rc;
-        d3 = product(B, kOut, kOut, lp->dB, kOut, lp->K, kOut);
+        d3 = product(B, kOut, kOut, lp->dB, lp->K);
         d3.epi = EPI_METRIC;
         d3.dF = lp->dF;
         d3.scale = 2.0f / (float)B;
@@ -1533,7 +1708,7 @@ static int lp_backward(sem_lp_t lp, const uint16_t* X, const float* T, const int
         d3.scale = 2.0f / (float)n3;
     }
     d3.part = lp->lpart;
-    d3.Cf = lin ? nullptr : lp->d3f; d3.Cb = lp->d3b; d3.ldc = kOut; d3.Ct = lp->d3t; d3.ldt = B;
+    d3.Cf = lin ? nullptr : lp->d3f; d3.ldc = kOut; d3.Cb = lp->d3b; d3.Ct = lp->d3t;
     if ((rc = wave_products(lp, d3, WaveGemm(), WaveAux(), &nb))) return rc;
     WaveAux sum;                                   // the loss beside the next products
     sum.part = lp->lpart; sum.nb = nb;
@@ -1545,21 +1720,21 @@ static int lp_backward(sem_lp_t lp, const uint16_t* X, const float* T, const int
     }
     // layer 3: gW3 = d3^T Y2 and d2 = (d3 W3) * (Y2 > 0)
     const int mask = lin ? 0 : EPI_MASK;
-    WaveGemm w = product(kOut, kHid, B, lp->d3t, B, lp->Y2t, B);
+    WaveGemm w = product(kOut, kHid, B, lp->d3t, lp->Y2t);
     w.Cf = lp->gW[2]; w.ldc = kHid;
-    g = product(B, kHid, kOut, lp->d3b, kOut, lp->W3t, kOut);
-    g.epi = mask; g.mask = lp->Y2; g.ldm = kHid;
-    g.Cf = lin ? nullptr : lp->d2f; g.Cb = lp->d2b; g.ldc = kHid; g.Ct = lp->d2t; g.ldt = B;
+    g = product(B, kHid, kOut, lp->d3b, lp->W3t);
+    g.epi = mask; g.mask = lp->Y2;
+    g.Cf = lin ? nullptr : lp->d2f; g.ldc = kHid; g.Cb = lp->d2b; g.Ct = lp->d2t;
     if ((rc = wave_products(lp, w, g, sum))) return rc;
     // layer 2: gW2 = d2^T Y1 and d1 = (d2 W2) * (Y1 > 0)
-    w = product(kHid, kHid, B, lp->d2t, B, lp->Y1t, B);
+    w = product(kHid, kHid, B, lp->d2t, lp->Y1t);
     w.Cf = lp->gW[1]; w.ldc = kHid;
-    g = product(B, kHid, kHid, lp->d2b, kHid, lp->W2t, kHid);
-    g.epi = mask; g.mask = lp->Y1; g.ldm = kHid;
-    g.Cf = lin ? nullptr : lp->d1f; g.ldc = kHid; g.Ct = lp->d1t; g.ldt = B;
+    g = product(B, kHid, kHid, lp->d2b, lp->W2t);
+    g.epi = mask; g.mask = lp->Y1;
+    g.Cf = lin ? nullptr : lp->d1f; g.ldc = kHid; g.Ct = lp->d1t;
     if ((rc = wave_products(lp, w, g))) return rc;
     // layer 1: gW1 = d1^T X
-    w = product(kHid, kInPad, B, lp->d1t, B, lp->Xt, B);
+    w = product(kHid, kInPad, B, lp->d1t, lp->Xt);
     w.Cf = lp->gW[0]; w.ldc = kInPad;
     if ((rc = wave_products(lp, w))) return rc;
     if (!lin) {     // bias gradients: column sums of the float32 errors
@@ -1590,17 +1765,20 @@ static int lp_train_buffers(sem_lp_t lp, int B) {
     void* p = nullptr;
     int rc;
 #define LP_ALLOC2(ptr, bytes) do { rc = lp_alloc(lp, &p, (bytes)); if (rc) return rc; ptr = (decltype(ptr))p; } while (0)
+    const size_t h = (size_t)kHid;
+    LP_ALLOC2(lp->Y1, 2 * packed_size(R, h));
+    LP_ALLOC2(lp->Y2, 2 * packed_size(R, h));
     LP_ALLOC2(lp->d3f, 4 * R * kOut);
-    LP_ALLOC2(lp->d3b, 2 * R * kOut);
-    LP_ALLOC2(lp->d2f, 4 * R * kHid);
-    LP_ALLOC2(lp->d2b, 2 * R * kHid);
-    LP_ALLOC2(lp->d1f, 4 * R * kHid);
-    LP_ALLOC2(lp->Xt, 2 * R * kInPad);
-    LP_ALLOC2(lp->Y1t, 2 * R * kHid);
-    LP_ALLOC2(lp->Y2t, 2 * R * kHid);
-    LP_ALLOC2(lp->d3t, 2 * R * kOut);
-    LP_ALLOC2(lp->d2t, 2 * R * kHid);
-    LP_ALLOC2(lp->d1t, 2 * R * kHid);
+    LP_ALLOC2(lp->d3b, 2 * packed_size(R, kOut));
+    LP_ALLOC2(lp->d2f, 4 * R * h);
+    LP_ALLOC2(lp->d2b, 2 * packed_size(R, h));
+    LP_ALLOC2(lp->d1f, 4 * R * h);
+    LP_ALLOC2(lp->Xt, 2 * packed_size(kInPad, R));
+    LP_ALLOC2(lp->Y1t, 2 * packed_size(h, R));
+    LP_ALLOC2(lp->Y2t, 2 * packed_size(h, R));
+    LP_ALLOC2(lp->d3t, 2 * packed_size(kOut, R));
+    LP_ALLOC2(lp->d2t, 2 * packed_size(h, R));
+    LP_ALLOC2(lp->d1t, 2 * packed_size(h, R));
     LP_ALLOC2(lp->colpart, 4 * ((R + kColRows - 1) / kColRows) * (2 * (size_t)kHid + kOut));
     // one loss partial per workgroup of the output layer's product, at most one per 32 x 32 tile
     LP_ALLOC2(lp->lpart, 8 * ((R + 31) / 32) * ((kOut + 31) / 32));
@@ -1648,14 +1826,14 @@ extern "C" int sem_lp_adam(sem_lp_t lp, double lr, double beta1, double beta2, d
         a.v[q] = isW ? lp->vW[l] : lp->vb[l];
         a.g[q] = isW ? lp->gW[l] : lp->gb[l];
         a.wb[q] = a.wt[q] = nullptr;
-        a.ldb[q] = 0;
+        a.kb[q] = 0;
         a.first[q] = first;
         first += (int)(((int64_t)a.rows[q] * a.cols[q] + kBlock - 1) / kBlock);
     }
     a.first[6] = first;
-    a.wb[0] = lp->W1b; a.ldb[0] = lp->nip;      // the padding columns stay zero from creation on
-    a.wb[2] = lp->W2b; a.ldb[2] = lp->nh; a.wt[2] = lp->W2t;
-    a.wb[4] = lp->W3b; a.ldb[4] = lp->nh; a.wt[4] = lp->W3t;
+    a.wb[0] = lp->W1b; a.kb[0] = ksteps(lp->nip);      // the padding stays zero from creation on
+    a.wb[2] = lp->W2b; a.kb[2] = ksteps(lp->nh); a.wt[2] = lp->W2t;
+    a.wb[4] = lp->W3b; a.kb[4] = ksteps(lp->nh); a.wt[4] = lp->W3t;
     adam_kernel<<<(unsigned)first, kBlock, 0, ctx->stream>>>(a, (float)lr, (float)beta1, (float)(1.0 - beta1),
                                                              (float)beta2, (float)(1.0 - beta2), (float)eps,
                                                              (float)c1, (float)c2);
@@ -1705,8 +1883,8 @@ int lin_product(sem_lp_t lp, const T* r) {
     SEM_LAUNCH_CHECK(ctx);
     if (lp->no != kOut || lp->product == 2) {   // the general product, outputs scattered to CSR order
         if (nel > 0x7fffffff) return sem::fail(ctx, SEM_EINVAL, "sem_lp: too many elements");
-        return gemm(lp, (int)nel, lp->no, lp->no, lp->X, lp->nip, lp->Wfb, lp->no, nullptr, nullptr, 0, lp->Y3,
-                    nullptr, lp->no, 0, lp->kappa_inv, lp->gs->upos);
+        return gemm(lp, (int)nel, lp->no, lp->no, lp->X, lp->nip, lp->Wfb, lp->no, lp->Y3, lp->no,
+                    lp->kappa_inv, lp->gs->upos);
     }
     const int64_t nchunks = (nel + kWsChunk - 1) / kWsChunk;
     const int groups = (int)std::min<int64_t>(kWsGroupsMax, (nchunks + 7) / 8 * 8);
@@ -1738,25 +1916,27 @@ int lp_apply_t(sem_lp_t lp, T* z, const T* r, bool unique) {
     if (rc) return rc;
     if (lp->linear) {   // one product with the folded matrix
         rc = refresh_fold(lp);
-        if (!rc) rc = gemm(lp, (int)nel, lp->no, lp->no, lp->X, lp->nip, lp->Wfb, lp->no, nullptr, nullptr, 0,
-                           lp->Y3, nullptr, lp->no, 0);
+        if (!rc) rc = gemm(lp, (int)nel, lp->no, lp->no, lp->X, lp->nip, lp->Wfb, lp->no, lp->Y3,
+                           lp->no);
     } else {
-        rc = forward(lp, lp->X, nel);
+        rc = forward(lp, lp->X, nel, lp->Y3);
     }
     if (rc) return rc;
-    if (unique) {
-        const int64_t nu = lp->gs->n_unique;
-        lp_output_unique_kernel<T><<<grid_of(nu), kBlock, 0, st>>>(
-            z, lp->Y3, lp->scale, lp->jacobi_base ? lp->minv : nullptr, r, lp->gs->uoff, lp->gs->uidx,
-            nu, lp->skip, lp->linear, lp->no);
-        SEM_LAUNCH_CHECK(ctx);
-        return SEM_OK;
+    const int64_t nu = lp->gs->n_unique, n = nel * lp->no;
+    const unsigned gu = (grid_of(nu) + 7) / 8 * 8;      // a multiple of 8 for the XCD order
+#define LP_OUT(NO) case NO: \
+        if (unique) lp_output_unique_kernel<T, NO><<<gu, kBlock, 0, st>>>(z, lp->Y3, lp->scale, \
+                lp->jacobi_base ? lp->minv : nullptr, r, lp->gs->uoff, lp->gs->uidx, nu, lp->skip); \
+        else lp_output_kernel<T, NO><<<grid_of(n), kBlock, 0, st>>>(z, lp->Y3, lp->scale, lp->gs->mult, \
+                lp->jacobi_base ? lp->minv : nullptr, r, n, lp->skip, lp->linear); \
+        break;
+    switch (lp->no) {
+        LP_OUT(64) LP_OUT(216) LP_OUT(512) LP_OUT(1000) LP_OUT(1728)
+        default: return sem::fail(ctx, SEM_EUNSUPPORTED_LX, "sem_lp: element size %d", lp->no);
     }
-    const int64_t n = nel * lp->no;
-    lp_output_kernel<T><<<grid_of(n), kBlock, 0, st>>>(z, lp->Y3, lp->scale, lp->gs->mult,
-                                                       lp->jacobi_base ? lp->minv : nullptr, r, n, lp->skip,
-                                                       lp->linear, lp->no);
+#undef LP_OUT
     SEM_LAUNCH_CHECK(ctx);
+    if (unique) return SEM_OK;
     return gs_launch(lp->gs, z, sizeof(T) == 8 ? SEM_F64 : SEM_F32, lp->skip);
 }
 

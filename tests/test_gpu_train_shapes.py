@@ -1,4 +1,5 @@
-"""The training step's products at the edges of their tiles: batches that are
+"""The network's products at the edges of their tiles: a forward pass of row
+counts around the 16- and 32-row workgroups, and in training batches that are
 not whole 16- or 32-row tiles (one smaller than an earlier one of the same
 network), element and hidden sizes that are not whole tiles, a batch taken
 through row indices, and features that do not lie on 16 bytes.
@@ -48,6 +49,22 @@ def _rows(lx, count, seed):
     Xpad[:, :ni] = to_bf16(X)
     T = (0.1 * r.standard_normal((count, n))).astype(np.float32)
     return torch.from_numpy(Xpad).to(torch.bfloat16).cuda(), torch.from_numpy(T).cuda()
+
+
+@pytest.mark.parametrize("form", ["mse", "linear"])
+@pytest.mark.parametrize("lx,hidden,rows", [(4, 16, 1), (6, 48, 17), (4, 256, 33), (4, 80, 8192), (6, 16, 8209),
+                                            (12, 1024, 5)])
+def test_forward_of_ragged_rows(sem_ctx, lx, hidden, rows, form):
+    lp, params = _network(sem_ctx, lx, hidden, rows, form)
+    X, _ = _rows(lx, rows, 63)
+    Y = torch.full((rows + 1, lx ** 3), -7.0, dtype=torch.float32, device="cuda")
+    P.sem_lp_forward(lp, X, Y[:rows])
+    assert bool((Y[rows] == -7.0).all())          # nothing past the last row
+    Xq = X.float().cpu().numpy().astype(np.float64)[:, :lx ** 3 + 6]
+    ref = mlp.forward_bf16(params, Xq, linear=form == "linear")[2]
+    err = np.max(np.abs(Y[:rows].cpu().numpy() - ref))
+    assert err <= EW_NET * np.max(np.abs(ref)), err
+    lp.close()
 
 
 @pytest.mark.parametrize("form", ["mse", "metric", "linear"])
