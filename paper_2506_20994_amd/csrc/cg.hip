@@ -36,6 +36,7 @@ constexpr int kBlock = 256;
 constexpr int kGrid = 8192;
 constexpr int kGrid32 = 2048;
 constexpr int kFinal = 1024;          // threads of the single-block finalisers
+constexpr int kPcgBlocks = 1024;      // most workgroups of the Jacobi-PCG vector kernels
 
 struct Scal {
     double rz, pAp, alpha, beta, rr, bb, tol2, mean, pw_prev;
@@ -43,7 +44,14 @@ struct Scal {
     int usej, njac, fallback;   // flexible CG: Jacobi this iteration, count, for good
     double delta2, rmax2;       // residual replacement: pause when rr < delta2 * rmax2
     int pause;
+    // Jacobi-PCG: r.z and the iteration count at the start of iteration seq in slot
+    // seq % 2 (its last kernel writes the other slot while its workgroups still
+    // read this one), and the iteration that set `done` (kNotDone while none has)
+    double rzs[2];
+    int its[2];
+    int done_at;
 };
+constexpr int kNotDone = 0x7fffffff;
 
 // sum of a per-thread double over a 256-thread block, valid in thread 0
 __device__ __forceinline__ double block_sum(double v, double* s_red) {
@@ -68,6 +76,32 @@ __device__ double final_sum(const double* __restrict__ part, int n, int stride, 
     for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += s_red[q];
     __syncthreads();
     return t;
+}
+
+// both sums of n pairs of partials, in the same order
+__device__ void final_sum2(const double* __restrict__ part, int n, double* s_red, double* a, double* b) {
+    double va = 0.0, vb = 0.0;
+    for (int q = threadIdx.x; q < n; q += blockDim.x) {
+        const double2 v = reinterpret_cast<const double2*>(part)[q];
+        va += v.x;
+        vb += v.y;
+    }
+    va = sem::wave_sum(va);
+    vb = sem::wave_sum(vb);
+    const int nw = (int)(blockDim.x >> 6);
+    if ((threadIdx.x & 63) == 0) {
+        s_red[threadIdx.x >> 6] = va;
+        s_red[nw + (threadIdx.x >> 6)] = vb;
+    }
+    __syncthreads();
+    double ta = 0.0, tb = 0.0;
+    for (int q = 0; q < nw; ++q) {
+        ta += s_red[q];
+        tb += s_red[nw + q];
+    }
+    __syncthreads();
+    *a = ta;
+    *b = tb;
 }
 
 #define GRID_LOOP(i, n) \
@@ -175,47 +209,127 @@ __global__ void pcg_init_final(Scal* __restrict__ S, const double* __restrict__ 
         S->rmax2 = bb;
         S->pause = 0;
         S->done = (bb == 0.0 || maxit <= 0) ? 1 : 0;
+        S->rzs[0] = S->rzs[1] = rz;
+        S->its[0] = S->its[1] = 0;
+        S->done_at = S->done ? -1 : kNotDone;
     }
 }
 
-__global__ void pcg_alpha_final(Scal* __restrict__ S, const double* __restrict__ part, int n) {
+// One Jacobi-PCG iteration is the operator and these two kernels.  Every
+// workgroup sums the partials of the kernel before it by itself, all in the same
+// order, instead of a single-workgroup kernel in between (2.3 + 3.2 us of the 24
+// us of an iteration on a 6^3 lx = 6 box, 8 of 42 on a 16^3 lx = 8 box in float32),
+// with the first node's loads issued ahead of the sum.  Workgroup 0 writes the
+// scalars.  At most 1024 workgroups of 256 threads, or 512 of 1024 (the whole
+// chip), so that the sums stay short.
+//
+// pAp from the operator's partials, alpha = r.z / pAp; r -= alpha w with w_u the
+// assembled w_L; partials (r.Minv.r, r.r)
+template <typename T, int BS>
+__global__ void __launch_bounds__(BS)
+pcg_update_kernel(T* __restrict__ r, const T* __restrict__ wl, const T* __restrict__ minv,
+                  sem::Copies cp, int64_t n, Scal* S, int seq,
+                  const double* __restrict__ part_ax, int nax, double* __restrict__ part) {
     if (S->done) return;
-    __shared__ double s_red[kFinal / 64];
-    const double pAp = final_sum(part, n, 1, s_red);
-    if (threadIdx.x == 0) {
+    __shared__ double s_red[BS / 64];
+    const int64_t step = (int64_t)gridDim.x * BS;
+    int64_t u = sem::xcd_order(blockIdx.x, gridDim.x) * BS + threadIdx.x;
+    T wv = 0, rv = 0, mv = 0;
+    // float32: the vectors ahead of the assembly's chain of loads (32^3, lx = 8: 207
+    // against 215 us an iteration); float64: after it (374 against 380 us)
+    auto load = [&]() {
+        if constexpr (sizeof(T) == 8) wv = assemble_local(wl, cp, u);
+        rv = r[u];
+        mv = minv[u];
+        if constexpr (sizeof(T) == 4) wv = assemble_local(wl, cp, u);
+    };
+    if (u < n) load();
+    const double pAp = final_sum(part_ax, nax, 1, s_red);
+    const bool ok = pAp > 0.0 && isfinite(pAp);
+    const double alpha = S->rzs[seq & 1] / pAp;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         S->pAp = pAp;
-        if (!(pAp > 0.0) || !isfinite(pAp)) {
+        if (ok) {
+            S->alpha = alpha;
+        } else {
             S->breakdown = 1;
             S->done = 1;
-        } else {
-            S->alpha = S->rz / pAp;
+            S->done_at = seq - 1;      // no step is taken
         }
     }
-}
-
-// w_u = assembled w_L; x += alpha p, r -= alpha w; partials (r.Minv.r, r.r)
-template <typename T>
-__global__ void pcg_update_kernel(T* __restrict__ x, T* __restrict__ r, const T* __restrict__ p,
-                                  const T* __restrict__ wl, const T* __restrict__ minv,
-                                  const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx,
-                                  int64_t n, const Scal* __restrict__ S, double* __restrict__ part) {
-    if (S->done) return;
-    __shared__ double s_red[kBlock / 64];
-    const T alpha = (T)S->alpha;
+    if (!ok) return;
+    const T at = (T)alpha;
     double a = 0.0, b = 0.0;
-    GRID_LOOP_XCD(u, n) {
-        const T wv = assemble_local(wl, uoff, uidx, u);
-        x[u] += alpha * p[u];
-        const T rv = r[u] - alpha * wv;
+    while (u < n) {
+        rv -= at * wv;
         r[u] = rv;
-        a += (double)rv * (double)(minv[u] * rv);
+        a += (double)rv * (double)(mv * rv);
         b += (double)rv * (double)rv;
+        u += step;
+        if (u >= n) break;
+        load();
     }
     a = block_sum(a, s_red);
     b = block_sum(b, s_red);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = a;
-        part[2 * blockIdx.x + 1] = b;
+    if (threadIdx.x == 0) reinterpret_cast<double2*>(part)[blockIdx.x] = double2{a, b};
+}
+
+// r.z and r.r from the update's partials; x += alpha p; unless the iteration
+// ends the loop, p = Minv r + beta p.  x is updated here rather than with r, where
+// p would be read a second time.  NT: past the caches.
+template <typename T, int BS, bool NT>
+__global__ void __launch_bounds__(BS)
+pcg_p_kernel(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, const T* __restrict__ minv, int64_t n,
+             Scal* S, int seq, const double* __restrict__ part, int npart) {
+    if (S->done_at < seq) return;      // done before this iteration (this kernel sets done_at = seq)
+    __shared__ double s_red[2 * (BS / 64)];
+    const int64_t step = (int64_t)gridDim.x * BS;
+    int64_t u = blockIdx.x * (int64_t)BS + threadIdx.x;
+    auto ld = [](const T* q) { return NT ? __builtin_nontemporal_load(q) : *q; };
+    auto st = [](T* q, T v) {
+        if (NT) __builtin_nontemporal_store(v, q);
+        else *q = v;
+    };
+    T xv = 0, pv = 0, rv = 0, mv = 0;
+    if (u < n) {
+        xv = ld(x + u);
+        pv = ld(p + u);
+        rv = ld(r + u);
+        mv = ld(minv + u);
+    }
+    double rz, rr;
+    final_sum2(part, npart, s_red, &rz, &rr);
+    const double rz0 = S->rzs[seq & 1];
+    const int it = S->its[seq & 1] + 1;
+    const double beta = rz / rz0;
+    const bool broke = !isfinite(rr) || !isfinite(rz);
+    // residual replacement due (or convergence to verify)
+    const bool pause = !broke && S->delta2 > 0.0 && (rr <= S->tol2 || rr < S->delta2 * S->rmax2);
+    const bool done = broke || pause || rr <= S->tol2 || it >= S->maxit;
+    const T alpha = (T)S->alpha, bt = (T)beta;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        S->it = it;
+        S->rr = rr;
+        S->rz = rz;
+        S->beta = beta;
+        S->rzs[(seq & 1) ^ 1] = rz;
+        S->its[(seq & 1) ^ 1] = it;
+        if (broke) S->breakdown = 1;
+        if (pause) S->pause = 1;
+        if (done) {
+            S->done = 1;
+            S->done_at = seq;
+        }
+    }
+    while (u < n) {
+        st(x + u, xv + alpha * pv);
+        if (!done) st(p + u, mv * rv + bt * pv);
+        u += step;
+        if (u >= n) break;
+        xv = ld(x + u);
+        pv = ld(p + u);
+        rv = ld(r + u);
+        mv = ld(minv + u);
     }
 }
 
@@ -241,12 +355,12 @@ __global__ void pcg_beta_final(Scal* __restrict__ S, const double* __restrict__ 
     }
 }
 
-// p = Minv r + beta p
-template <typename T>
-__global__ void pcg_p_kernel(T* __restrict__ p, const T* __restrict__ r, const T* __restrict__ minv,
-                             int64_t n, const Scal* __restrict__ S) {
+// the direction update that a paused iteration skipped, with the replaced
+// residual: p = Minv r + beta p
+__global__ void pcg_resume_p_kernel(float* __restrict__ p, const float* __restrict__ r, const float* __restrict__ minv,
+                                    int64_t n, const Scal* __restrict__ S) {
     if (S->done) return;
-    const T beta = (T)S->beta;
+    const float beta = (float)S->beta;
     GRID_LOOP(u, n) p[u] = minv[u] * r[u] + beta * p[u];
 }
 
@@ -287,9 +401,11 @@ __global__ void sub_mean_kernel(double* __restrict__ x, const double* __restrict
 
 // r_u = b_u - assembled w_L
 __global__ void residual_kernel(double* __restrict__ r, const double* __restrict__ b,
-                                const double* __restrict__ wl, const int32_t* __restrict__ uoff,
-                                const int32_t* __restrict__ uidx, int64_t nu) {
-    GRID_LOOP_XCD(u, nu) r[u] = b[u] - assemble_local(wl, uoff, uidx, u);
+                                const double* __restrict__ wl, sem::Copies cp, int64_t nu) {
+    GRID_LOOP_XCD(u, nu) {
+        const double bv = b[u];
+        r[u] = bv - assemble_local(wl, cp, u);
+    }
 }
 
 // IR: rhat = (float)((r - mean) / norm), mean = s0 * inv_nu (inv_nu = 1 / nu on
@@ -519,20 +635,20 @@ __global__ void fcg_alpha_final(Scal* __restrict__ S, const double* __restrict__
 template <typename T>
 __global__ void fcg_update_kernel(T* __restrict__ x, T* __restrict__ r, T* __restrict__ wu,
                                   const T* __restrict__ p, const T* __restrict__ wl,
-                                  const T* __restrict__ minv, const int32_t* __restrict__ uoff,
-                                  const int32_t* __restrict__ uidx, int64_t n,
+                                  const T* __restrict__ minv, sem::Copies cp, int64_t n,
                                   const Scal* __restrict__ S, double* __restrict__ part) {
     if (S->done) return;
     __shared__ double s_red[kBlock / 64];
     const T alpha = (T)S->alpha;
     double a = 0.0, b = 0.0;
     GRID_LOOP_XCD(u, n) {
-        const T wv = assemble_local(wl, uoff, uidx, u);
+        const T xv = x[u], pv = p[u], ro = r[u], mv = minv[u];   // issued before the assembly's chain of loads
+        const T wv = assemble_local(wl, cp, u);
         wu[u] = wv;
-        x[u] += alpha * p[u];
-        const T rv = r[u] - alpha * wv;
+        x[u] = xv + alpha * pv;
+        const T rv = ro - alpha * wv;
         r[u] = rv;
-        a += (double)rv * (double)(minv[u] * rv);
+        a += (double)rv * (double)(mv * rv);
         b += (double)rv * (double)rv;
     }
     a = block_sum(a, s_red);
@@ -582,6 +698,9 @@ __global__ void rr_resume_final(Scal* __restrict__ S, const double* __restrict__
         S->rmax2 = rr;
         S->pause = 0;
         S->done = (S->it >= S->maxit) ? 1 : 0;
+        S->rzs[0] = S->rzs[1] = rz;
+        S->its[0] = S->its[1] = S->it;
+        if (!S->done) S->done_at = kNotDone;
     }
 }
 
@@ -614,6 +733,7 @@ struct sem_cg_s {
     sem::AxArgs A64{};
     Scal* S = nullptr;
     double* part = nullptr;        // max(4*kGrid, ax_blocks) doubles
+    double* part_vec = nullptr;    // 2*kPcgBlocks doubles: the Jacobi-PCG update's partials
     double* part2 = nullptr;       // kGrid doubles (flexible CG: p.r partials)
     double* sums = nullptr;        // 2 doubles
     Scal* S_host = nullptr;        // pinned
@@ -653,6 +773,38 @@ unsigned vec_grid(int64_t n, int cap = kGrid) {
 template <typename T>
 unsigned vec_grid_t(int64_t n) { return vec_grid(n, sizeof(T) == 8 ? kGrid : kGrid32); }
 
+// the vector kernels of one Jacobi-PCG iteration, after the operator wrote wl and
+// its nb partials: 256-thread workgroups up to 1024 of them (one node a thread),
+// above that the chip filled once with 1024-thread ones
+template <typename T>
+int pcg_vectors(sem_cg_t cg, Level& lv, int nb, int seq) {
+    hipStream_t st = cg->ctx->stream;
+    const int64_t n = cg->nu;
+    T *x = (T*)lv.x, *r = (T*)lv.r, *p = (T*)lv.p;
+    const T *wl = (const T*)lv.wl, *minv = (const T*)lv.minv;
+    const sem::Copies cp{cg->gs->link, cg->gs->more};
+    if (n <= 256 * (int64_t)kPcgBlocks) {
+        const unsigned g = (unsigned)((n + 255) / 256 + 7) / 8 * 8;       // a multiple of 8: the XCD order
+        pcg_update_kernel<T, 256><<<g, 256, 0, st>>>(r, wl, minv, cp, n, cg->S, seq, cg->part, nb, cg->part_vec);
+        pcg_p_kernel<T, 256, false><<<g, 256, 0, st>>>(x, p, r, minv, n, cg->S, seq, cg->part_vec, (int)g);
+    } else {
+        const unsigned g = kPcgBlocks / 2;
+        pcg_update_kernel<T, 1024><<<g, 1024, 0, st>>>(r, wl, minv, cp, n, cg->S, seq, cg->part, nb, cg->part_vec);
+        // What an iteration touches (six factors, lid and w per local node, five
+        // vectors) against the 256 MB last-level cache: above it the streams of this
+        // kernel go past the caches (32^3, lx = 8: 399 -> 378 us an iteration in
+        // float64, 210 -> 207 in float32), below it they find their lines there (16^3:
+        // 58.2 against 60.4 and 40.8 against 41.8 us).
+        const double touched = (double)cg->n * (7 * sizeof(T) + 4) + 5.0 * sizeof(T) * n;
+        if (touched > 256e6)
+            pcg_p_kernel<T, 1024, true><<<g, 1024, 0, st>>>(x, p, r, minv, n, cg->S, seq, cg->part_vec, (int)g);
+        else
+            pcg_p_kernel<T, 1024, false><<<g, 1024, 0, st>>>(x, p, r, minv, n, cg->S, seq, cg->part_vec, (int)g);
+    }
+    SEM_LAUNCH_CHECK(cg->ctx);
+    return SEM_OK;
+}
+
 // PCG on level lv from x = 0 with right-hand side rhs (unique, type T);
 // leaves the iterate in lv.x.
 template <typename T>
@@ -664,21 +816,17 @@ int pcg_run(sem_cg_t cg, Level& lv, const T* rhs, double tol, int maxit, int che
     const unsigned g = vec_grid_t<T>(n);
     T* x = (T*)lv.x; T* r = (T*)lv.r; T* p = (T*)lv.p; T* wl = (T*)lv.wl;
     const T* minv = (const T*)lv.minv;
-    const int32_t *lid = cg->gs->lid, *uoff = cg->gs->uoff, *uidx = cg->gs->uidx;
     pcg_init_kernel<T><<<g, kBlock, 0, st>>>(x, r, p, rhs, minv, n, cg->part);
     pcg_init_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g, tol, maxit);
     SEM_LAUNCH_CHECK(ctx);
     const int nb = sem::ax_blocks(lv.A.lx, lv.A.nel);
+    int seq = 0;
     for (;;) {
-        for (int q = 0; q < check_every; ++q) {
-            int rc = sem::launch_ax(ctx, lv.kind, lv.A, wl, p, &cg->S->done, cg->part, lid);
+        for (int q = 0; q < check_every; ++q, ++seq) {
+            int rc = sem::launch_ax(ctx, lv.kind, lv.A, wl, p, &cg->S->done, cg->part, cg->gs->lid);
+            if (!rc) rc = pcg_vectors<T>(cg, lv, nb, seq);
             if (rc) return rc;
-            pcg_alpha_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, nb);
-            pcg_update_kernel<T><<<g, kBlock, 0, st>>>(x, r, p, wl, minv, uoff, uidx, n, cg->S, cg->part);
-            pcg_beta_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g);
-            pcg_p_kernel<T><<<g, kBlock, 0, st>>>(p, r, minv, n, cg->S);
         }
-        SEM_LAUNCH_CHECK(ctx);
         SEM_HIP(ctx, hipMemcpyAsync(cg->S_host, cg->S, sizeof(Scal), hipMemcpyDeviceToHost, st));
         SEM_HIP(ctx, hipStreamSynchronize(st));
         if (cg->S_host->done) break;
@@ -748,7 +896,8 @@ int rr_run(sem_cg_t cg, Level& lv, double tol, double delta, int maxit, int chec
     const unsigned g = vec_grid_t<float>(n);
     float* x = (float*)lv.x; float* r = (float*)lv.r; float* p = (float*)lv.p; float* wl = (float*)lv.wl;
     const float* minv = (const float*)lv.minv;
-    const int32_t *lid = cg->gs->lid, *uoff = cg->gs->uoff, *uidx = cg->gs->uidx;
+    const int32_t* lid = cg->gs->lid;
+    const sem::Copies cp{cg->gs->link, cg->gs->more};
     // x64 = 0, r64 = b; inner start: x = 0, r = (float) b, p = Minv r
     zero_kernel<<<g, kBlock, 0, st>>>(cg->x64, n);
     rr_replace_kernel<<<g, kBlock, 0, st>>>(cg->rhs32, cg->b64, minv, n, cg->part);
@@ -757,7 +906,7 @@ int rr_run(sem_cg_t cg, Level& lv, double tol, double delta, int maxit, int chec
     set_delta<<<1, 1, 0, st>>>(cg->S, delta * delta);
     SEM_LAUNCH_CHECK(ctx);
     const int nb = sem::ax_blocks(lv.A.lx, lv.A.nel);
-    int nrep = 0;
+    int nrep = 0, seq = 0;
     float* z = (float*)lv.z;
     float* wu = (float*)lv.wu;
     bool fallen = false;
@@ -772,17 +921,14 @@ int rr_run(sem_cg_t cg, Level& lv, double tol, double delta, int maxit, int chec
                 rc = sem::launch_ax(ctx, lv.kind, lv.A, wl, p, &cg->S->done, cg->part, lid);
                 if (rc) return rc;
                 fcg_alpha_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, nb, cg->part2, (int)g);
-                fcg_update_kernel<float><<<g, kBlock, 0, st>>>(x, r, wu, p, wl, minv, uoff, uidx, n, cg->S,
+                fcg_update_kernel<float><<<g, kBlock, 0, st>>>(x, r, wu, p, wl, minv, cp, n, cg->S,
                                                                cg->part);
                 pcg_beta_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g);
                 continue;
             }
             int rc = sem::launch_ax(ctx, lv.kind, lv.A, wl, p, &cg->S->done, cg->part, lid);
+            if (!rc) rc = pcg_vectors<float>(cg, lv, nb, seq++);
             if (rc) return rc;
-            pcg_alpha_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, nb);
-            pcg_update_kernel<float><<<g, kBlock, 0, st>>>(x, r, p, wl, minv, uoff, uidx, n, cg->S, cg->part);
-            pcg_beta_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g);
-            pcg_p_kernel<float><<<g, kBlock, 0, st>>>(p, r, minv, n, cg->S);
         }
         SEM_LAUNCH_CHECK(ctx);
         SEM_HIP(ctx, hipMemcpyAsync(cg->S_host, cg->S, sizeof(Scal), hipMemcpyDeviceToHost, st));
@@ -818,7 +964,7 @@ int rr_run(sem_cg_t cg, Level& lv, double tol, double delta, int maxit, int chec
         // PCG: the paused iteration skipped its direction update, redone with
         // the replaced residual and that iteration's beta (flexible CG forms
         // its direction at the start of the next iteration instead)
-        if (!flexible(cg)) pcg_p_kernel<float><<<g, kBlock, 0, st>>>(p, r, minv, n, cg->S);
+        if (!flexible(cg)) pcg_resume_p_kernel<<<g, kBlock, 0, st>>>(p, r, minv, n, cg->S);
         SEM_LAUNCH_CHECK(ctx);
     }
     *iters_out = cg->S_host->it;
@@ -840,7 +986,8 @@ int fcg_run(sem_cg_t cg, Level& lv, const T* rhs, double tol, int maxit, int che
     T* x = (T*)lv.x; T* r = (T*)lv.r; T* p = (T*)lv.p; T* wl = (T*)lv.wl; T* z = (T*)lv.z;
     T* wu = (T*)lv.wu;
     const T* minv = (const T*)lv.minv;
-    const int32_t *lid = cg->gs->lid, *uoff = cg->gs->uoff, *uidx = cg->gs->uidx;
+    const int32_t* lid = cg->gs->lid;
+    const sem::Copies cp{cg->gs->link, cg->gs->more};
     pcg_init_kernel<T><<<g, kBlock, 0, st>>>(x, r, p, rhs, minv, n, cg->part);
     pcg_init_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g, tol, maxit);
     SEM_LAUNCH_CHECK(ctx);
@@ -857,7 +1004,7 @@ int fcg_run(sem_cg_t cg, Level& lv, const T* rhs, double tol, int maxit, int che
             rc = sem::launch_ax(ctx, lv.kind, lv.A, wl, p, &cg->S->done, cg->part, lid);
             if (rc) return rc;
             fcg_alpha_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, nb, cg->part2, (int)g);
-            fcg_update_kernel<T><<<g, kBlock, 0, st>>>(x, r, wu, p, wl, minv, uoff, uidx, n, cg->S, cg->part);
+            fcg_update_kernel<T><<<g, kBlock, 0, st>>>(x, r, wu, p, wl, minv, cp, n, cg->S, cg->part);
             pcg_beta_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g);
         }
         SEM_LAUNCH_CHECK(ctx);
@@ -901,7 +1048,7 @@ int residual64(sem_cg_t cg, const double* xu) {
     int rc = sem::launch_ax(cg->ctx, sem::AxKind::F64, cg->A64, cg->wl64, xu, nullptr, nullptr, cg->gs->lid);
     if (rc) return rc;
     residual_kernel<<<vec_grid(cg->nu), kBlock, 0, cg->ctx->stream>>>(cg->r64, cg->b64, cg->wl64,
-                                                                      cg->gs->uoff, cg->gs->uidx, cg->nu);
+                                                                      sem::Copies{cg->gs->link, cg->gs->more}, cg->nu);
     SEM_LAUNCH_CHECK(cg->ctx);
     return SEM_OK;
 }
@@ -977,6 +1124,7 @@ extern "C" int sem_cg_setup(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A,
 #define CG_ALLOC(ptr, bytes) do { int rc_ = cg_alloc(cg, (void**)&(ptr), (bytes)); if (rc_) return bail(rc_); } while (0)
     CG_ALLOC(cg->S, sizeof(Scal));
     CG_ALLOC(cg->part, sizeof(double) * npart);
+    CG_ALLOC(cg->part_vec, sizeof(double) * 2 * kPcgBlocks);
     CG_ALLOC(cg->part2, sizeof(double) * kGrid);
     CG_ALLOC(cg->sums, sizeof(double) * 2);
     CG_ALLOC(cg->b64, u64);

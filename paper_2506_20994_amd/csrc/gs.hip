@@ -2,9 +2,9 @@
 //
 // Plan: only ids that occur more than once need work.  Those "shared" ids are
 // listed in the order their first local copy appears (so neighbouring threads
-// touch neighbouring memory), each with the CSR list of its local copies in
-// increasing local index.  One thread per shared id sums its copies in that
-// fixed order and writes the sum back to every copy: deterministic, no atomics.
+// touch neighbouring memory), each with its local copies (sem::Copies).  One
+// thread per shared id sums its copies in increasing local index and writes the
+// sum back to every copy: deterministic, no atomics.
 //
 // Negative ids mark Dirichlet nodes (homogeneous Dirichlet conditions): they
 // are no unknowns.  They take no unique index (lid = -1), sit after every
@@ -23,8 +23,7 @@ constexpr int kBlock = 256;
 // threads [0, n_shared) sum the shared ids; threads [n_shared, n_shared +
 // n_masked) zero the Dirichlet nodes listed in midx
 template <typename T>
-__global__ void gs_kernel(T* __restrict__ u, const int32_t* __restrict__ off,
-                          const int32_t* __restrict__ idx, int64_t n_shared, const int* __restrict__ skip,
+__global__ void gs_kernel(T* __restrict__ u, sem::Copies cp, int64_t n_shared, const int* __restrict__ skip,
                           const int32_t* __restrict__ midx, int64_t n_masked) {
     if (skip && *skip) return;
     const int64_t g = sem::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
@@ -32,25 +31,65 @@ __global__ void gs_kernel(T* __restrict__ u, const int32_t* __restrict__ off,
         if (g < n_shared + n_masked) u[midx[g - n_shared]] = T(0);
         return;
     }
-    // the first eight copies (a hexahedral mesh has at most eight) by independent
-    // predicated loads issued together, summed in CSR order; any further copies
-    // one by one
-    const int32_t b = off[g], e = off[g + 1];
-    int32_t L[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) L[q] = b + q < e ? idx[b + q] : -1;
-    T v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = L[q] >= 0 ? u[L[q]] : T(0);
-    T s = v[0];
-#pragma unroll
-    for (int q = 1; q < 8; ++q)
-        if (L[q] >= 0) s += v[q];
-    for (int32_t q = b + 8; q < e; ++q) s += u[idx[q]];
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        if (L[q] >= 0) u[L[q]] = s;
-    for (int32_t q = b + 8; q < e; ++q) u[idx[q]] = s;
+    const int2 c = cp.link[g];
+    const int4 i = c.y < -1 ? cp.more[-2 - c.y] : int4{-1, -1, -1, 0};
+    const T s = sem::sum_copies_flat<T>(cp, g, [=](int32_t L) { return u[L]; });
+    u[c.x] = s;
+    if (c.y >= 0) u[c.y] = s;
+    if (i.x >= 0) {
+        u[i.x] = s;
+        u[i.y] = s;
+    }
+    if (i.z >= 0) u[i.z] = s;
+    for (int k = 1; k <= i.w; ++k) {
+        const int4 j = cp.more[-2 - c.y + k];
+        u[j.x] = s;
+        if (j.y >= 0) u[j.y] = s;
+        if (j.z >= 0) u[j.z] = s;
+        if (j.w >= 0) u[j.w] = s;
+    }
+}
+
+// int4 entries that a node of m copies takes in sem::Copies::more
+__host__ __device__ inline int64_t more_entries(int32_t m) { return m < 3 ? 0 : 1 + (m > 4 ? (m - 1) / 4 : 0); }
+
+// link[u] and more from the CSR lists; *next counts the entries of more handed
+// out, a workgroup's at a time (their order differs from build to build, what
+// they hold does not)
+__global__ void link_kernel(int2* __restrict__ link, int4* __restrict__ more, unsigned* __restrict__ next,
+                            const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu) {
+    __shared__ unsigned s_count, s_base;
+    for (int64_t u0 = blockIdx.x * (int64_t)blockDim.x; u0 < nu; u0 += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t u = u0 + threadIdx.x;
+        const int32_t b = u < nu ? uoff[u] : 0, m = u < nu ? uoff[u + 1] - b : 1;
+        const unsigned n = (unsigned)more_entries(m);
+        if (threadIdx.x == 0) s_count = 0;
+        __syncthreads();
+        const unsigned mine = n ? atomicAdd(&s_count, n) : 0;
+        __syncthreads();
+        if (threadIdx.x == 0 && s_count) s_base = atomicAdd(next, s_count);
+        __syncthreads();
+        if (u < nu) {
+            int2 c{uidx[b], m == 2 ? uidx[b + 1] : -1};
+            if (n) {
+                const int32_t q = (int32_t)(s_base + mine);
+                c.y = -2 - q;
+                auto at = [&](int32_t k) { return k < m ? uidx[b + k] : -1; };
+                more[q] = int4{at(1), at(2), at(3), (int32_t)n - 1};
+                for (int32_t k = 1; k < (int32_t)n; ++k)
+                    more[q + k] = int4{at(4 * k), at(4 * k + 1), at(4 * k + 2), at(4 * k + 3)};
+            }
+            link[u] = c;
+        }
+        __syncthreads();
+    }
+}
+
+// slink[g] = link of the g-th shared id, whose first copy is idx[off[g]]
+__global__ void slink_kernel(int2* __restrict__ slink, const int2* __restrict__ link, const int32_t* __restrict__ lid,
+                             const int32_t* __restrict__ off, const int32_t* __restrict__ idx, int64_t n_shared) {
+    const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (g < n_shared) slink[g] = link[lid[idx[off[g]]]];
 }
 
 __global__ void mult_kernel(double* __restrict__ mult, const int32_t* __restrict__ off,
@@ -117,7 +156,11 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
     for (int64_t L = 0; L < n_local; ++L)
         if (key[L] >= 0) ++count[(size_t)key[L]];
     int64_t n_unique = 0;
-    for (int32_t c : count) n_unique += (c > 0);
+    int64_t n_more = 0;
+    for (int32_t c : count) {
+        n_unique += (c > 0);
+        n_more += more_entries(c);
+    }
     // shared ids in order of first appearance; slot[id] = shared index or -1
     std::vector<int32_t> slot((size_t)(idmax + 1), -1);
     std::vector<int32_t> off(1, 0);
@@ -177,9 +220,18 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
     gs->n_unique = n_unique;
     gs->n_shared = n_shared;
     gs->n_masked = n_masked;
-    gs->n_entries = (int64_t)idx.size();
-    hipError_t e = hipMalloc(&gs->off, sizeof(int32_t) * off.size());
-    if (e == hipSuccess && !idx.empty()) e = hipMalloc(&gs->idx, sizeof(int32_t) * idx.size());
+    // the shared ids' lists, needed here only, and one block for the plan's copies
+    int32_t* d_tmp = nullptr;
+    hipError_t e = hipMalloc(&d_tmp, sizeof(int32_t) * (off.size() + idx.size() + 1));
+    int32_t *d_off = d_tmp, *d_idx = d_tmp + off.size();
+    unsigned* d_next = reinterpret_cast<unsigned*>(d_idx + idx.size());
+    if (e == hipSuccess) e = hipMemset(d_next, 0, sizeof(unsigned));
+    if (e == hipSuccess && n_unique > 0)
+        e = hipMalloc(&gs->more, sizeof(int4) * n_more + sizeof(int2) * (n_unique + n_shared));
+    if (e == hipSuccess && n_unique > 0) {
+        gs->link = reinterpret_cast<int2*>(gs->more + n_more);
+        gs->slink = gs->link + n_unique;
+    }
     if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->mult, sizeof(double) * n_local);
     if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->owner, sizeof(double) * n_local);
     if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->lid, sizeof(int32_t) * n_local);
@@ -193,17 +245,22 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
     if (e == hipSuccess && n_local > 0)
         e = hipMemcpy(gs->uidx, uidx.data(), sizeof(int32_t) * n_local, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(gs->uoff, uoff.data(), sizeof(int32_t) * uoff.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(gs->off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(d_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !idx.empty())
-        e = hipMemcpy(gs->idx, idx.data(), sizeof(int32_t) * idx.size(), hipMemcpyHostToDevice);
+        e = hipMemcpy(d_idx, idx.data(), sizeof(int32_t) * idx.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && n_local > 0) {
         fill_kernel<<<1024, kBlock, 0, ctx->stream>>>(gs->mult, 1.0, n_local);
         fill_kernel<<<1024, kBlock, 0, ctx->stream>>>(gs->owner, 1.0, n_local);
         e = hipGetLastError();
+        if (e == hipSuccess && n_unique > 0) {
+            link_kernel<<<4096, kBlock, 0, ctx->stream>>>(gs->link, gs->more, d_next, gs->uoff, gs->uidx, n_unique);
+            e = hipGetLastError();
+        }
         if (e == hipSuccess && n_shared > 0) {
             const unsigned gr = (unsigned)((n_shared + kBlock - 1) / kBlock);
-            mult_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->mult, gs->off, gs->idx, n_shared);
-            owner_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->owner, gs->off, gs->idx, n_shared);
+            mult_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->mult, d_off, d_idx, n_shared);
+            owner_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->owner, d_off, d_idx, n_shared);
+            slink_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->slink, gs->link, gs->lid, d_off, d_idx, n_shared);
             e = hipGetLastError();
         }
         if (e == hipSuccess && n_masked > 0) {
@@ -213,6 +270,7 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     }
+    if (d_tmp) (void)hipFree(d_tmp);
     if (e != hipSuccess) {
         sem_gs_destroy(gs);
         return sem::check_hip(ctx, e, "sem_gs_setup");
@@ -224,8 +282,7 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
 extern "C" int sem_gs_destroy(sem_gs_t gs) {
     if (!gs) return SEM_OK;
     if (gs->ctx) (void)hipSetDevice(gs->ctx->device);
-    if (gs->off) (void)hipFree(gs->off);
-    if (gs->idx) (void)hipFree(gs->idx);
+    if (gs->more) (void)hipFree(gs->more);
     if (gs->mult) (void)hipFree(gs->mult);
     if (gs->owner) (void)hipFree(gs->owner);
     if (gs->lid) (void)hipFree(gs->lid);
@@ -259,11 +316,12 @@ int gs_launch(sem_gs_t gs, void* u, sem_dtype_t dtype, const int* skip) {
     constexpr int kGsBlock = 512;           // measured: 256 and 1024 threads are slower
     const unsigned grid = (unsigned)((nt + 8 * kGsBlock - 1) / (8 * kGsBlock) * 8);   // a multiple of 8
     const int32_t* midx = gs->uidx + (gs->n_local - gs->n_masked);
+    const Copies cp{gs->slink, gs->more};
     if (dtype == SEM_F64)
-        gs_kernel<double><<<grid, kGsBlock, 0, ctx->stream>>>((double*)u, gs->off, gs->idx, gs->n_shared, skip,
+        gs_kernel<double><<<grid, kGsBlock, 0, ctx->stream>>>((double*)u, cp, gs->n_shared, skip,
                                                               midx, gs->n_masked);
     else if (dtype == SEM_F32)
-        gs_kernel<float><<<grid, kGsBlock, 0, ctx->stream>>>((float*)u, gs->off, gs->idx, gs->n_shared, skip,
+        gs_kernel<float><<<grid, kGsBlock, 0, ctx->stream>>>((float*)u, cp, gs->n_shared, skip,
                                                              midx, gs->n_masked);
     else
         return fail(ctx, SEM_EINVAL, "sem_gs: dtype %d not supported (F64 or F32)", (int)dtype);

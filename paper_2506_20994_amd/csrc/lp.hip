@@ -730,35 +730,23 @@ __global__ void lp_output_kernel(T* __restrict__ z, const float* __restrict__ Y3
 }
 
 // unique layout: z_u = mean over the copies L of u of scale[e(L)] Y3[L] (+ Minv_u
-// r_u with the Jacobi base).  Bound by the chain offsets -> copies -> values: the
-// first eight copies (a hexahedral mesh has at most eight) go out as independent
-// predicated loads, summed in CSR order, and the workgroups run in XCD order.
+// r_u with the Jacobi base), the workgroups in XCD order.  Bound by the chain
+// copies -> values: the CSR lists walked one copy at a time took 29 us on a 20^3
+// lx = 8 box.
 template <typename T, int NO>
 __global__ void lp_output_unique_kernel(T* __restrict__ z, const float* __restrict__ Y3,
-                                        const float* __restrict__ scale, const double* __restrict__ minv,
-                                        const T* __restrict__ r, const int32_t* __restrict__ uoff,
-                                        const int32_t* __restrict__ uidx, int64_t nu,
+                                        const float* __restrict__ scale, const double* __restrict__ minvu,
+                                        const T* __restrict__ r, sem::Copies cp, int64_t nu,
                                         const int* __restrict__ skip) {
     if (skip && *skip) return;
     for (int64_t u = sem::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; u < nu;
          u += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t b = uoff[u], e = uoff[u + 1];
-        int32_t L[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) L[q] = b + q < e ? uidx[b + q] : -1;
-        float y[8], c[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            y[q] = L[q] >= 0 ? Y3[L[q]] : 0.f;
-            c[q] = L[q] >= 0 ? scale[L[q] / NO] : 0.f;
-        }
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (L[q] >= 0) s += (double)c[q] * (double)y[q];
-        for (int32_t q = b + 8; q < e; ++q) s += (double)scale[uidx[q] / NO] * (double)Y3[uidx[q]];
-        s *= 1.0 / (double)(e - b);
-        if (minv) s += minv[L[0]] * (double)r[u];
+        int m;
+        double s = sem::sum_copies<double>(cp, u, [=](int32_t L) {
+            return (double)scale[(uint32_t)L / (uint32_t)NO] * (double)Y3[L];
+        }, &m);
+        s *= 1.0 / (double)m;
+        if (minvu) s += minvu[u] * (double)r[u];
         z[u] = (T)s;
     }
 }
@@ -1926,7 +1914,7 @@ int lp_apply_t(sem_lp_t lp, T* z, const T* r, bool unique) {
     const unsigned gu = (grid_of(nu) + 7) / 8 * 8;      // a multiple of 8 for the XCD order
 #define LP_OUT(NO) case NO: \
         if (unique) lp_output_unique_kernel<T, NO><<<gu, kBlock, 0, st>>>(z, lp->Y3, lp->scale, \
-                lp->jacobi_base ? lp->minv : nullptr, r, lp->gs->uoff, lp->gs->uidx, nu, lp->skip); \
+                lp->jacobi_base ? lp->minvu : nullptr, r, sem::Copies{lp->gs->link, lp->gs->more}, nu, lp->skip); \
         else lp_output_kernel<T, NO><<<grid_of(n), kBlock, 0, st>>>(z, lp->Y3, lp->scale, lp->gs->mult, \
                 lp->jacobi_base ? lp->minv : nullptr, r, n, lp->skip, lp->linear); \
         break;

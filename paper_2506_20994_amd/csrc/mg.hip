@@ -53,8 +53,11 @@ constexpr int kMaxF3 = SEM_LX_MAX * SEM_LX_MAX * SEM_LX_MAX;   // fine element n
 constexpr int kMaxC = SEM_LX_MAX / 2;                          // coarse lx of any transfer
 constexpr int64_t kCoarseMax = 2048;                           // unknowns of the dense coarsest solve
 
-#define MG_LOOP(i, n) \
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
+// grid-stride loop with the workgroups in XCD order: the elements that neighbouring
+// nodes share are then read through one L2 (32^3 multigrid solve 48.4 -> 47.3 ms)
+#define MG_LOOP(i, n)                                                                            \
+    for (int64_t i = sem::xcd_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; i < (n); \
+         i += (int64_t)gridDim.x * blockDim.x)
 
 unsigned vgrid(int64_t n) {
     const int64_t b = (n + kBlock - 1) / kBlock;
@@ -70,14 +73,15 @@ using sem::assemble_local;
 __global__ void cheb_first_kernel(float* __restrict__ x, float* __restrict__ r, float* __restrict__ d,
                                   float* __restrict__ bout, const float* __restrict__ bin,
                                   const float* __restrict__ bl, const float* __restrict__ minv, float c0,
-                                  const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu,
+                                  sem::Copies cp, int64_t nu,
                                   const int* __restrict__ skip) {
     if (skip && *skip) return;
     MG_LOOP(u, nu) {
-        const float bv = bl ? assemble_local(bl, uoff, uidx, u) : bin[u];
+        const float mv = minv[u];              // vectors are read ahead of the assembly's chain of loads
+        const float bv = bl ? assemble_local(bl, cp, u) : bin[u];
         if (bout) bout[u] = bv;
         r[u] = bv;
-        const float dv = c0 * minv[u] * bv;
+        const float dv = c0 * mv * bv;
         d[u] = dv;
         x[u] = dv;
     }
@@ -86,38 +90,42 @@ __global__ void cheb_first_kernel(float* __restrict__ x, float* __restrict__ r, 
 // Later steps: r -= A d (assembled from wl), d = c1 d + c2 Minv r, x += d.
 __global__ void cheb_step_kernel(float* __restrict__ x, float* __restrict__ r, float* __restrict__ d,
                                  const float* __restrict__ wl, const float* __restrict__ minv, float c1, float c2,
-                                 const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu,
+                                 sem::Copies cp, int64_t nu,
                                  const int* __restrict__ skip) {
     if (skip && *skip) return;
     MG_LOOP(u, nu) {
-        const float rv = r[u] - assemble_local(wl, uoff, uidx, u);
+        const float ro = r[u], dold = d[u], mv = minv[u], xv = x[u];
+        const float rv = ro - assemble_local(wl, cp, u);
         r[u] = rv;
-        const float dv = c1 * d[u] + c2 * minv[u] * rv;
+        const float dv = c1 * dold + c2 * mv * rv;
         d[u] = dv;
-        x[u] += dv;
+        x[u] = xv + dv;
     }
 }
 
 // r -= A d: the residual b - A x after the pre-smoothing's last step
 __global__ void cheb_resid_kernel(float* __restrict__ r, const float* __restrict__ wl,
-                                  const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu,
+                                  sem::Copies cp, int64_t nu,
                                   const int* __restrict__ skip) {
     if (skip && *skip) return;
-    MG_LOOP(u, nu) r[u] -= assemble_local(wl, uoff, uidx, u);
+    MG_LOOP(u, nu) {
+        const float ro = r[u];
+        r[u] = ro - assemble_local(wl, cp, u);
+    }
 }
 
 // First step from a given x (post-smoothing): r = b - A x, d = c0 Minv r, x += d.
 __global__ void cheb_post_kernel(float* __restrict__ x, float* __restrict__ r, float* __restrict__ d,
                                  const float* __restrict__ b, const float* __restrict__ wl,
-                                 const float* __restrict__ minv, float c0, const int32_t* __restrict__ uoff,
-                                 const int32_t* __restrict__ uidx, int64_t nu, const int* __restrict__ skip) {
+                                 const float* __restrict__ minv, float c0, sem::Copies cp, int64_t nu, const int* __restrict__ skip) {
     if (skip && *skip) return;
     MG_LOOP(u, nu) {
-        const float rv = b[u] - assemble_local(wl, uoff, uidx, u);
+        const float bv = b[u], mv = minv[u], xv = x[u];
+        const float rv = bv - assemble_local(wl, cp, u);
         r[u] = rv;
-        const float dv = c0 * minv[u] * rv;
+        const float dv = c0 * mv * rv;
         d[u] = dv;
-        x[u] += dv;
+        x[u] = xv + dv;
     }
 }
 
@@ -459,11 +467,11 @@ bool prolong_p_wave(hipStream_t st, int lf, int lc, float* xf, const float* xc, 
 constexpr int kCoarseRows = 4;
 __global__ void __launch_bounds__(kBlock)
 coarse_kernel(float* __restrict__ x, const float* __restrict__ bin, const float* __restrict__ bl,
-              const float* __restrict__ ainv, const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx,
+              const float* __restrict__ ainv, sem::Copies cp,
               int nu, const int* __restrict__ skip) {
     if (skip && *skip) return;
     __shared__ float sb[kCoarseMax];
-    for (int u = threadIdx.x; u < nu; u += blockDim.x) sb[u] = bl ? assemble_local(bl, uoff, uidx, u) : bin[u];
+    for (int u = threadIdx.x; u < nu; u += blockDim.x) sb[u] = bl ? assemble_local(bl, cp, u) : bin[u];
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int row0 = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * kCoarseRows;
@@ -609,8 +617,8 @@ __global__ void zero_f32_kernel(float* __restrict__ v, int64_t n) {
 
 // Minv_u = 1 / (assembled diagonal) from the element-local diagonal dl
 __global__ void diag_recip_kernel(float* __restrict__ minv, const double* __restrict__ dl,
-                                  const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu) {
-    MG_LOOP(u, nu) minv[u] = (float)(1.0 / assemble_local(dl, uoff, uidx, u));
+                                  sem::Copies cp, int64_t nu) {
+    MG_LOOP(u, nu) minv[u] = (float)(1.0 / assemble_local(dl, cp, u));
 }
 
 // own[L] = 1 for the first local copy of a unique node, 0 otherwise (and on
@@ -629,8 +637,8 @@ __global__ void unit_local_kernel(double* __restrict__ ul, const int32_t* __rest
 }
 
 __global__ void column_kernel(double* __restrict__ col, const double* __restrict__ wl,
-                              const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu) {
-    MG_LOOP(u, nu) col[u] = assemble_local(wl, uoff, uidx, u);
+                              sem::Copies cp, int64_t nu) {
+    MG_LOOP(u, nu) col[u] = assemble_local(wl, cp, u);
 }
 
 // ---- Lanczos on M = D^-1/2 A D^-1/2 (float32 vectors, float64 partial sums)
@@ -668,12 +676,12 @@ __global__ void half_jacobi_kernel(float* __restrict__ out, const float* __restr
 // w = D^-1/2 (A p) - beta vprev and partials of w . v
 __global__ void lanczos_w_kernel(float* __restrict__ w, const float* __restrict__ wl, const float* __restrict__ v,
                                  const float* __restrict__ vprev, const float* __restrict__ minv, float beta,
-                                 const int32_t* __restrict__ uoff, const int32_t* __restrict__ uidx, int64_t nu,
+                                 sem::Copies cp, int64_t nu,
                                  double* __restrict__ part) {
     __shared__ double s_red[kBlock / 64];
     double s = 0.0;
     MG_LOOP(u, nu) {
-        const float wv = sqrtf(minv[u]) * assemble_local(wl, uoff, uidx, u) - beta * vprev[u];
+        const float wv = sqrtf(minv[u]) * assemble_local(wl, cp, u) - beta * vprev[u];
         w[u] = wv;
         s += (double)wv * v[u];
     }
@@ -824,7 +832,7 @@ int estimate_lmax(sem_mg_t mg, MgLevel& lv, int steps, uint32_t seed) {
     const int64_t nu = lv.nu;
     const unsigned g = vgrid(nu);
     float *v = lv.r, *vprev = lv.b, *w = lv.x, *p = lv.d;
-    const int32_t *uoff = lv.gs->uoff, *uidx = lv.gs->uidx;
+    const sem::Copies cp{lv.gs->link, lv.gs->more};
     start_kernel<<<g, kBlock, 0, st>>>(v, nu, seed, mg->part);
     SEM_LAUNCH_CHECK(mg->ctx);
     double nn;
@@ -839,7 +847,7 @@ int estimate_lmax(sem_mg_t mg, MgLevel& lv, int steps, uint32_t seed) {
         half_jacobi_kernel<<<g, kBlock, 0, st>>>(p, v, lv.minv, nu);
         rc = level_ax(mg, lv, lv.wl, p, nullptr);
         if (rc) return rc;
-        lanczos_w_kernel<<<g, kBlock, 0, st>>>(w, lv.wl, v, vprev, lv.minv, j ? beta : 0.f, uoff, uidx, nu,
+        lanczos_w_kernel<<<g, kBlock, 0, st>>>(w, lv.wl, v, vprev, lv.minv, j ? beta : 0.f, cp, nu,
                                                mg->part);
         SEM_LAUNCH_CHECK(mg->ctx);
         double alpha;
@@ -885,7 +893,7 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
     auto& Ls = mg->L;
     if (nl == 1) {
         MgLevel& c = Ls[0];
-        coarse_kernel<<<coarse_grid(c.nu), kBlock, 0, st>>>(xout, bin, nullptr, mg->ainv, c.gs->uoff, c.gs->uidx,
+        coarse_kernel<<<coarse_grid(c.nu), kBlock, 0, st>>>(xout, bin, nullptr, mg->ainv, sem::Copies{c.gs->link, c.gs->more},
                                                     (int)c.nu, skip);
         SEM_LAUNCH_CHECK(mg->ctx);
         return SEM_OK;
@@ -895,17 +903,17 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
         MgLevel& lv = Ls[q];
         MgLevel& nx = Ls[q + 1];
         const unsigned g = vgrid(lv.nu);
-        const int32_t *uoff = lv.gs->uoff, *uidx = lv.gs->uidx;
+        const sem::Copies cp{lv.gs->link, lv.gs->more};
         float* x = q == 0 ? xout : lv.x;
         cheb_first_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, q == 0 ? nullptr : lv.b, q == 0 ? bin : nullptr,
-                                                q == 0 ? nullptr : lv.bl, lv.minv, lv.c0, uoff, uidx, lv.nu, skip);
+                                                q == 0 ? nullptr : lv.bl, lv.minv, lv.c0, cp, lv.nu, skip);
         for (int m = 1; m < mg->degree; ++m) {
             if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
-            cheb_step_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], uoff, uidx,
+            cheb_step_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], cp,
                                                    lv.nu, skip);
         }
         if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
-        cheb_resid_kernel<<<g, kBlock, 0, st>>>(lv.r, lv.wl, uoff, uidx, lv.nu, skip);
+        cheb_resid_kernel<<<g, kBlock, 0, st>>>(lv.r, lv.wl, cp, lv.nu, skip);
         if (lv.kind == 1 && lv.lx == 2)
             restrict_h_kernel<<<vgrid(8 * nx.nel), kBlock, 0, st>>>(nx.bl, lv.r, lv.gs->lid, lv.own, lv.n, nx.n,
                                                                     nx.nel, skip);
@@ -917,7 +925,7 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
     }
     {
         MgLevel& c = Ls[nl - 1];
-        coarse_kernel<<<coarse_grid(c.nu), kBlock, 0, st>>>(c.x, nullptr, c.bl, mg->ainv, c.gs->uoff, c.gs->uidx,
+        coarse_kernel<<<coarse_grid(c.nu), kBlock, 0, st>>>(c.x, nullptr, c.bl, mg->ainv, sem::Copies{c.gs->link, c.gs->more},
                                                     (int)c.nu, skip);
         SEM_LAUNCH_CHECK(mg->ctx);
     }
@@ -925,7 +933,7 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
         MgLevel& lv = Ls[q];
         MgLevel& nx = Ls[q + 1];
         const unsigned g = vgrid(lv.nu);
-        const int32_t *uoff = lv.gs->uoff, *uidx = lv.gs->uidx;
+        const sem::Copies cp{lv.gs->link, lv.gs->more};
         float* x = q == 0 ? xout : lv.x;
         const float* b = q == 0 ? bin : lv.b;
         const int f3 = lv.lx * lv.lx * lv.lx;
@@ -938,10 +946,10 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
                                                                                 nx.gs->lid, lv.J, lv.lx, nx.lx,
                                                                                 lv.kind, lv.n, nx.n, lv.nel, skip);
         if ((rc = level_ax(mg, lv, lv.wl, x, skip))) return rc;
-        cheb_post_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, uoff, uidx, lv.nu, skip);
+        cheb_post_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
         for (int m = 1; m < mg->degree; ++m) {
             if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
-            cheb_step_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], uoff, uidx,
+            cheb_step_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], cp,
                                                    lv.nu, skip);
         }
         SEM_LAUNCH_CHECK(mg->ctx);
@@ -1270,7 +1278,7 @@ extern "C" int sem_mg_create(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A
             if (hb64) add_scaled_kernel<<<gl, kBlock, 0, st>>>(dl, hb64, 1.0, nloc);
         }
         MG_ALLOC(lv.minv, sizeof(float) * lv.nu);
-        diag_recip_kernel<<<vgrid(lv.nu), kBlock, 0, st>>>(lv.minv, dl, lv.gs->uoff, lv.gs->uidx, lv.nu);
+        diag_recip_kernel<<<vgrid(lv.nu), kBlock, 0, st>>>(lv.minv, dl, sem::Copies{lv.gs->link, lv.gs->more}, lv.nu);
         MG_ALLOC(lv.own, nloc);
         owner_kernel<<<gl, kBlock, 0, st>>>(lv.own, lv.gs->lid, lv.gs->uoff, lv.gs->uidx, nloc);
         const size_t vu = sizeof(float) * std::max<int64_t>(lv.nu, 1);
@@ -1312,7 +1320,7 @@ extern "C" int sem_mg_create(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A
                 for (int64_t j = 0; j < m; ++j) {
                     unit_local_kernel<<<gl, kBlock, 0, st>>>(ul, lv.gs->lid, j, nloc);
                     MG_TTRY(sem::launch_ax(ctx, sem::AxKind::F64, a64, wl, ul, nullptr, nullptr, nullptr));
-                    column_kernel<<<vgrid(m), kBlock, 0, st>>>(cols + j * m, wl, lv.gs->uoff, lv.gs->uidx, m);
+                    column_kernel<<<vgrid(m), kBlock, 0, st>>>(cols + j * m, wl, sem::Copies{lv.gs->link, lv.gs->more}, m);
                 }
                 SEM_LAUNCH_CHECK(ctx);
                 MG_TTRY(sem::check_hip(ctx, hipStreamSynchronize(st), "sem_mg_create: hipStreamSynchronize"));
