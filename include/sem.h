@@ -179,11 +179,14 @@ int sem_ax_helmholtz(sem_ctx_t ctx, void* w, const void* u,
 /* Kernel variants of the float64 operator (sem_ax and sem_ax_helmholtz with
  * field dtype SEM_F64), all computing the same sums (results agree to
  * rounding):
- *   SEM_AX_COLUMN     one thread per (i, j) column, u's column in registers,
- *                     the element's slices and fluxes in LDS (Sec. 4.2, the
- *                     per-(i, j) thread mapping with a k loop);
- *   SEM_AX_COLUMN_PF  the same with the opposite choice of fetching the next
- *                     slice's factors one slice ahead;
+ *   SEM_AX_COLUMN     the built-in kernel: one thread per (i, j) column, u's
+ *                     column in registers, the element's slices and fluxes in
+ *                     LDS (Sec. 4.2, the per-(i, j) thread mapping with a k
+ *                     loop); at lx = 12, and at lx = 5 and 6 for large arrays,
+ *                     if all of them lie on 16 bytes: whole elements with
+ *                     the derivatives on matrix cores;
+ *   SEM_AX_COLUMN_PF  the column mapping with the opposite choice of fetching
+ *                     the next slice's factors one slice ahead;
  *   SEM_AX_SLICE      the column mapping with the element passing through LDS
  *                     one slice at a time (double-buffered, one barrier per
  *                     slice; 6 lx^2 LDS values per element instead of ~3 lx^3);

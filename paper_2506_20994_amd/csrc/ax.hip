@@ -9,7 +9,10 @@
 // rows of a k-slice, so the element is staged once in LDS; the r/s fluxes are
 // staged in LDS for the transposed pass.
 // The streamed arrays (u, w, h1, g11..g23) are read and written exactly once,
-// with consecutive threads on consecutive addresses.
+// with consecutive threads on consecutive addresses.  Where lx^2 columns fit waves
+// and lines badly, or the registers of a column are what limits the waves, a second
+// kernel takes whole elements as they lie in memory and forms the derivatives on the
+// matrix cores (ax_flat_kernel; kFlat, flat_pays and kFlatSolver say where).
 //
 // Storage type TS (u, h1, G) and compute type TC:
 //   double / double   (SEM_F64)
@@ -161,6 +164,33 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// dot[blockIdx.x] = sum of v over the workgroup's NT threads, in a fixed order
+template <int NT>
+__device__ __forceinline__ void block_dot(double v, double* __restrict__ dot) {
+    const int tid = threadIdx.x;
+    if constexpr (NT % 64 == 0) {              // whole waves: shuffle, then one value per wave
+        __shared__ double s_red[NT / 64];
+        v = sem::wave_sum(v);
+        if ((tid & 63) == 0) s_red[tid >> 6] = v;
+        __syncthreads();
+        if (tid == 0) {
+            double t = 0.0;
+            for (int q = 0; q < NT / 64; ++q) t += s_red[q];
+            dot[blockIdx.x] = t;
+        }
+    } else {                                   // partial last wave: LDS tree
+        __shared__ double s_red[NT];
+        s_red[tid] = v;
+        __syncthreads();
+        constexpr int P2 = NT <= 128 ? 64 : NT <= 256 ? 128 : 256;
+        for (int st = P2; st > 0; st >>= 1) {
+            if (tid < st && tid + st < NT) s_red[tid] += s_red[tid + st];
+            __syncthreads();
+        }
+        if (tid == 0) dot[blockIdx.x] = s_red[0];
+    }
 }
 
 // Any form returns at once when skip is given and *skip is non-zero (a
@@ -322,30 +352,313 @@ ax_kernel(TW* __restrict__ w, const TU* __restrict__ u,
         }
         if (FUSE) pw += (double)uc[k] * (double)(TW)acc;
     }
-    if (FUSE) {
-        constexpr int NT = EPB * TPE;
-        if constexpr (NT % 64 == 0) {          // whole waves: shuffle, then one value per wave
-            __shared__ double s_red[NT / 64];
-            pw = sem::wave_sum(pw);
-            if ((tid & 63) == 0) s_red[tid >> 6] = pw;
-            __syncthreads();
-            if (tid == 0) {
-                double t = 0.0;
-                for (int q = 0; q < NT / 64; ++q) t += s_red[q];
-                dot[blockIdx.x] = t;
+    if constexpr (FUSE) block_dot<EPB * TPE>(pw, dot);
+}
+
+// ---- the operator on whole elements and matrix cores -------------------------
+// Each derivative is a product of the lx x lx matrix with the element's lines:
+// out[q][line] = sum_l D[l][q] in[l][line].  A wave takes 16 lines at a time as
+// the columns of 16x16x4 MFMA blocks; lane (n, g), n = lane % 16, g = lane / 16,
+// feeds in[4 s + g][line n] in step s and receives out[4 r + g][line n] in
+// register r.  Every value passes LDS once per direction and product instead of
+// being read 2 lx times by the column mapping, and no thread owns a node: the
+// streamed arrays are read and written in memory order, V neighbouring nodes a lane
+// from the workgroup's first node on, all of them issued at the start.
+// What bounded the column mapping: at lx = 12 its 6 lx LDS reads per node (557 us
+// of 775 at 32768 elements), elsewhere slices that are no whole lines (lx 5, 6, 7,
+// 9, 10, 11) and loads of 2 and 4 bytes a lane.  Per 16.8M nodes with h1, column
+// mapping against this kernel: float64 lx 5 230 / 220, lx 6 224 / 200, lx 12
+// 232 / 207 us (6.0, 5.9 TB/s); float32 lx 4 115 / 101, 5 131 / 109, 6 124 / 103,
+// 7 121 / 111, 10 125 / 109, 12 127 / 107; bfloat16 lx 4 86 / 61,
+// 5 99 / 78, 6 97 / 75, 7 108 / 80, 8 97 / 61, 9 123 / 86, 10 134 / 75, 11 146 / 84,
+// 12 164 / 74.
+typedef double mvec4d __attribute__((ext_vector_type(4)));
+typedef float mvec4f __attribute__((ext_vector_type(4)));
+template <typename TC> struct Mfma;
+template <> struct Mfma<double> {
+    typedef mvec4d acc;
+    // logical row of A's lane n: the result's register r of group g is row 4 r + g
+    __device__ static int row(int n) { return n; }
+    __device__ static acc mul(double a, double b, acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+};
+template <> struct Mfma<float> {
+    typedef mvec4f acc;
+    // the float32 block returns row 4 g + r there: A's rows are permuted to match
+    __device__ static int row(int n) { return 4 * (n & 3) + (n >> 2); }
+    __device__ static acc mul(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+
+// Where it is the built-in kernel.  The column mapping stays where it measured no
+// slower: float64 lx 4 (194 against 195 us), 7 (224 / 242), 8 (187 / 196),
+// 9 (224 / 242), 10 (221 / 223), 11 (224 / 273); float32 lx 8 (98 / 100),
+// 9 (131 / 123, but 13.0 / 15.4 us at 1500 elements) and 11 (128 / 132).  The matrix
+// blocks pad lx to a multiple of 4, which is what the odd orders pay for.
+template <int LX, typename TS>
+constexpr bool kFlat = std::is_same<TS, double>::value ? (LX == 5 || LX == 6 || LX == 12)
+                     : std::is_same<TS, float>::value ? (LX >= 4 && LX != 8 && LX != 9 && LX != 11) : LX >= 4;
+
+// Where it is that at every size; the others of kFlat take it for large arrays
+// (flat_pays).
+template <int LX, typename TS>
+constexpr bool kFlatAlways = kFlat<LX, TS> && (LX > 7 || (std::is_same<TS, uint16_t>::value && LX > 5));
+
+// Where the solver form takes it: not at lx = 4, 5 and float32 lx = 7, where the gather
+// hides what the accesses gain.  One conjugate-gradient iteration, column / whole
+// elements, us: float64 lx 5 26.8 / 30.0 at 16^3 elements and 66.1 / 68.3 at 26^3, lx 6
+// 18.2 / 17.1 at 6^3, 24.7 / 25.6 at 12^3, 54.1 / 52.7 at 20^3 and 101.9 / 102.1 at
+// 26^3; float32 lx 5 47.1 / 49.5 at 26^3, lx 6 25.5 / 24.0 at 12^3, 38.5 / 39.6 at 20^3
+// and 65.8 / 65.1 at 26^3, lx 7 36.9 / 39.1 at 16^3 and 97.3 / 96.2 at 26^3; bfloat16
+// lx 5 42.1 / 46.8 and lx 6 61.1 / 58.5 at 26^3.
+template <int LX, typename TS>
+constexpr bool kFlatSolver = kFlatAlways<LX, TS> || (kFlat<LX, TS> && LX == 6);
+
+// EPB elements per workgroup of NW waves, V nodes per access (V divides the
+// workgroup's nodes): two or three accesses per thread and array, and workgroups
+// that fill the 16 waves that four per SIMD allow (six waves leave four idle:
+// float32 lx = 9 measured 145 us with six and 123 with eight)
+template <int LX, bool F64> struct ShapeF;
+template <int LX> struct ShapeF<LX, true> {
+    static constexpr int EPB = LX == 5 ? 8 : LX == 6 ? 4 : 1;
+    static constexpr int NW = LX == 12 ? 8 : 4;
+    static constexpr int V = 2;
+};
+template <int LX> struct ShapeF<LX, false> {
+    static constexpr int EPB = LX == 4 ? 32 : LX == 5 ? 16 : LX == 6 ? 8 : LX <= 9 ? 4 : 2;
+    static constexpr int NW = LX == 7 ? 3 : LX == 9 ? 8 : LX == 11 ? 7 : LX == 12 ? 8 : 4;
+    static constexpr int V = LX == 11 ? 2 : 4;
+};
+
+template <bool WP>
+__device__ __forceinline__ void element_sync() {
+    if (WP) wave_sync();
+    else __syncthreads();
+}
+
+template <int LX, int EPB, int NW, int V, typename TU, typename TS, typename TC, typename TW, bool FUSE, bool GATHER,
+          bool HB>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 8)))
+ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
+               const TC* __restrict__ dx, const TC* __restrict__ dy, const TC* __restrict__ dz,
+               const TC* __restrict__ dxt, const TC* __restrict__ dyt, const TC* __restrict__ dzt,
+               const TS* __restrict__ h1, const TS* __restrict__ g11, const TS* __restrict__ g22,
+               const TS* __restrict__ g33, const TS* __restrict__ g12, const TS* __restrict__ g13,
+               const TS* __restrict__ g23, int64_t nel, const int* __restrict__ skip,
+               double* __restrict__ dot, const int32_t* __restrict__ lid, const TS* __restrict__ hb) {
+    typedef typename Mfma<TC>::acc acc_t;
+    constexpr int L2 = LX * LX, L3 = L2 * LX, C = EPB * L2, N = EPB * L3;
+    constexpr int KS = (LX + 3) / 4;
+    constexpr int T = NW * 64, NQ = (N + V * T - 1) / (V * T);
+    constexpr int TILES = (C + 15) / 16;
+    // whole elements per wave, its nodes and its lines: no workgroup barriers
+    constexpr bool WP = N == V * T * NQ && (V * 64 * NQ) % L3 == 0 && TILES * 16 == C && TILES % NW == 0;
+    typedef TS vec_s __attribute__((ext_vector_type(V)));
+    typedef TU vec_u __attribute__((ext_vector_type(V)));
+    typedef TC vec_c __attribute__((ext_vector_type(V)));
+    typedef TW vec_w __attribute__((ext_vector_type(V)));
+    static_assert(N % V == 0, "vectors");
+    if (skip && *skip) return;
+    __shared__ __attribute__((aligned(16))) TC s_t[N], s_r[N], s_s[N];    // u and the t-direction; r; s
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n = lane & 15, g = lane >> 4;
+    const int64_t e0 = (int64_t)blockIdx.x * EPB, b0 = e0 * L3;           // first element and node of the workgroup
+    const int nn = (nel - e0 < EPB ? (int)(nel - e0) : EPB) * L3;         // its nodes
+
+    // A operand of out = D^T in: lane (n, g), step s holds D[4 s + g][row n]
+    auto matrix = [&](TC (&a)[KS], const TC* __restrict__ m) {
+        const int q = Mfma<TC>::row(n);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int l = 4 * s + g;
+            const bool in = l < LX && q < LX;
+            const TC v = m[in ? l * LX + q : 0];
+            a[s] = in ? v : TC(0);
+        }
+    };
+    TC ar[KS], as[KS], at[KS];
+    matrix(ar, dx);
+    matrix(as, dy);
+    matrix(at, dz);
+
+    // this thread's vector q starts at node at_node(q)
+    auto at_node = [&](int q) { return V * (WP ? (wv * NQ + q) * 64 + lane : q * T + tid); };
+    const bool full = nn == N;                 // uniform: all but the mesh's last workgroup
+    // nodes o .. o + V - 1 of a streamed array.  A whole workgroup reads without a
+    // branch (threads past its last vector read that one); the last one reads node by
+    // node, zero past the end.
+    auto load_whole = [&](const TS* __restrict__ p, int o) {
+        const vec_s* q = reinterpret_cast<const vec_s*>(p + b0 + min(o, N - V));
+        return __builtin_nontemporal_load(q);
+    };
+    auto load_part = [&](const TS* __restrict__ p, int o) {
+        vec_s v = 0;
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+            if (o + i < nn) v[i] = p[b0 + o + i];
+        return v;
+    };
+    auto to_c = [](const vec_s& v) {
+        vec_c c;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            if constexpr (std::is_same<TS, uint16_t>::value) c[i] = __uint_as_float((uint32_t)v[i] << 16);
+            else c[i] = v[i];
+        }
+        return c;
+    };
+    vec_c uv[NQ];
+    vec_s us[NQ], f11[NQ], f22[NQ], f33[NQ], f12[NQ], f13[NQ], f23[NQ], fh[NQ];
+    auto load_all = [&](auto load) {
+        if constexpr (!GATHER)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) us[q] = load(u, at_node(q));
+        if (h1)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) fh[q] = load(h1, at_node(q));
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int o = at_node(q);
+            f11[q] = load(g11, o); f22[q] = load(g22, o); f33[q] = load(g33, o);
+            f12[q] = load(g12, o); f13[q] = load(g13, o); f23[q] = load(g23, o);
+        }
+    };
+    typedef int32_t vec_i __attribute__((ext_vector_type(V)));
+    vec_i id[NQ];
+    if constexpr (GATHER) {                    // the numbering ahead of the factors, its nodes of u after them
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int o = at_node(q);
+            if (full) {
+                id[q] = __builtin_nontemporal_load(reinterpret_cast<const vec_i*>(lid + b0 + min(o, N - V)));
+            } else {
+#pragma unroll
+                for (int i = 0; i < V; ++i) id[q][i] = o + i < nn ? lid[b0 + o + i] : -1;
             }
-        } else {                               // partial last wave: LDS tree
-            __shared__ double s_red[NT];
-            s_red[tid] = pw;
-            __syncthreads();
-            constexpr int P2 = NT <= 128 ? 64 : NT <= 256 ? 128 : 256;
-            for (int st = P2; st > 0; st >>= 1) {
-                if (tid < st && tid + st < NT) s_red[tid] += s_red[tid + st];
-                __syncthreads();
-            }
-            if (tid == 0) dot[blockIdx.x] = s_red[0];
         }
     }
+    if (full) load_all(load_whole);
+    else load_all(load_part);
+    if constexpr (GATHER) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int i = 0; i < V; ++i) uv[q][i] = id[q][i] >= 0 ? (TC)u[id[q][i]] : TC(0);
+    }
+    __builtin_amdgcn_sched_barrier(0);         // every load is in flight before anything waits
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if constexpr (!GATHER) uv[q] = to_c(us[q]);
+        if (at_node(q) < N) *reinterpret_cast<vec_c*>(s_t + at_node(q)) = uv[q];
+    }
+    element_sync<WP>();
+
+    const bool last = LX % 4 == 0 || 4 * (KS - 1) + g < LX;   // row 4 (KS - 1) + g exists
+    auto has = [&](int r) { return r + 1 < KS || last; };
+    // one line: out[q] = sum_l D[l][q] in[l], nodes `step` apart
+    auto product = [&](const TC (&a)[KS], const TC* in, int step) {
+        acc_t c = {0, 0, 0, 0};
+        TC b[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const TC v = in[has(s) ? (4 * s + g) * step : 0];
+            b[s] = has(s) ? v : TC(0);         // rows past lx: zeros of the matrix times zero
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) c = Mfma<TC>::mul(a[s], b[s], c);
+        return c;
+    };
+    auto put = [&](TC* out, int step, const acc_t& c, bool ok) {
+#pragma unroll
+        for (int r = 0; r < KS; ++r)
+            if (ok && has(r)) out[(4 * r + g) * step] = c[r];
+    };
+    // the wave's tiles; line c of the r-, s- and t-direction starts at
+    auto first_tile = [&]() { return WP ? wv * (TILES / NW) : wv; };
+    auto end_tile = [&]() { return WP ? (wv + 1) * (TILES / NW) : TILES; };
+    constexpr int STEP = WP ? 1 : NW;
+    auto r_at = [&](int c) { return c * LX; };
+    auto s_at = [&](int c) { return c / LX * L2 + c % LX; };
+    auto t_at = [&](int c) { return c / L2 * L3 + c % L2; };
+    for (int t = first_tile(); t < end_tile(); t += STEP) {
+        const bool ok = C % 16 == 0 || t * 16 + n < C;
+        const int c = ok ? t * 16 + n : C - 1;
+        const acc_t vr = product(ar, s_t + r_at(c), 1);
+        const acc_t vs = product(as, s_t + s_at(c), LX);
+        put(s_r + r_at(c), 1, vr, ok);
+        put(s_s + s_at(c), LX, vs, ok);
+    }
+    matrix(ar, dxt);
+    matrix(as, dyt);
+    element_sync<WP>();                        // u has been read along r and s
+    for (int t = first_tile(); t < end_tile(); t += STEP) {
+        const bool ok = C % 16 == 0 || t * 16 + n < C;
+        const int c = ok ? t * 16 + n : C - 1;
+        put(s_t + t_at(c), L2, product(at, s_t + t_at(c), L2), ok);   // a line's lanes are one wave: in place
+    }
+    matrix(at, dzt);
+    element_sync<WP>();
+    double pw = 0.0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int o = at_node(q);
+        if (o >= N) continue;
+        vec_c* pr = reinterpret_cast<vec_c*>(s_r + o);
+        vec_c* ps = reinterpret_cast<vec_c*>(s_s + o);
+        vec_c* pt = reinterpret_cast<vec_c*>(s_t + o);
+        const vec_c r = *pr, s = *ps, t = *pt;
+        const vec_c G11 = to_c(f11[q]), G22 = to_c(f22[q]), G33 = to_c(f33[q]), G12 = to_c(f12[q]), G13 = to_c(f13[q]),
+                    G23 = to_c(f23[q]);
+        vec_c H = 1;
+        if (h1) H = to_c(fh[q]);
+        const vec_c vr = H * (G11 * r + G12 * s + G13 * t);
+        const vec_c vs = H * (G12 * r + G22 * s + G23 * t);
+        const vec_c vt = H * (G13 * r + G23 * s + G33 * t);
+        *pr = vr;
+        *ps = vs;
+        *pt = vt;
+        // p^T A p = (D p)^T v (+ h2 B p^2)
+        if constexpr (FUSE)
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+                pw += (double)r[i] * (double)vr[i] + (double)s[i] * (double)vs[i] + (double)t[i] * (double)vt[i];
+    }
+    element_sync<WP>();
+    for (int t = first_tile(); t < end_tile(); t += STEP) {
+        const bool ok = C % 16 == 0 || t * 16 + n < C;
+        const int c = ok ? t * 16 + n : C - 1;
+        const acc_t vr = product(ar, s_r + r_at(c), 1);
+        const acc_t vs = product(as, s_s + s_at(c), LX);
+        const acc_t vt = product(at, s_t + t_at(c), L2);
+        put(s_r + r_at(c), 1, vr, ok);
+        put(s_s + s_at(c), LX, vs, ok);
+        put(s_t + t_at(c), L2, vt, ok);
+    }
+    element_sync<WP>();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int o = at_node(q);
+        if (o >= nn) continue;
+        vec_c v = *reinterpret_cast<const vec_c*>(s_t + o) + *reinterpret_cast<const vec_c*>(s_r + o) +
+                  *reinterpret_cast<const vec_c*>(s_s + o);
+        if constexpr (HB) {                    // Helmholtz: + h2 B u
+            const vec_c m = to_c(full ? load_whole(hb, o) : load_part(hb, o)) * uv[q];
+            if constexpr (FUSE)
+#pragma unroll
+                for (int i = 0; i < V; ++i) pw += (double)m[i] * (double)uv[q][i];
+            v += m;
+        }
+        vec_w x;
+#pragma unroll
+        for (int i = 0; i < V; ++i) x[i] = (TW)v[i];
+        if (full) {
+            vec_w* d = reinterpret_cast<vec_w*>(w + b0 + o);
+            __builtin_nontemporal_store(x, d);
+        } else {
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+                if (o + i < nn) w[b0 + o + i] = x[i];
+        }
+    }
+    if constexpr (FUSE) block_dot<T>(pw, dot);
 }
 
 // Slice-pipelined column mapping: one thread per (i, j) column as in
@@ -544,6 +857,9 @@ ax3d_kernel(TW* __restrict__ w, const TS* __restrict__ u,
     if (live) store_nt(w, g, (TW)acc);
 }
 
+// values between the planes of a solver copy of n nodes: 16-byte steps in every type
+constexpr int64_t plane_stride(int64_t n) { return (n + 7) / 8 * 8; }
+
 // The Helmholtz term is a template flag (HB), so that the two forms are
 // separate kernels (and separate rows of a kernel trace).
 // the float64 public form's kernel variants (SEM_AX_* of sem.h)
@@ -573,6 +889,44 @@ void launch_3d(sem_ctx_t ctx, void* w, const void* u, const void* const* D, cons
             (const TC*)D[4], (const TC*)D[5], (const TS*)h1, (const TS*)G[0], (const TS*)G[1],
             (const TS*)G[2], (const TS*)G[3], (const TS*)G[4], (const TS*)G[5], nel, (const TS*)hb);
     }
+}
+
+// Below about a hundred megabytes of arrays the short orders stay on the column
+// mapping, whose workgroups are smaller: a launch that is over in a few waves of
+// workgroups is paced by the chain load, LDS, product, LDS, store of one of them.
+// Column / whole elements, us: float64 lx 5 at 8000 elements (64 MB) 16.6 / 18.5, at
+// 16000 34.8 / 32.7; lx 6 at 5000 (69 MB) 15.0 / 18.6, at 8000 (111 MB) 29.9 / 27.2;
+// float32 lx 4 at 32000 (66 MB) 14.5 / 17.3, at 50000 25.0 / 25.0; lx 5 at 16000
+// (64 MB) 16.1 / 18.9, at 32000 36.0 / 32.0; lx 6 at 8000 (55 MB) 14.3 / 16.0, at 16000
+// 29.7 / 26.9; lx 7 at 8000 (88 MB) 22.9 / 25.3, at 16000 44.6 / 41.5; bfloat16 lx 4 at
+// 50000 (51 MB) 17.8 / 19.9, lx 5 at 32000 (64 MB) 22.5 / 23.8, at 50000 (100 MB)
+// 41.1 / 33.5.  From bfloat16 lx 6 (16000: 20.6 / 19.7; 8000: 13.1 / 13.7, launch-bound)
+// and lx 7 on, and for the long orders, whole elements are not slower at any size.
+template <int LX, typename TS>
+bool flat_pays(int64_t nel) {
+    return kFlatAlways<LX, TS> || nel * (LX * LX * LX) * 8 * (int64_t)sizeof(TS) >= (96 << 20);
+}
+
+// whole elements also need alignment: accesses are V values wide, so every array it
+// streams has to lie on that (any array of torch or hipMalloc does; a view into one
+// may not, and takes the column mapping)
+template <int LX, typename TS, typename TW>
+bool flat_aligned(const void* w, const void* u, const void* h1, const void* const* G, const void* hb) {
+    constexpr int V = ShapeF<LX, std::is_same<TS, double>::value>::V;
+    uintptr_t bits = (uintptr_t)u | (uintptr_t)h1 | (uintptr_t)hb;
+    for (int q = 0; q < 6; ++q) bits |= (uintptr_t)G[q];
+    return bits % (V * sizeof(TS)) == 0 && (uintptr_t)w % (V * sizeof(TW)) == 0;
+}
+
+template <int LX, typename TU, typename TS, typename TC, typename TW, bool FUSE, bool GATHER, bool HB>
+void launch_flat(sem_ctx_t ctx, void* w, const void* u, const void* const* D, const void* h1, const void* const* G,
+                 int64_t nel, const int* skip, double* dot, const int32_t* lid, const void* hb) {
+    typedef ShapeF<LX, std::is_same<TS, double>::value> F;
+    ax_flat_kernel<LX, F::EPB, F::NW, F::V, TU, TS, TC, TW, FUSE, GATHER, HB>
+        <<<(unsigned)((nel + F::EPB - 1) / F::EPB), F::NW * 64, 0, ctx->stream>>>(
+            (TW*)w, (const TU*)u, (const TC*)D[0], (const TC*)D[1], (const TC*)D[2], (const TC*)D[3], (const TC*)D[4],
+            (const TC*)D[5], (const TS*)h1, (const TS*)G[0], (const TS*)G[1], (const TS*)G[2], (const TS*)G[3],
+            (const TS*)G[4], (const TS*)G[5], nel, skip, dot, lid, (const TS*)hb);
 }
 
 // a non-default variant of the float64 public form; false if it does not exist
@@ -626,6 +980,27 @@ int launch_form(sem_ctx_t ctx, void* w, const void* u, const void* const* D, con
     constexpr int EPB = Shape<LX>::EPB;
     const int64_t blocks = (nel + EPB - 1) / EPB;
     if (blocks > 0x7fffffff) return sem::fail(ctx, SEM_EINVAL, "sem_ax: nel too large");
+    if (dot && !lid) return sem::fail(ctx, SEM_EINVAL, "launch_ax: the fused dot needs the solver form");
+    if (lid && !gp) return sem::fail(ctx, SEM_EINVAL, "launch_ax: the solver form needs packed factors");
+    if constexpr (kFlatSolver<LX, TS>) {
+        if (lid) {                             // the solver's copy is planes (sem::factor_stride)
+            const int64_t stride = plane_stride(nel * LX * LX * LX);
+            const void* P[6];
+            for (int q = 0; q < 6; ++q) P[q] = (const TS*)gp + q * stride;
+            if (dot) launch_flat<LX, TU, TS, TC, TW, true, true, HB>(ctx, w, u, D, h1, P, nel, skip, dot, lid, hb);
+            else launch_flat<LX, TU, TS, TC, TW, false, true, HB>(ctx, w, u, D, h1, P, nel, skip, dot, lid, hb);
+            SEM_LAUNCH_CHECK(ctx);
+            return SEM_OK;
+        }
+    }
+    if constexpr (kFlat<LX, TS> && std::is_same<TU, TS>::value) {
+        if (!lid && (variant == SEM_AX_DEFAULT || variant == SEM_AX_COLUMN) && nel <= 0x7fffffff &&
+            flat_pays<LX, TS>(nel) && flat_aligned<LX, TS, TW>(w, u, h1, G, hb)) {
+            launch_flat<LX, TU, TS, TC, TW, false, false, HB>(ctx, w, u, D, h1, G, nel, skip, nullptr, nullptr, hb);
+            SEM_LAUNCH_CHECK(ctx);
+            return SEM_OK;
+        }
+    }
     if (!lid && !dot && variant >= 0 &&
         launch_variant<LX, TS, TC, TW, HB>(ctx, variant, w, u, D, h1, G, nel, hb)) {
         SEM_LAUNCH_CHECK(ctx);
@@ -636,15 +1011,13 @@ int launch_form(sem_ctx_t ctx, void* w, const void* u, const void* const* D, con
         (const TS*)G[1], (const TS*)G[2], (const TS*)G[3], (const TS*)G[4], (const TS*)G[5], \
         nel, skip, dot, lid, (const TS*)gp, (const TS*)hb
     const dim3 grid((unsigned)blocks), block(EPB * LX * LX);
-    if (lid && !gp) return sem::fail(ctx, SEM_EINVAL, "launch_ax: the solver form needs packed factors");
-    if (dot && lid)
-        ax_kernel<LX, EPB, TU, TS, TC, TW, true, true, HB><<<grid, block, 0, ctx->stream>>>(SEM_AX_ARGS);
-    else if (lid)
-        ax_kernel<LX, EPB, TU, TS, TC, TW, false, true, HB><<<grid, block, 0, ctx->stream>>>(SEM_AX_ARGS);
-    else if (!dot)
-        ax_kernel<LX, EPB, TU, TS, TC, TW, false, false, HB><<<grid, block, 0, ctx->stream>>>(SEM_AX_ARGS);
-    else
-        return sem::fail(ctx, SEM_EINVAL, "launch_ax: the fused dot needs the solver form");
+    if constexpr (!kFlatSolver<LX, TS>) {
+        if (dot)
+            ax_kernel<LX, EPB, TU, TS, TC, TW, true, true, HB><<<grid, block, 0, ctx->stream>>>(SEM_AX_ARGS);
+        else if (lid)
+            ax_kernel<LX, EPB, TU, TS, TC, TW, false, true, HB><<<grid, block, 0, ctx->stream>>>(SEM_AX_ARGS);
+    }
+    if (!lid) ax_kernel<LX, EPB, TU, TS, TC, TW, false, false, HB><<<grid, block, 0, ctx->stream>>>(SEM_AX_ARGS);
 #undef SEM_AX_ARGS
     SEM_LAUNCH_CHECK(ctx);
     return SEM_OK;
@@ -670,6 +1043,13 @@ int dispatch(sem_ctx_t ctx, int lx, void* w, const void* u, const void* const* D
 #undef SEM_AX_CASE
         default: return sem::fail(ctx, SEM_EUNSUPPORTED_LX, "sem_ax: lx=%d outside [2,12]", lx);
     }
+}
+
+// elements per workgroup of the solver form
+template <int LX, typename TS>
+constexpr int epb_of() {
+    if constexpr (kFlatSolver<LX, TS>) return ShapeF<LX, std::is_same<TS, double>::value>::EPB;
+    else return Shape<LX>::EPB;
 }
 
 size_t dsize(sem_dtype_t t) { return t == SEM_F64 ? 8 : t == SEM_F32 ? 4 : 2; }
@@ -744,16 +1124,31 @@ extern "C" int sem_ax_helmholtz(sem_ctx_t ctx, void* w, const void* u, const voi
 
 namespace sem {
 
-int ax_blocks(int lx, int64_t nel) {
+// workgroups of the solver form
+int ax_blocks(AxKind kind, int lx, int64_t nel) {
     int epb = 1;
     switch (lx) {
-#define SEM_AX_EPB(L) case L: epb = Shape<L>::EPB; break;
+#define SEM_AX_EPB(L) case L: epb = kind == AxKind::F64 ? epb_of<L, double>() : kind == AxKind::F32 ? epb_of<L, float>() \
+                                   : epb_of<L, uint16_t>(); break;
         SEM_AX_EPB(2) SEM_AX_EPB(3) SEM_AX_EPB(4) SEM_AX_EPB(5) SEM_AX_EPB(6) SEM_AX_EPB(7)
         SEM_AX_EPB(8) SEM_AX_EPB(9) SEM_AX_EPB(10) SEM_AX_EPB(11) SEM_AX_EPB(12)
 #undef SEM_AX_EPB
         default: break;
     }
     return (int)((nel + epb - 1) / epb);
+}
+
+int64_t factor_stride(AxKind kind, int lx, int64_t n) {
+    bool flat = false;
+    switch (lx) {
+#define SEM_AX_FLAT(L) case L: flat = kind == AxKind::F64 ? kFlatSolver<L, double> : kind == AxKind::F32 ? kFlatSolver<L, float> \
+                                    : kFlatSolver<L, uint16_t>; break;
+        SEM_AX_FLAT(2) SEM_AX_FLAT(3) SEM_AX_FLAT(4) SEM_AX_FLAT(5) SEM_AX_FLAT(6) SEM_AX_FLAT(7)
+        SEM_AX_FLAT(8) SEM_AX_FLAT(9) SEM_AX_FLAT(10) SEM_AX_FLAT(11) SEM_AX_FLAT(12)
+#undef SEM_AX_FLAT
+        default: break;
+    }
+    return flat ? plane_stride(n) : 0;
 }
 
 int launch_ax(sem_ctx_t ctx, AxKind kind, const AxArgs& a, void* w, const void* u,

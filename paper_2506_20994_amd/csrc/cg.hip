@@ -488,6 +488,16 @@ __global__ void pack_bf16_kernel(uint16_t* __restrict__ out, Six G, const double
     }
 }
 
+// the same values as six planes, stride apart (h1 times the factor where h1 is given)
+template <typename T>
+__global__ void plane_kernel(T* __restrict__ out, Six G, const double* __restrict__ h1, int64_t stride, int64_t n) {
+    GRID_LOOP(L, n) {
+        const double h = h1 ? h1[L] : 1.0;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) out[a * stride + L] = cvt<T>(h1 ? h * G.g[a][L] : G.g[a][L]);
+    }
+}
+
 template <typename T>
 __global__ void pack_kernel(T* __restrict__ out, Six G, int64_t n) {
     GRID_LOOP(L, n) {
@@ -819,7 +829,7 @@ int pcg_run(sem_cg_t cg, Level& lv, const T* rhs, double tol, int maxit, int che
     pcg_init_kernel<T><<<g, kBlock, 0, st>>>(x, r, p, rhs, minv, n, cg->part);
     pcg_init_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g, tol, maxit);
     SEM_LAUNCH_CHECK(ctx);
-    const int nb = sem::ax_blocks(lv.A.lx, lv.A.nel);
+    const int nb = sem::ax_blocks(lv.kind, lv.A.lx, lv.A.nel);
     int seq = 0;
     for (;;) {
         for (int q = 0; q < check_every; ++q, ++seq) {
@@ -905,7 +915,7 @@ int rr_run(sem_cg_t cg, Level& lv, double tol, double delta, int maxit, int chec
     pcg_init_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g, tol, maxit);
     set_delta<<<1, 1, 0, st>>>(cg->S, delta * delta);
     SEM_LAUNCH_CHECK(ctx);
-    const int nb = sem::ax_blocks(lv.A.lx, lv.A.nel);
+    const int nb = sem::ax_blocks(lv.kind, lv.A.lx, lv.A.nel);
     int nrep = 0, seq = 0;
     float* z = (float*)lv.z;
     float* wu = (float*)lv.wu;
@@ -991,7 +1001,7 @@ int fcg_run(sem_cg_t cg, Level& lv, const T* rhs, double tol, int maxit, int che
     pcg_init_kernel<T><<<g, kBlock, 0, st>>>(x, r, p, rhs, minv, n, cg->part);
     pcg_init_final<<<1, kFinal, 0, st>>>(cg->S, cg->part, (int)g, tol, maxit);
     SEM_LAUNCH_CHECK(ctx);
-    const int nb = sem::ax_blocks(lv.A.lx, lv.A.nel);
+    const int nb = sem::ax_blocks(lv.kind, lv.A.lx, lv.A.nel);
     const bool f64 = sizeof(T) == 8;
     bool fallen = false;
     std::vector<std::pair<int, double>> hist;   // (iteration, r.r) at each check
@@ -1066,19 +1076,23 @@ int remove_mean_u(sem_cg_t cg, double* xu) {
 
 namespace sem {
 
-void pack_factors_f32(hipStream_t st, float* out, const double* const* G, int64_t n, int lx) {
+void pack_factors(hipStream_t st, AxKind kind, void* out, const double* const* G, const double* h1, int64_t n, int lx) {
     Six six;
     for (int q = 0; q < 6; ++q) six.g[q] = G[q];
     six.l2 = lx * lx;
-    pack_kernel<float><<<vec_grid(n), kBlock, 0, st>>>(out, six, n);
-}
-
-void pack_factors_bf16(hipStream_t st, uint16_t* out, const double* const* G, const double* h1, int64_t n,
-                       int lx) {
-    Six six;
-    for (int q = 0; q < 6; ++q) six.g[q] = G[q];
-    six.l2 = lx * lx;
-    pack_bf16_kernel<<<vec_grid(n), kBlock, 0, st>>>(out, six, h1, n);
+    const unsigned g = vec_grid(n);
+    const int64_t stride = factor_stride(kind, lx, n);
+    if (kind == AxKind::F64) {
+        if (stride) plane_kernel<double><<<g, kBlock, 0, st>>>((double*)out, six, nullptr, stride, n);
+        else pack_kernel<double><<<g, kBlock, 0, st>>>((double*)out, six, n);
+    } else if (kind == AxKind::F32) {
+        if (stride) plane_kernel<float><<<g, kBlock, 0, st>>>((float*)out, six, nullptr, stride, n);
+        else pack_kernel<float><<<g, kBlock, 0, st>>>((float*)out, six, n);
+    } else if (stride) {
+        plane_kernel<uint16_t><<<g, kBlock, 0, st>>>((uint16_t*)out, six, h1, stride, n);
+    } else {
+        pack_bf16_kernel<<<g, kBlock, 0, st>>>((uint16_t*)out, six, h1, n);
+    }
 }
 
 }  // namespace sem
@@ -1117,7 +1131,9 @@ extern "C" int sem_cg_setup(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A,
     hipStream_t st = ctx->stream;
     const int64_t nu = cg->nu;
     const unsigned gl = vec_grid(n), gu = vec_grid(nu);
-    const int nb = sem::ax_blocks(A->lx, A->nel);
+    int nb = 0;                                // the operator's partials, in whichever precision
+    for (sem::AxKind k : {sem::AxKind::F64, sem::AxKind::F32, sem::AxKind::F32_BF16})
+        nb = std::max(nb, sem::ax_blocks(k, A->lx, A->nel));
     const size_t npart = (size_t)std::max(4 * kGrid, nb);
     const size_t u64 = sizeof(double) * nu, u32 = sizeof(float) * nu;
     auto bail = [&](int code) { sem_cg_destroy(cg); return code; };
@@ -1131,13 +1147,10 @@ extern "C" int sem_cg_setup(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A,
     CG_ALLOC(cg->x64, u64);
     CG_ALLOC(cg->r64, u64);
     CG_ALLOC(cg->wl64, sizeof(double) * n);
-    Six six;
-    for (int q = 0; q < 6; ++q) six.g[q] = Gp[q];
-    six.l2 = A->lx * A->lx;
     {
         void* gp = nullptr;
-        CG_ALLOC(gp, sizeof(double) * 6 * n);
-        pack_kernel<double><<<gl, kBlock, 0, st>>>((double*)gp, six, n);
+        CG_ALLOC(gp, sizeof(double) * sem::factor_count(sem::AxKind::F64, A->lx, n));
+        sem::pack_factors(st, sem::AxKind::F64, gp, Gp, nullptr, n, A->lx);
         cg->A64.Gp = gp;
     }
     {
@@ -1194,9 +1207,8 @@ extern "C" int sem_cg_setup(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A,
         for (int q = 0; q < 6; ++q) L.A.G[q] = nullptr;     // the solver form reads the packed copy
         {
             void* d = nullptr;
-            CG_ALLOC(d, vs * 6 * n);
-            if (bf) pack_bf16_kernel<<<gl, kBlock, 0, st>>>((uint16_t*)d, six, A->h1, n);   // h1 folded in
-            else pack_kernel<float><<<gl, kBlock, 0, st>>>((float*)d, six, n);
+            CG_ALLOC(d, vs * sem::factor_count(L.kind, A->lx, n));
+            sem::pack_factors(st, L.kind, d, Gp, bf ? A->h1 : nullptr, n, A->lx);   // bfloat16: h1 folded in
             L.A.Gp = d;
         }
         if (A->h1 && !bf) {

@@ -1250,15 +1250,10 @@ extern "C" int sem_mg_create(sem_ctx_t ctx, sem_gs_t gs, const sem_operator_t* A
             }
             const bool bf = q == 0 && opts->fine_bf16;   // bfloat16 factors on the finest level
             lv.axkind = bf ? sem::AxKind::F32_BF16 : sem::AxKind::F32;
-            if (bf) {
-                uint16_t* gp = nullptr;
-                MG_ALLOC(gp, sizeof(uint16_t) * 6 * nloc);
-                sem::pack_factors_bf16(st, gp, G64, nullptr, nloc, lx);
-                lv.A.Gp = gp;
-            } else {
-                float* gp = nullptr;
-                MG_ALLOC(gp, sizeof(float) * 6 * nloc);
-                sem::pack_factors_f32(st, gp, G64, nloc, lx);
+            {
+                void* gp = nullptr;
+                MG_ALLOC(gp, (bf ? sizeof(uint16_t) : sizeof(float)) * sem::factor_count(lv.axkind, lx, nloc));
+                sem::pack_factors(st, lv.axkind, gp, G64, nullptr, nloc, lx);
                 lv.A.Gp = gp;
             }
             lv.A.h1 = nullptr;

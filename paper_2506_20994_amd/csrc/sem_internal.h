@@ -83,7 +83,8 @@ struct AxArgs {
     // multiple of lx^2) and column ij, pair a of (g11,g22), (g33,g12),
     // (g13,g23) sits at 2-vector index 3 s + a lx^2 + ij.  bfloat16: one
     // record (h1 g11, h1 g22, h1 g33, h1 g12, h1 g13, h1 g23) per local node L
-    // at 6 L, h1 folded in (h1 is then null)
+    // at 6 L, h1 folded in (h1 is then null).  Where factor_stride() is not 0 the
+    // six are planes instead, that many values apart (bfloat16 with h1 folded in)
     const void* Gp = nullptr;
     // Helmholtz: h2 B per local node in the storage type (+ h2 B u), or null
     const void* hb = nullptr;
@@ -99,7 +100,14 @@ enum class AxKind {
 // lid < 0); the output stays in the local layout.
 int launch_ax(sem_ctx_t ctx, AxKind kind, const AxArgs& a, void* w, const void* u,
               const int* skip, double* dot, const int32_t* lid = nullptr);
-int ax_blocks(int lx, int64_t nel);
+int ax_blocks(AxKind kind, int lx, int64_t nel);
+// layout of the solver form's factors for n local nodes: values between two planes,
+// or 0 for the packed layout; a copy holds factor_count() values
+int64_t factor_stride(AxKind kind, int lx, int64_t n);
+inline int64_t factor_count(AxKind kind, int lx, int64_t n) {
+    const int64_t s = factor_stride(kind, lx, n);
+    return 6 * (s ? s : n);
+}
 // gather-scatter launch that returns at once when skip && *skip
 int gs_launch(sem_gs_t gs, void* u, sem_dtype_t dtype, const int* skip);
 // learned preconditioner z = P(r) on the bound operator (lp.hip); vectors
@@ -124,12 +132,10 @@ int64_t mg_nel(sem_mg_t mg);
 // inverse of a symmetric positive definite matrix (row-major n x n, float64,
 // in place) by Cholesky factorisation; false if a pivot is not positive
 bool spd_inverse(std::vector<double>& A, int n);
-// the six factors of an element-local operator packed for the solver form
-// (the layout of AxArgs::Gp) in float32 or bfloat16 (times h1, when given);
-// n local nodes, asynchronous on st
-void pack_factors_f32(hipStream_t st, float* out, const double* const* G, int64_t n, int lx);
-void pack_factors_bf16(hipStream_t st, uint16_t* out, const double* const* G, const double* h1, int64_t n,
-                       int lx);
+// the six factors of an element-local operator in the solver form's layout (that of
+// AxArgs::Gp) for `kind`, n local nodes: float64, float32, or bfloat16 times h1
+// (when given); out holds factor_count() values.  Asynchronous on st
+void pack_factors(hipStream_t st, AxKind kind, void* out, const double* const* G, const double* h1, int64_t n, int lx);
 
 #ifdef __HIPCC__
 // f(L) summed over the local copies L of node u in increasing order, starting
