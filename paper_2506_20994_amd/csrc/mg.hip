@@ -67,9 +67,16 @@ unsigned vgrid(int64_t n) {
 using sem::assemble_local;
 
 // ---------------------------------------------------------------- smoothing
+// The recurrence's vectors pass memory bound (the finest level of 32^3 elements at
+// lx = 8 has 11 million nodes; the steps reach about 4.7 TB/s of them), so nothing is
+// written that the next kernel has at hand: x of a first step is d, its r is b (both
+// only at degree 1, where no later step writes them), the post-smoothing's x takes d
+// of its first step together with the second's, and the last step leaves r and d.
+// That is 28 of 128 bytes per node at degree 2 and 28 of 194 at degree 3.
+
 // First Chebyshev step from x = 0: b is the caller's vector (bin) or the
-// assembled restricted field (bl, then also stored to bout); r = b,
-// d = c0 Minv b, x = d.
+// assembled restricted field (bl, then also stored to bout); d = c0 Minv b, and
+// where they are not null r = b, x = d.
 __global__ void cheb_first_kernel(float* __restrict__ x, float* __restrict__ r, float* __restrict__ d,
                                   float* __restrict__ bout, const float* __restrict__ bin,
                                   const float* __restrict__ bl, const float* __restrict__ minv, float c0,
@@ -80,25 +87,34 @@ __global__ void cheb_first_kernel(float* __restrict__ x, float* __restrict__ r, 
         const float mv = minv[u];              // vectors are read ahead of the assembly's chain of loads
         const float bv = bl ? assemble_local(bl, cp, u) : bin[u];
         if (bout) bout[u] = bv;
-        r[u] = bv;
+        if (r) r[u] = bv;
         const float dv = c0 * mv * bv;
         d[u] = dv;
-        x[u] = dv;
+        if (x) x[u] = dv;
     }
 }
 
-// Later steps: r -= A d (assembled from wl), d = c1 d + c2 Minv r, x += d.
-__global__ void cheb_step_kernel(float* __restrict__ x, float* __restrict__ r, float* __restrict__ d,
+// What a later step adds its d to: x, the first step's d (x = 0 before it), or x
+// and the first step's d
+enum { kToX, kToD, kToXD };
+
+// Later steps: r = rin - A d (assembled from wl), d = c1 d + c2 Minv r, x += d;
+// the last step of all keeps neither r nor d.  rin may be r.
+template <int TO, bool LAST>
+__global__ void cheb_step_kernel(float* __restrict__ x, const float* rin, float* r, float* __restrict__ d,
                                  const float* __restrict__ wl, const float* __restrict__ minv, float c1, float c2,
                                  sem::Copies cp, int64_t nu,
                                  const int* __restrict__ skip) {
     if (skip && *skip) return;
     MG_LOOP(u, nu) {
-        const float ro = r[u], dold = d[u], mv = minv[u], xv = x[u];
+        const float ro = rin[u], dold = d[u], mv = minv[u];
+        const float xv = TO == kToX ? x[u] : TO == kToD ? dold : x[u] + dold;
         const float rv = ro - assemble_local(wl, cp, u);
-        r[u] = rv;
         const float dv = c1 * dold + c2 * mv * rv;
-        d[u] = dv;
+        if (!LAST) {
+            r[u] = rv;
+            d[u] = dv;
+        }
         x[u] = xv + dv;
     }
 }
@@ -114,18 +130,23 @@ __global__ void cheb_resid_kernel(float* __restrict__ r, const float* __restrict
     }
 }
 
-// First step from a given x (post-smoothing): r = b - A x, d = c0 Minv r, x += d.
+// First step from a given x (post-smoothing): r = b - A x, d = c0 Minv r; if it is
+// the only one, x += d instead.
+template <bool ONLY>
 __global__ void cheb_post_kernel(float* __restrict__ x, float* __restrict__ r, float* __restrict__ d,
                                  const float* __restrict__ b, const float* __restrict__ wl,
                                  const float* __restrict__ minv, float c0, sem::Copies cp, int64_t nu, const int* __restrict__ skip) {
     if (skip && *skip) return;
     MG_LOOP(u, nu) {
-        const float bv = b[u], mv = minv[u], xv = x[u];
+        const float bv = b[u], mv = minv[u], xv = ONLY ? x[u] : 0.f;
         const float rv = bv - assemble_local(wl, cp, u);
-        r[u] = rv;
         const float dv = c0 * mv * rv;
-        d[u] = dv;
-        x[u] = xv + dv;
+        if (ONLY) {
+            x[u] = xv + dv;
+        } else {
+            r[u] = rv;
+            d[u] = dv;
+        }
     }
 }
 
@@ -886,6 +907,25 @@ void set_chebyshev(sem_mg_t mg, MgLevel& lv) {
     }
 }
 
+// step m >= 1 of a smoothing; pre-smoothing starts from x = 0 and right-hand side b
+int cheb_step(sem_mg_t mg, MgLevel& lv, float* x, const float* b, int m, bool pre, const int* skip) {
+    const unsigned g = vgrid(lv.nu);
+    hipStream_t st = mg->ctx->stream;
+    const sem::Copies cp{lv.gs->link, lv.gs->more};
+    const int rc = level_ax(mg, lv, lv.wl, lv.d, skip);
+    if (rc) return rc;
+    const bool last = !pre && m + 1 == mg->degree;
+#define MG_STEP(TO, LAST, RIN) cheb_step_kernel<TO, LAST><<<g, kBlock, 0, st>>>( \
+        x, RIN, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], cp, lv.nu, skip)
+    if (m == 1 && pre) MG_STEP(kToD, false, b);
+    else if (m == 1 && last) MG_STEP(kToXD, true, lv.r);
+    else if (m == 1) MG_STEP(kToXD, false, lv.r);
+    else if (last) MG_STEP(kToX, true, lv.r);
+    else MG_STEP(kToX, false, lv.r);
+#undef MG_STEP
+    return SEM_OK;
+}
+
 // the V-cycle on float32 unique vectors of level 0: x = V(b)
 int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
     hipStream_t st = mg->ctx->stream;
@@ -905,13 +945,12 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
         const unsigned g = vgrid(lv.nu);
         const sem::Copies cp{lv.gs->link, lv.gs->more};
         float* x = q == 0 ? xout : lv.x;
-        cheb_first_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, q == 0 ? nullptr : lv.b, q == 0 ? bin : nullptr,
+        const bool one = mg->degree == 1;
+        cheb_first_kernel<<<g, kBlock, 0, st>>>(one ? x : nullptr, one ? lv.r : nullptr, lv.d,
+                                                q == 0 ? nullptr : lv.b, q == 0 ? bin : nullptr,
                                                 q == 0 ? nullptr : lv.bl, lv.minv, lv.c0, cp, lv.nu, skip);
-        for (int m = 1; m < mg->degree; ++m) {
-            if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
-            cheb_step_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], cp,
-                                                   lv.nu, skip);
-        }
+        for (int m = 1; m < mg->degree; ++m)
+            if ((rc = cheb_step(mg, lv, x, q == 0 ? bin : lv.b, m, true, skip))) return rc;
         if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
         cheb_resid_kernel<<<g, kBlock, 0, st>>>(lv.r, lv.wl, cp, lv.nu, skip);
         if (lv.kind == 1 && lv.lx == 2)
@@ -946,12 +985,12 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
                                                                                 nx.gs->lid, lv.J, lv.lx, nx.lx,
                                                                                 lv.kind, lv.n, nx.n, lv.nel, skip);
         if ((rc = level_ax(mg, lv, lv.wl, x, skip))) return rc;
-        cheb_post_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
-        for (int m = 1; m < mg->degree; ++m) {
-            if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
-            cheb_step_kernel<<<g, kBlock, 0, st>>>(x, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], cp,
-                                                   lv.nu, skip);
-        }
+        if (mg->degree == 1)
+            cheb_post_kernel<true><<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
+        else
+            cheb_post_kernel<false><<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
+        for (int m = 1; m < mg->degree; ++m)
+            if ((rc = cheb_step(mg, lv, x, b, m, false, skip))) return rc;
         SEM_LAUNCH_CHECK(mg->ctx);
     }
     return SEM_OK;
