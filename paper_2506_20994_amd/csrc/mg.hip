@@ -531,6 +531,80 @@ __global__ void dense_ax_kernel(float* __restrict__ wl, const float* __restrict_
     }
 }
 
+// Galerkin levels: the operator and the smoothing step that follows it in one
+// kernel, eight lanes per unknown, one for each of its copies (its corner of up to
+// eight elements; an unknown with more goes round again).  A lane forms its copy's
+// row product; the lanes' sum, in the copies' order, is A d at the unknown.  Every
+// unknown's d is read by its neighbours, so the new d goes to another vector.
+// These levels are bound by their launches and the chain link, more, M and lid, d: one
+// such kernel measured 4.7 us, as the operator and the vector update each did, on the
+// levels of 16^3 and 32^3 elements.  Flexible PCG, two kernels / one: 32^3 lx 8 45.4 /
+// 44.2 ms, 16^3 lx 8 12.3 / 11.0 ms, 8^3 lx 6 8.4 / 6.6 ms, and 64^3 lx 4, whose lx = 2
+// level has 262144 unknowns, 44.3 / 40.5 ms.
+enum { kDenseResid, kDensePost, kDenseD, kDenseXD, kDenseX, kDenseLastXD, kDenseLastX };
+template <int WHAT>
+__global__ void __launch_bounds__(kBlock)
+dense_step_kernel(float* __restrict__ x, const float* rin, float* r, const float* __restrict__ d,
+                  float* __restrict__ dnew, const float* __restrict__ M, const int32_t* __restrict__ lid,
+                  const float* __restrict__ minv, float c1, float c2, sem::Copies cp, int64_t nu,
+                  const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    const int j = threadIdx.x & 7;
+    MG_LOOP(t, 8 * nu) {
+        const int64_t u = t >> 3;
+        const int2 c = cp.link[u];
+        const int4* q = cp.more + (c.y < -1 ? -2 - c.y : 0);
+        const int32_t* qi = reinterpret_cast<const int32_t*>(q);
+        const float ro = rin[u], dold = d[u], mv = minv[u];
+        const float xo = WHAT == kDenseXD || WHAT == kDenseX || WHAT == kDenseLastXD || WHAT == kDenseLastX ? x[u] : 0.f;
+        const int32_t w = c.y < -1 ? qi[3] : 0;
+        int32_t L = j == 0 ? c.x : -1;
+        if (c.y < -1) {
+            if (j >= 1 && j < 4) L = qi[j - 1];
+            else if (j >= 4 && w > 0) L = qi[j];
+        } else if (j == 1) {
+            L = c.y;
+        }
+        float s = 0.f;
+        for (int k = 2;; k += 2) {
+            float v = 0.f;
+            if (L >= 0) {
+                const float4* row = reinterpret_cast<const float4*>(M + 8 * (int64_t)L);
+                const int4* id = reinterpret_cast<const int4*>(lid + (L & ~7));
+                const float4 m0 = row[0], m1 = row[1];
+                const int4 i0 = id[0], i1 = id[1];
+                v += m0.x * (i0.x >= 0 ? d[i0.x] : 0.f);
+                v += m0.y * (i0.y >= 0 ? d[i0.y] : 0.f);
+                v += m0.z * (i0.z >= 0 ? d[i0.z] : 0.f);
+                v += m0.w * (i0.w >= 0 ? d[i0.w] : 0.f);
+                v += m1.x * (i1.x >= 0 ? d[i1.x] : 0.f);
+                v += m1.y * (i1.y >= 0 ? d[i1.y] : 0.f);
+                v += m1.z * (i1.z >= 0 ? d[i1.z] : 0.f);
+                v += m1.w * (i1.w >= 0 ? d[i1.w] : 0.f);
+            }
+#pragma unroll
+            for (int o = 0; o < 8; ++o) s += __shfl(v, o, 8);
+            if (k > w) break;
+            L = k + (j >> 2) <= w ? qi[4 * k + j] : -1;
+        }
+        if (j) continue;
+        const float rv = ro - s;
+        if (WHAT == kDenseResid) {
+            r[u] = rv;
+            continue;
+        }
+        // for the post-smoothing's first step d is x, and c2 its only factor
+        const float dv = WHAT == kDensePost ? c2 * mv * rv : c1 * dold + c2 * mv * rv;
+        if (WHAT != kDenseLastX && WHAT != kDenseLastXD) {
+            r[u] = rv;
+            dnew[u] = dv;
+        }
+        if (WHAT == kDenseD) x[u] = dold + dv;
+        else if (WHAT == kDenseXD || WHAT == kDenseLastXD) x[u] = xo + dold + dv;
+        else if (WHAT == kDenseX || WHAT == kDenseLastX) x[u] = xo + dv;
+    }
+}
+
 // The coarse basis function bc (0..7, lexicographic over the 2 x 2 x 2 coarse
 // element) interpolated to the lf^3 nodes of every element: J[i][a] (lf x 2).
 __global__ void basis_field_kernel(double* __restrict__ ul, const double* __restrict__ J, int lf, int bc,
@@ -907,22 +981,57 @@ void set_chebyshev(sem_mg_t mg, MgLevel& lv) {
     }
 }
 
-// step m >= 1 of a smoothing; pre-smoothing starts from x = 0 and right-hand side b
-int cheb_step(sem_mg_t mg, MgLevel& lv, float* x, const float* b, int m, bool pre, const int* skip) {
+// a step of a Galerkin level in one kernel: the operator on u, then `what`
+void dense_step(sem_mg_t mg, MgLevel& lv, int what, float* x, const float* rin, const float* u, float* dnew, float c1,
+                float c2, const int* skip) {
+    const sem::Copies cp{lv.gs->link, lv.gs->more};
+    const unsigned g = vgrid(8 * lv.nu);
+    switch (what) {
+#define MG_DENSE(W) case W: dense_step_kernel<W><<<g, kBlock, 0, mg->ctx->stream>>>( \
+        x, rin, lv.r, u, dnew, lv.M, lv.gs->lid, lv.minv, c1, c2, cp, lv.nu, skip); break;
+        MG_DENSE(kDenseResid) MG_DENSE(kDensePost) MG_DENSE(kDenseD) MG_DENSE(kDenseXD) MG_DENSE(kDenseX)
+        MG_DENSE(kDenseLastXD) MG_DENSE(kDenseLastX)
+#undef MG_DENSE
+    }
+}
+
+// steps 1 .. degree-1 of a smoothing from first step d; pre-smoothing starts from
+// x = 0 and right-hand side b, and returns r = b - A x as well
+int cheb_steps(sem_mg_t mg, MgLevel& lv, float* x, const float* b, bool pre, const int* skip) {
     const unsigned g = vgrid(lv.nu);
     hipStream_t st = mg->ctx->stream;
     const sem::Copies cp{lv.gs->link, lv.gs->more};
-    const int rc = level_ax(mg, lv, lv.wl, lv.d, skip);
-    if (rc) return rc;
-    const bool last = !pre && m + 1 == mg->degree;
+    if (lv.M) {
+        float *d = lv.d, *dn = lv.wl;          // the two places of d: the operator's field is free here
+        if (!pre) std::swap(d, dn);            // the first step read x and wrote wl
+        for (int m = 1; m < mg->degree; ++m) {
+            const bool last = !pre && m + 1 == mg->degree;
+            const int what = m == 1 ? (pre ? kDenseD : last ? kDenseLastXD : kDenseXD) : last ? kDenseLastX : kDenseX;
+            dense_step(mg, lv, what, x, m == 1 && pre ? b : lv.r, d, dn, lv.c1[m], lv.c2[m], skip);
+            std::swap(d, dn);
+        }
+        if (pre) dense_step(mg, lv, kDenseResid, x, mg->degree == 1 ? b : lv.r, d, nullptr, 0.f, 0.f, skip);
+        SEM_LAUNCH_CHECK(mg->ctx);
+        return SEM_OK;
+    }
+    int rc;
+    for (int m = 1; m < mg->degree; ++m) {
+        if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
+        const bool last = !pre && m + 1 == mg->degree;
 #define MG_STEP(TO, LAST, RIN) cheb_step_kernel<TO, LAST><<<g, kBlock, 0, st>>>( \
         x, RIN, lv.r, lv.d, lv.wl, lv.minv, lv.c1[m], lv.c2[m], cp, lv.nu, skip)
-    if (m == 1 && pre) MG_STEP(kToD, false, b);
-    else if (m == 1 && last) MG_STEP(kToXD, true, lv.r);
-    else if (m == 1) MG_STEP(kToXD, false, lv.r);
-    else if (last) MG_STEP(kToX, true, lv.r);
-    else MG_STEP(kToX, false, lv.r);
+        if (m == 1 && pre) MG_STEP(kToD, false, b);
+        else if (m == 1 && last) MG_STEP(kToXD, true, lv.r);
+        else if (m == 1) MG_STEP(kToXD, false, lv.r);
+        else if (last) MG_STEP(kToX, true, lv.r);
+        else MG_STEP(kToX, false, lv.r);
 #undef MG_STEP
+    }
+    if (pre) {
+        if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
+        cheb_resid_kernel<<<g, kBlock, 0, st>>>(lv.r, lv.wl, cp, lv.nu, skip);
+    }
+    SEM_LAUNCH_CHECK(mg->ctx);
     return SEM_OK;
 }
 
@@ -949,10 +1058,7 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
         cheb_first_kernel<<<g, kBlock, 0, st>>>(one ? x : nullptr, one ? lv.r : nullptr, lv.d,
                                                 q == 0 ? nullptr : lv.b, q == 0 ? bin : nullptr,
                                                 q == 0 ? nullptr : lv.bl, lv.minv, lv.c0, cp, lv.nu, skip);
-        for (int m = 1; m < mg->degree; ++m)
-            if ((rc = cheb_step(mg, lv, x, q == 0 ? bin : lv.b, m, true, skip))) return rc;
-        if ((rc = level_ax(mg, lv, lv.wl, lv.d, skip))) return rc;
-        cheb_resid_kernel<<<g, kBlock, 0, st>>>(lv.r, lv.wl, cp, lv.nu, skip);
+        if ((rc = cheb_steps(mg, lv, x, q == 0 ? bin : lv.b, true, skip))) return rc;
         if (lv.kind == 1 && lv.lx == 2)
             restrict_h_kernel<<<vgrid(8 * nx.nel), kBlock, 0, st>>>(nx.bl, lv.r, lv.gs->lid, lv.own, lv.n, nx.n,
                                                                     nx.nel, skip);
@@ -984,13 +1090,16 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
             prolong_kernel<<<(unsigned)lv.nel, f3 <= 64 ? 64 : kBlock, 0, st>>>(x, nx.x, lv.gs->lid, lv.own,
                                                                                 nx.gs->lid, lv.J, lv.lx, nx.lx,
                                                                                 lv.kind, lv.n, nx.n, lv.nel, skip);
-        if ((rc = level_ax(mg, lv, lv.wl, x, skip))) return rc;
-        if (mg->degree == 1)
-            cheb_post_kernel<true><<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
-        else
-            cheb_post_kernel<false><<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
-        for (int m = 1; m < mg->degree; ++m)
-            if ((rc = cheb_step(mg, lv, x, b, m, false, skip))) return rc;
+        if (lv.M && mg->degree > 1) {
+            dense_step(mg, lv, kDensePost, x, b, x, lv.wl, 0.f, lv.c0, skip);
+        } else {
+            if ((rc = level_ax(mg, lv, lv.wl, x, skip))) return rc;
+            if (mg->degree == 1)
+                cheb_post_kernel<true><<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
+            else
+                cheb_post_kernel<false><<<g, kBlock, 0, st>>>(x, lv.r, lv.d, b, lv.wl, lv.minv, lv.c0, cp, lv.nu, skip);
+        }
+        if ((rc = cheb_steps(mg, lv, x, b, false, skip))) return rc;
         SEM_LAUNCH_CHECK(mg->ctx);
     }
     return SEM_OK;

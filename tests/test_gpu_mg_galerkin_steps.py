@@ -1,0 +1,79 @@
+"""The Galerkin levels' smoothing steps, operator and vector update in one kernel,
+at the degrees and sizes where they take other paths: degree 1 (no later step),
+2 (the second step is the last) and 4 (steps that are neither first nor last);
+one element and two in a direction, where an unknown's copies lie in one or a few
+elements; Dirichlet nodes, which are no unknowns; and a level of more unknowns
+than one pass of the grid holds.
+
+Bound: as in test_gpu_mg.py, 1e-4 of the largest value against the oracle's
+float64 V-cycle; the large level is compared with its own element-by-element
+symmetry instead (a periodic undeformed box and data that repeat every eight
+elements give a result that does)."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import mg as omg
+from oracle.mesh import global_ids
+from tests.test_gpu_mg import MG_TOL, _plan_order
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2506_20994_amd")
+from paper_2506_20994_amd.box import BoxOperator  # noqa: E402
+
+
+@pytest.mark.parametrize("n,lx,amp,dirichlet,h2,degree", [
+    (4, 4, 0.1, True, None, 1), (4, 2, 0.1, False, 3.0, 1), (8, 2, 0.1, True, None, 2), (8, 3, 0.08, False, None, 4),
+    (4, 5, 0.1, True, 5.0, 4), (2, 4, 0.1, False, 2.0, 3)])
+def test_degrees(sem_ctx, n, lx, amp, dirichlet, h2, degree):
+    op = BoxOperator(sem_ctx, n, lx, amp, dirichlet=dirichlet, keep_coords=False)
+    mg = op.multigrid(h2=h2 or 0.0, degree=degree, lo=0.2, galerkin=True)
+    H = omg.Hierarchy(n, lx, amp, dirichlet=dirichlet, h2=h2, degree=degree, lo=0.2, galerkin=True)
+    H.set_lmax([P.sem_mg_level_info(mg, q)[3] for q in range(P.sem_mg_levels(mg) - 1)])
+    B = H.boxes[0]
+    plan_of = _plan_order(B.ids, B.nu)
+    rG = synth.unique_normal(B.nu, 71)
+    rp = np.empty(B.nu)
+    rp[plan_of] = rG
+    r = torch.from_numpy(rp).float().cuda()
+    z = torch.full_like(r, float("nan"))
+    for _ in range(2):                         # a second application finds nothing of the first
+        P.sem_mg_apply(mg, z, r)
+    torch.cuda.synchronize()
+    zref = H.vcycle(rG)
+    assert np.max(np.abs(z.double().cpu().numpy()[plan_of] - zref)) <= MG_TOL * np.max(np.abs(zref))
+    mg.close()
+    op.gs.close()
+
+
+def test_more_unknowns_than_one_pass(sem_ctx):
+    """48^3 elements of lx = 3: 110592 unknowns on the lx = 2 level, whose kernels take
+    65536 at a time"""
+    n, lx, every = 48, 3, 8
+    op = BoxOperator(sem_ctx, n, lx, 0.0, keep_coords=False)
+    mg = op.multigrid(h2=1.0, degree=2, lo=0.2, galerkin=True, n_coarse=6)
+    ids = global_ids(n, lx)
+    nu = P.sem_mg_level_info(mg, 0)[2]
+    plan_of = _plan_order(ids, nu)
+    # data by grid node, repeating every `every` elements
+    e, p = np.arange(n ** 3), every * (lx - 1)
+    ex, ey, ez = e % n, (e // n) % n, e // n ** 2
+    like = ex % every + n * (ey % every + n * (ez % every))
+    k, j, i = np.meshgrid(*[np.arange(lx)] * 3, indexing="ij")
+    at = [(q[:, None, None, None] * (lx - 1) + o) % p for q, o in ((ez, k), (ey, j), (ex, i))]
+    rG = np.empty(nu)
+    rG[ids] = synth.unique_normal(p ** 3, 72).reshape(p, p, p)[tuple(at)]
+    assert np.array_equal(rG[ids], rG[ids][like])
+    rp = np.empty(nu)
+    rp[plan_of] = rG
+    r = torch.from_numpy(rp).float().cuda()
+    z = torch.empty_like(r)
+    P.sem_mg_apply(mg, z, r)
+    torch.cuda.synchronize()
+    zl = z.double().cpu().numpy()[plan_of][ids]
+    assert np.isfinite(zl).all() and np.max(np.abs(zl)) > 0
+    assert np.max(np.abs(zl - zl[like])) <= MG_TOL * np.max(np.abs(zl))
+    mg.close()
+    op.gs.close()
