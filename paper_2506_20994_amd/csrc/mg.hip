@@ -427,34 +427,38 @@ __global__ void prolong_h_kernel(float* __restrict__ xf, const float* __restrict
     }
 }
 
-// P^T of an h-transfer (lx = 2 boxes): one thread per coarse element node c,
-// summing over the 8 children and their 8 nodes with the parent's trilinear
-// basis at the child's vertices
+// P^T of an h-transfer (lx = 2 boxes): eight lanes per coarse element node c, one for
+// each of the 8 children, summing over its 8 nodes with the parent's trilinear basis
+// at the child's vertices.  All loads of a kind are in flight together: one thread
+// for the 64 nodes, branching at each, took 13.3 us for 16^3 coarse elements, this takes 4.7
 __global__ void restrict_h_kernel(float* __restrict__ blc, const float* __restrict__ rf, const int32_t* __restrict__ lidf,
                                   const uint8_t* __restrict__ ownf, int nf, int nc, int64_t nelc,
                                   const int* __restrict__ skip) {
     if (skip && *skip) return;
-    MG_LOOP(t, nelc * 8) {
-        const int64_t E = t >> 3;
-        const int c = (int)(t & 7), ax = c & 1, ay = (c >> 1) & 1, az = c >> 2;
+    MG_LOOP(t, nelc * 64) {
+        const int64_t E = t >> 6;
+        const int c = (int)(t >> 3) & 7, ax = c & 1, ay = (c >> 1) & 1, az = c >> 2;
+        const int ch = (int)t & 7, px = ch & 1, py = (ch >> 1) & 1, pz = ch >> 2;
         const int64_t ecx = E % nc, ecy = (E / nc) % nc, ecz = E / ((int64_t)nc * nc);
+        const int64_t ef = (2 * ecx + px) + nf * ((2 * ecy + py) + (int64_t)nf * (2 * ecz + pz));
+        const uint64_t own = *reinterpret_cast<const uint64_t*>(ownf + 8 * ef);
+        const int4* q = reinterpret_cast<const int4*>(lidf + 8 * ef);
+        const int4 q0 = q[0], q1 = q[1];
+        const int32_t id[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
         float acc = 0.f;
-        for (int ch = 0; ch < 8; ++ch) {
-            const int px = ch & 1, py = (ch >> 1) & 1, pz = ch >> 2;
-            const int64_t ef = (2 * ecx + px) + nf * ((2 * ecy + py) + (int64_t)nf * (2 * ecz + pz));
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int ix = i & 1, iy = (i >> 1) & 1, iz = i >> 2;
-                // phi_a(eta), eta = -1 + p + i in {-1, 0, 1}: 1, 1/2 or 0
-                const float wx = (float)(ax ? px + ix : 2 - px - ix) * 0.5f;
-                const float wy = (float)(ay ? py + iy : 2 - py - iy) * 0.5f;
-                const float wz = (float)(az ? pz + iz : 2 - pz - iz) * 0.5f;
-                const float wgt = wx * wy * wz;
-                const int64_t L = ef * 8 + i;
-                if (wgt != 0.f && ownf[L]) acc += wgt * rf[lidf[L]];
-            }
+        for (int i = 0; i < 8; ++i) {
+            const int ix = i & 1, iy = (i >> 1) & 1, iz = i >> 2;
+            // phi_a(eta), eta = -1 + p + i in {-1, 0, 1}: 1, 1/2 or 0
+            const float wx = (float)(ax ? px + ix : 2 - px - ix) * 0.5f;
+            const float wy = (float)(ay ? py + iy : 2 - py - iy) * 0.5f;
+            const float wz = (float)(az ? pz + iz : 2 - pz - iz) * 0.5f;
+            const float wgt = wx * wy * wz;
+            if (wgt != 0.f && (own >> (8 * i) & 0xff)) acc += wgt * rf[id[i]];
         }
-        blc[t] = acc;
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) acc += __shfl_xor(acc, o, 8);
+        if (ch == 0) blc[t >> 3] = acc;
     }
 }
 
@@ -483,35 +487,39 @@ bool prolong_p_wave(hipStream_t st, int lf, int lc, float* xf, const float* xc, 
 
 // Coarsest level: x = Ainv b with b assembled from the restricted local field
 // (bl) or given (bin).  Every workgroup assembles all of b into LDS, then each
-// of its waves forms kCoarseRows rows of Ainv b, the lanes striding along the
-// row (coalesced) and a wave sum closing it.
-constexpr int kCoarseRows = 4;
+// of its waves forms one row of Ainv b, the lanes striding along the row
+// (coalesced) and a wave sum closing it.  The kernel is the latency of its loads:
+// the row's first kCoarseAhead are under way while b is assembled, and one row a
+// wave leaves no second row to wait for (512 unknowns: four rows a wave, each read
+// after the assembly, 20.2 us; this 5.6 us)
+constexpr int kCoarseAhead = 8;
 __global__ void __launch_bounds__(kBlock)
 coarse_kernel(float* __restrict__ x, const float* __restrict__ bin, const float* __restrict__ bl,
               const float* __restrict__ ainv, sem::Copies cp,
               int nu, const int* __restrict__ skip) {
     if (skip && *skip) return;
     __shared__ float sb[kCoarseMax];
+    const int lane = threadIdx.x & 63;
+    const int i = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const float* row = ainv + (int64_t)min(i, nu - 1) * nu;
+    float ahead[kCoarseAhead];
+#pragma unroll
+    for (int k = 0; k < kCoarseAhead; ++k) ahead[k] = row[min(lane + 64 * k, nu - 1)];
     for (int u = threadIdx.x; u < nu; u += blockDim.x) sb[u] = bl ? assemble_local(bl, cp, u) : bin[u];
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int row0 = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * kCoarseRows;
-    for (int q = 0; q < kCoarseRows; ++q) {
-        const int i = row0 + q;
-        if (i >= nu) break;                       // uniform across the wave
-        const float* row = ainv + (int64_t)i * nu;
-        float s = 0.f;
-        for (int j = lane; j < nu; j += 64) s += row[j] * sb[j];
+    if (i >= nu) return;                          // uniform across the wave
+    float s = 0.f;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (lane == 0) x[i] = s;
-    }
+    for (int k = 0; k < kCoarseAhead; ++k)
+        if (lane + 64 * k < nu) s += ahead[k] * sb[lane + 64 * k];
+#pragma unroll 4
+    for (int j = lane + 64 * kCoarseAhead; j < nu; j += 64) s += row[j] * sb[j];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) x[i] = s;
 }
 
-unsigned coarse_grid(int64_t nu) {
-    const int64_t rows_per_block = (kBlock / 64) * kCoarseRows;
-    return (unsigned)std::max<int64_t>(1, (nu + rows_per_block - 1) / rows_per_block);
-}
+unsigned coarse_grid(int64_t nu) { return (unsigned)std::max<int64_t>(1, (nu + kBlock / 64 - 1) / (kBlock / 64)); }
 
 // Galerkin level operator: w_l = M_e u_e, one thread per local node of the
 // lx = 2 elements (M row-major per element, 8 x 8; Dirichlet nodes read 0)
@@ -1060,7 +1068,7 @@ int vcycle(sem_mg_t mg, float* xout, const float* bin, const int* skip) {
                                                 q == 0 ? nullptr : lv.bl, lv.minv, lv.c0, cp, lv.nu, skip);
         if ((rc = cheb_steps(mg, lv, x, q == 0 ? bin : lv.b, true, skip))) return rc;
         if (lv.kind == 1 && lv.lx == 2)
-            restrict_h_kernel<<<vgrid(8 * nx.nel), kBlock, 0, st>>>(nx.bl, lv.r, lv.gs->lid, lv.own, lv.n, nx.n,
+            restrict_h_kernel<<<vgrid(64 * nx.nel), kBlock, 0, st>>>(nx.bl, lv.r, lv.gs->lid, lv.own, lv.n, nx.n,
                                                                     nx.nel, skip);
         else if (lv.kind != 0 || !restrict_p_wave(st, lv.lx, nx.lx, nx.bl, lv.r, lv.gs->lid, lv.own, lv.J, nx.nel,
                                                   skip))

@@ -1,7 +1,7 @@
-"""The Galerkin levels' smoothing steps, operator and vector update in one kernel,
-at the degrees and sizes where they take other paths: degree 1 (no later step),
-2 (the second step is the last) and 4 (steps that are neither first nor last);
-one element and two in a direction, where an unknown's copies lie in one or a few
+"""The coarse levels of a V-cycle: the Galerkin levels' smoothing steps, operator and
+vector update in one kernel, and the dense coarsest solve, at the degrees and sizes
+where they take other paths: degree 1 (no later step), 2 (the second step is the
+last) and 4 (steps that are neither first nor last); one element and two in a direction, where an unknown's copies lie in one or a few
 elements; Dirichlet nodes, which are no unknowns; and a level of more unknowns
 than one pass of the grid holds.
 
@@ -41,6 +41,31 @@ def test_degrees(sem_ctx, n, lx, amp, dirichlet, h2, degree):
     z = torch.full_like(r, float("nan"))
     for _ in range(2):                         # a second application finds nothing of the first
         P.sem_mg_apply(mg, z, r)
+    torch.cuda.synchronize()
+    zref = H.vcycle(rG)
+    assert np.max(np.abs(z.double().cpu().numpy()[plan_of] - zref)) <= MG_TOL * np.max(np.abs(zref))
+    mg.close()
+    op.gs.close()
+
+
+@pytest.mark.parametrize("n,lx,dirichlet", [(5, 2, False), (9, 2, True), (9, 3, False), (5, 3, True), (12, 2, False)])
+def test_coarsest_level(sem_ctx, n, lx, dirichlet):
+    """64 to 729 unknowns on the coarsest level, as the only one (its right-hand side
+    the caller's vector) and below another; h-transfers from 12^3 to 6^3"""
+    n_coarse = 6 if n == 12 else 0
+    op = BoxOperator(sem_ctx, n, lx, 0.05, dirichlet=dirichlet, keep_coords=False)
+    mg = op.multigrid(h2=2.0, degree=2, lo=0.2, galerkin=True, n_coarse=n_coarse)
+    H = omg.Hierarchy(n, lx, 0.05, dirichlet=dirichlet, h2=2.0, degree=2, lo=0.2, galerkin=True,
+                      n_coarse=n_coarse or 2)
+    H.set_lmax([P.sem_mg_level_info(mg, q)[3] for q in range(P.sem_mg_levels(mg) - 1)])
+    B = H.boxes[0]
+    plan_of = _plan_order(B.ids, B.nu)
+    rG = synth.unique_normal(B.nu, 73)
+    rp = np.empty(B.nu)
+    rp[plan_of] = rG
+    r = torch.from_numpy(rp).float().cuda()
+    z = torch.full_like(r, float("nan"))
+    P.sem_mg_apply(mg, z, r)
     torch.cuda.synchronize()
     zref = H.vcycle(rG)
     assert np.max(np.abs(z.double().cpu().numpy()[plan_of] - zref)) <= MG_TOL * np.max(np.abs(zref))
