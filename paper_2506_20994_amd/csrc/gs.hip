@@ -20,6 +20,12 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Bound by the lines of the local layout (an element's faces touch every line of it:
+// 325 MB at 32^3, lx 8, for 211 MB of values and indices) and the chain link, more,
+// values: with both of a node's entries of more read at once and kept for the stores
+// 85.5 us there and 12.6 us at 19^3, lx 7 (one entry at a time, read again for the
+// stores: 88.5 and 13.7; three index lists per node: 87.0 and 12.6; 256 and 1024
+// threads a workgroup: 86.4 and 87.8).
 // threads [0, n_shared) sum the shared ids; threads [n_shared, n_shared +
 // n_masked) zero the Dirichlet nodes listed in midx
 template <typename T>
@@ -31,18 +37,21 @@ __global__ void gs_kernel(T* __restrict__ u, sem::Copies cp, int64_t n_shared, c
         if (g < n_shared + n_masked) u[midx[g - n_shared]] = T(0);
         return;
     }
-    const int2 c = cp.link[g];
-    const int4 i = c.y < -1 ? cp.more[-2 - c.y] : int4{-1, -1, -1, 0};
-    const T s = sem::sum_copies_flat<T>(cp, g, [=](int32_t L) { return u[L]; });
-    u[c.x] = s;
-    if (c.y >= 0) u[c.y] = s;
-    if (i.x >= 0) {
-        u[i.x] = s;
-        u[i.y] = s;
+    const sem::NodeCopies n = sem::node_copies(cp, g);
+    const T s = sem::sum_copies_flat<T>(cp, n, [=](int32_t L) { return u[L]; });
+    u[n.c.x] = s;
+    if (n.c.y >= 0) u[n.c.y] = s;
+    if (n.i.x >= 0) {
+        u[n.i.x] = s;
+        u[n.i.y] = s;
     }
-    if (i.z >= 0) u[i.z] = s;
-    for (int k = 1; k <= i.w; ++k) {
-        const int4 j = cp.more[-2 - c.y + k];
+    if (n.i.z >= 0) u[n.i.z] = s;
+    if (n.j.x >= 0) u[n.j.x] = s;
+    if (n.j.y >= 0) u[n.j.y] = s;
+    if (n.j.z >= 0) u[n.j.z] = s;
+    if (n.j.w >= 0) u[n.j.w] = s;
+    for (int k = 2; k <= n.i.w; ++k) {
+        const int4 j = cp.more[-2 - n.c.y + k];
         u[j.x] = s;
         if (j.y >= 0) u[j.y] = s;
         if (j.z >= 0) u[j.z] = s;
@@ -313,7 +322,7 @@ int gs_launch(sem_gs_t gs, void* u, sem_dtype_t dtype, const int* skip) {
     const int64_t nt = gs->n_shared + gs->n_masked;
     if (nt == 0) return SEM_OK;
     if (!u) return fail(ctx, SEM_EINVAL, "sem_gs: null field");
-    constexpr int kGsBlock = 512;           // measured: 256 and 1024 threads are slower
+    constexpr int kGsBlock = 512;
     const unsigned grid = (unsigned)((nt + 8 * kGsBlock - 1) / (8 * kGsBlock) * 8);   // a multiple of 8
     const int32_t* midx = gs->uidx + (gs->n_local - gs->n_masked);
     const Copies cp{gs->slink, gs->more};
