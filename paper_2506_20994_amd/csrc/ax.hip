@@ -400,7 +400,7 @@ constexpr bool kFlat = std::is_same<TS, double>::value ? (LX == 5 || LX == 6 || 
 // Where it is that at every size; the others of kFlat take it for large arrays
 // (flat_pays).
 template <int LX, typename TS>
-constexpr bool kFlatAlways = kFlat<LX, TS> && (LX > 7 || (std::is_same<TS, uint16_t>::value && LX > 5));
+constexpr bool kFlatAlways = kFlat<LX, TS> && LX > 7;
 
 // Where the solver form takes it: not at lx = 4, 5 and float32 lx = 7, where the gather
 // hides what the accesses gain.  One conjugate-gradient iteration, column / whole
@@ -410,7 +410,7 @@ constexpr bool kFlatAlways = kFlat<LX, TS> && (LX > 7 || (std::is_same<TS, uint1
 // and 65.8 / 65.1 at 26^3, lx 7 36.9 / 39.1 at 16^3 and 97.3 / 96.2 at 26^3; bfloat16
 // lx 5 42.1 / 46.8 and lx 6 61.1 / 58.5 at 26^3.
 template <int LX, typename TS>
-constexpr bool kFlatSolver = kFlatAlways<LX, TS> || (kFlat<LX, TS> && LX == 6);
+constexpr bool kFlatSolver = kFlat<LX, TS> && (LX > 7 || LX == 6 || (LX == 7 && std::is_same<TS, uint16_t>::value));
 
 // EPB elements per workgroup of NW waves, V nodes per access (V divides the
 // workgroup's nodes): two or three accesses per thread and array, and workgroups
@@ -891,20 +891,25 @@ void launch_3d(sem_ctx_t ctx, void* w, const void* u, const void* const* D, cons
     }
 }
 
-// Below about a hundred megabytes of arrays the short orders stay on the column
-// mapping, whose workgroups are smaller: a launch that is over in a few waves of
-// workgroups is paced by the chain load, LDS, product, LDS, store of one of them.
-// Column / whole elements, us: float64 lx 5 at 8000 elements (64 MB) 16.6 / 18.5, at
-// 16000 34.8 / 32.7; lx 6 at 5000 (69 MB) 15.0 / 18.6, at 8000 (111 MB) 29.9 / 27.2;
-// float32 lx 4 at 32000 (66 MB) 14.5 / 17.3, at 50000 25.0 / 25.0; lx 5 at 16000
-// (64 MB) 16.1 / 18.9, at 32000 36.0 / 32.0; lx 6 at 8000 (55 MB) 14.3 / 16.0, at 16000
-// 29.7 / 26.9; lx 7 at 8000 (88 MB) 22.9 / 25.3, at 16000 44.6 / 41.5; bfloat16 lx 4 at
-// 50000 (51 MB) 17.8 / 19.9, lx 5 at 32000 (64 MB) 22.5 / 23.8, at 50000 (100 MB)
-// 41.1 / 33.5.  From bfloat16 lx 6 (16000: 20.6 / 19.7; 8000: 13.1 / 13.7, launch-bound)
-// and lx 7 on, and for the long orders, whole elements are not slower at any size.
-template <int LX, typename TS>
+// The short orders take whole elements only for arrays well beyond the 256 MB
+// last-level cache.  Within it a call on arrays just used finds them there, and the
+// column mapping, whose smaller workgroups then set the pace and whose accesses go
+// through the caches at these orders, is the faster.  Column / whole elements, us, on
+// the same arrays again and again: float64 lx 5 at 16000 elements (144 MB) 25.5 / 31.7,
+// at 32768 (295 MB) 50.9 / 57.4, at 65536 114.6 / 106.1; lx 6 at 16000 (249 MB) 40.3 /
+// 46.0, at 32768 (510 MB) 98.4 / 86.9; float32 lx 4 at 65536 (151 MB) 24.1 / 28.7; lx 5
+// at 32768 (147 MB) 26.6 / 31.2, at 65536 (295 MB) 58.6 / 54.9; lx 6 at 32768 (255 MB)
+// 41.3 / 46.0, at 65536 105.0 / 85.5; lx 7 at 16000 (198 MB) 33.4 / 40.3, at 32768
+// (405 MB) 81.3 / 74.9; bfloat16 lx 5 at 65536 (147 MB) 37.2 / 40.5.  On arrays from
+// memory whole elements lead from about 110 MB on (float64 lx 6 at 8000, 124 MB: 29.9 /
+// 27.2), but by less.  bfloat16 lx 6 and 7 turn at about 40 MB (lx 6: 8000 elements,
+// 31 MB, 11.4 / 12.7, 13000, 51 MB, 17.6 / 17.0, 32768 34.2 / 33.2, from memory 32000
+// 44.2 / 33.0; lx 7: 3000, 19 MB, 10.4 / 11.5, 8000, 49 MB, 20.3 / 17.8).  The long
+// orders lead at every size that is not bound by the launch.
+template <int LX, typename TS, bool HB>
 bool flat_pays(int64_t nel) {
-    return kFlatAlways<LX, TS> || nel * (LX * LX * LX) * 8 * (int64_t)sizeof(TS) >= (96 << 20);
+    constexpr int64_t kLeast = (int64_t)(std::is_same<TS, uint16_t>::value && LX >= 6 ? 40 : 320) << 20;
+    return kFlatAlways<LX, TS> || nel * (LX * LX * LX) * (9 + HB) * (int64_t)sizeof(TS) >= kLeast;
 }
 
 // whole elements also need alignment: accesses are V values wide, so every array it
@@ -995,7 +1000,7 @@ int launch_form(sem_ctx_t ctx, void* w, const void* u, const void* const* D, con
     }
     if constexpr (kFlat<LX, TS> && std::is_same<TU, TS>::value) {
         if (!lid && (variant == SEM_AX_DEFAULT || variant == SEM_AX_COLUMN) && nel <= 0x7fffffff &&
-            flat_pays<LX, TS>(nel) && flat_aligned<LX, TS, TW>(w, u, h1, G, hb)) {
+            flat_pays<LX, TS, HB>(nel) && flat_aligned<LX, TS, TW>(w, u, h1, G, hb)) {
             launch_flat<LX, TU, TS, TC, TW, false, false, HB>(ctx, w, u, D, h1, G, nel, skip, nullptr, nullptr, hb);
             SEM_LAUNCH_CHECK(ctx);
             return SEM_OK;

@@ -84,13 +84,14 @@ def test_arrays_off_the_access_width(lx, kind):
 
 
 @pytest.mark.parametrize("kind,lx", [("f64", 5), ("f64", 6), ("f32", 4), ("f32", 5), ("f32", 6), ("f32", 7),
-                                     ("bf16", 4), ("bf16", 5)])
+                                     ("bf16", 4), ("bf16", 5), ("bf16", 6), ("bf16", 7)])
 def test_orders_that_take_it_for_large_arrays(lx, kind):
-    """either side of 96 MB of arrays, and there off the access width: 61 elements
+    """either side of 320 MB of arrays (bfloat16 lx = 6, 7: 40 MB), and there off the access width: 61 elements
     repeated, every copy against the oracle's 61"""
     dt, out, q, tol = TYPES[kind]
     size = {"f64": 8, "f32": 4, "bf16": 2}[kind]
-    edge = -(-(96 << 20) // (lx ** 3 * 8 * size))        # the first element count of 96 MB
+    least = (40 if kind == "bf16" and lx >= 6 else 320) << 20
+    edge = -(-least // (lx ** 3 * 10 * size))  # the first element count of that size
     p = 61
     G, h1 = synth.random_spd_factors(p, lx, 910 + lx)
     u, hb = synth.local_normal(p, lx, 911 + lx), np.abs(synth.local_normal(p, lx, 912 + lx))
