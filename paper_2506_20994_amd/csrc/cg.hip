@@ -46,7 +46,7 @@ struct Scal {
     int pause;
     // Jacobi-PCG: r.z and the iteration count at the start of iteration seq in slot
     // seq % 2 (its last kernel writes the other slot while its workgroups still
-    // read this one), and the iteration that set `done` (kNotDone while none has)
+    // read this one), and the last iteration that took its step (kNotDone in the loop)
     double rzs[2];
     int its[2];
     int done_at;
@@ -251,9 +251,8 @@ pcg_update_kernel(T* __restrict__ r, const T* __restrict__ wl, const T* __restri
         S->pAp = pAp;
         if (ok) {
             S->alpha = alpha;
-        } else {
+        } else {                       // S->done, which the other workgroups still test, is left to pcg_p_kernel
             S->breakdown = 1;
-            S->done = 1;
             S->done_at = seq - 1;      // no step is taken
         }
     }
@@ -281,7 +280,10 @@ template <typename T, int BS, bool NT>
 __global__ void __launch_bounds__(BS)
 pcg_p_kernel(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, const T* __restrict__ minv, int64_t n,
              Scal* S, int seq, const double* __restrict__ part, int npart) {
-    if (S->done_at < seq) return;      // done before this iteration (this kernel sets done_at = seq)
+    if (S->done_at < seq) {            // done before this kernel, which itself sets done_at = seq
+        if (blockIdx.x == 0 && threadIdx.x == 0) S->done = 1;      // a breakdown in the update
+        return;
+    }
     __shared__ double s_red[2 * (BS / 64)];
     const int64_t step = (int64_t)gridDim.x * BS;
     int64_t u = blockIdx.x * (int64_t)BS + threadIdx.x;
