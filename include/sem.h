@@ -280,7 +280,8 @@ int sem_remove_mean_static(sem_gs_t gs, double* x);
  * be NULL (h1 = 1, the Poisson case).  With h2b non-NULL the operator is the
  * Helmholtz form of sem_ax_helmholtz, A_e + diag(h2b) on every element
  * (h2b = h2 * bm per local node, h2 > 0: the velocity-type solves), whose
- * assembled matrix is positive definite. */
+ * assembled matrix is positive definite.  No array needs more than the
+ * alignment of a float64 (a view into a buffer will do). */
 typedef struct {
     const double* dx; const double* dy; const double* dz;
     const double* dxt; const double* dyt; const double* dzt;

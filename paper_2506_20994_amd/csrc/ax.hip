@@ -489,6 +489,16 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
         const vec_s* q = reinterpret_cast<const vec_s*>(p + b0 + min(o, N - V));
         return __builtin_nontemporal_load(q);
     };
+    // the coefficients h1 and h2 B, which the float64 solver form reads from the
+    // caller's arrays: those promise the alignment of one value only (the type says so;
+    // the load is the same instruction)
+    typedef TS vec_caller __attribute__((ext_vector_type(V), aligned(sizeof(TS))));
+    auto load_coef = [&](const TS* __restrict__ p, int o) -> vec_s {
+        if constexpr (GATHER && std::is_same<TS, double>::value)
+            return __builtin_nontemporal_load(reinterpret_cast<const vec_caller*>(p + b0 + min(o, N - V)));
+        else
+            return load_whole(p, o);
+    };
     auto load_part = [&](const TS* __restrict__ p, int o) {
         vec_s v = 0;
 #pragma unroll
@@ -507,13 +517,13 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
     };
     vec_c uv[NQ];
     vec_s us[NQ], f11[NQ], f22[NQ], f33[NQ], f12[NQ], f13[NQ], f23[NQ], fh[NQ];
-    auto load_all = [&](auto load) {
+    auto load_all = [&](auto load, auto load_h1) {
         if constexpr (!GATHER)
 #pragma unroll
             for (int q = 0; q < NQ; ++q) us[q] = load(u, at_node(q));
         if (h1)
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) fh[q] = load(h1, at_node(q));
+            for (int q = 0; q < NQ; ++q) fh[q] = load_h1(h1, at_node(q));
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const int o = at_node(q);
@@ -535,8 +545,8 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
             }
         }
     }
-    if (full) load_all(load_whole);
-    else load_all(load_part);
+    if (full) load_all(load_whole, load_coef);
+    else load_all(load_part, load_part);
     if constexpr (GATHER) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
@@ -640,7 +650,7 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
         vec_c v = *reinterpret_cast<const vec_c*>(s_t + o) + *reinterpret_cast<const vec_c*>(s_r + o) +
                   *reinterpret_cast<const vec_c*>(s_s + o);
         if constexpr (HB) {                    // Helmholtz: + h2 B u
-            const vec_c m = to_c(full ? load_whole(hb, o) : load_part(hb, o)) * uv[q];
+            const vec_c m = to_c(full ? load_coef(hb, o) : load_part(hb, o)) * uv[q];
             if constexpr (FUSE)
 #pragma unroll
                 for (int i = 0; i < V; ++i) pw += (double)m[i] * (double)uv[q][i];
@@ -914,7 +924,8 @@ bool flat_pays(int64_t nel) {
 
 // whole elements also need alignment: accesses are V values wide, so every array it
 // streams has to lie on that (any array of torch or hipMalloc does; a view into one
-// may not, and takes the column mapping)
+// may not, and takes the column mapping).  The solver form has no such rule: its arrays
+// are the library's own but for float64 h1 and h2 B (load_coef).
 template <int LX, typename TS, typename TW>
 bool flat_aligned(const void* w, const void* u, const void* h1, const void* const* G, const void* hb) {
     constexpr int V = ShapeF<LX, std::is_same<TS, double>::value>::V;
