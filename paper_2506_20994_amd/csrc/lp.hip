@@ -1635,7 +1635,15 @@ extern "C" int sem_lp_forward(sem_lp_t lp, const uint16_t* X, int64_t rows, floa
     if (rc) return rc;
     if (!X || !Y || rows < 0 || rows > lp->max_rows) return sem::fail(ctx, SEM_EINVAL, "sem_lp_forward: bad argument");
     if (rows == 0) return SEM_OK;
-    return forward(lp, X, rows, Y);
+    // outputs that overlap the features go through the network's own buffer: a workgroup
+    // writes its rows while others still read theirs
+    const size_t ny = 4 * (size_t)rows * lp->no;
+    const char *x = reinterpret_cast<const char*>(X), *y = reinterpret_cast<const char*>(Y);
+    if (x >= y + ny || y >= x + 2 * (size_t)rows * lp->nip) return forward(lp, X, rows, Y);
+    rc = forward(lp, X, rows, lp->Y3);
+    if (rc) return rc;
+    SEM_HIP(ctx, hipMemcpyAsync(Y, lp->Y3, ny, hipMemcpyDeviceToDevice, ctx->stream));
+    return SEM_OK;
 }
 
 // gradients of the batch loss into the gradient slots (and the loss into
