@@ -1006,10 +1006,11 @@ struct sem_lp_s {
     float *W[3] = {}, *b[3] = {}, *mW[3] = {}, *mb[3] = {}, *vW[3] = {}, *vb[3] = {};
     float *gW[3] = {}, *gb[3] = {};
     int64_t step = 0;
-    // packed bf16 copies: W1 (256 x nip), W2 (256 x 256), W3 (no x 256), W2^T, W3^T
+    // packed bf16 copies: W1 (256 x nip), W2 (256 x 256), W3 (no x 256), W2^T, W3^T.
+    // Whoever writes the weights (sem_lp_set, sem_lp_adam) writes these as well, so that
+    // a captured call finds the weights of its replay, not those of its capture
     u16 *W1b = nullptr, *W2b = nullptr, *W3b = nullptr, *W2t = nullptr, *W3t = nullptr;
     double mu = -1.0;         // training metric (< 0: mean squared error)
-    bool dirty = true;        // bf16 copies of the weights out of date
     bool fold_dirty = true;   // folded matrix of the linear form out of date
     float* colpart = nullptr; // column-sum partials (bias gradients)
     // activations / work for up to max_rows rows
@@ -1117,15 +1118,13 @@ int wave_products(sem_lp_t lp, const WaveGemm& g0, const WaveGemm& g1 = WaveGemm
     return SEM_OK;
 }
 
-int refresh_bf16(sem_lp_t lp) {
-    const int kHid = lp->nh;     // this network's hidden width
-    if (!lp->dirty) return SEM_OK;
-    hipStream_t st = lp->ctx->stream;
-    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W1b, ksteps(lp->nip), nullptr, lp->W[0], kHid, lp->ni);
-    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W2b, ksteps(kHid), lp->W2t, lp->W[1], kHid, kHid);
-    weights_to_bf16<<<256, kBlock, 0, st>>>(lp->W3b, ksteps(kHid), lp->W3t, lp->W[2], lp->no, kHid);
+// the bf16 copies of layer l's weights
+int pack_weights(sem_lp_t lp, int l) {
+    u16* out[3] = {lp->W1b, lp->W2b, lp->W3b};
+    u16* outT[3] = {nullptr, lp->W2t, lp->W3t};
+    weights_to_bf16<<<256, kBlock, 0, lp->ctx->stream>>>(out[l], ksteps(l == 0 ? lp->nip : lp->nh), outT[l], lp->W[l],
+                                                         param_rows(lp, l), param_cols(lp, l));
     SEM_LAUNCH_CHECK(lp->ctx);
-    lp->dirty = false;
     return SEM_OK;
 }
 
@@ -1133,8 +1132,7 @@ int refresh_bf16(sem_lp_t lp) {
 // needed by inference only, so training steps do not recompute it
 int refresh_fold(sem_lp_t lp) {
     const int kHid = lp->nh;     // this network's hidden width
-    int rc = refresh_bf16(lp);
-    if (rc || !lp->fold_dirty || !lp->linear || !lp->Wfb) return rc;
+    if (!lp->fold_dirty || !lp->linear || !lp->Wfb) return SEM_OK;
     hipStream_t st = lp->ctx->stream;
     const int no = lp->no;
     matmul_f32<<<dim3((kHid + 255) / 256, no), 256, 0, st>>>(lp->T32, lp->W[2], lp->W[1], no, kHid,
@@ -1156,8 +1154,6 @@ constexpr size_t kLdsMax = 160 * 1024;      // per workgroup on gfx950
 
 // forward of M rows of X (on 16 bytes) into Y (float32)
 int forward(sem_lp_t lp, const u16* X, int64_t M, float* Y) {
-    int rc = refresh_bf16(lp);
-    if (rc) return rc;
     if (M > 0x7fffffff) return sem::fail(lp->ctx, SEM_EINVAL, "sem_lp: too many rows");
     hipStream_t st = lp->ctx->stream;
 #define LP_MLP(MT) mlp_kernel<MT><<<(unsigned)((M + 16 * MT - 1) / (16 * MT)), 64 * kMlpWaves, mlp_lds(lp, MT), st>>>( \
@@ -1284,7 +1280,12 @@ extern "C" int sem_lp_set(sem_lp_t lp, int which, const float* host, int64_t cou
     } else {
         SEM_HIP(lp->ctx, hipMemcpy(*slot, host, 4 * (size_t)n, hipMemcpyHostToDevice));
     }
-    if (which < 6) lp->dirty = lp->fold_dirty = true;
+    if (which < 6) lp->fold_dirty = true;
+    if (which < 6 && which % 2 == 0) {
+        rc = pack_weights(lp, which / 2);
+        if (rc) return rc;
+        SEM_HIP(lp->ctx, hipStreamSynchronize(lp->ctx->stream));
+    }
     return SEM_OK;
 }
 
@@ -1399,7 +1400,7 @@ extern "C" int sem_lp_set_linear(sem_lp_t lp, int on) {
         if (rc) return rc;
         lp->Wfb = (u16*)p;
     }
-    lp->dirty = lp->fold_dirty = true;
+    lp->fold_dirty = true;
     return SEM_OK;
 }
 
@@ -1656,8 +1657,7 @@ static int lp_backward(sem_lp_t lp, const uint16_t* X, const float* T, const int
     const int kHid = lp->nh;     // this network's hidden width
     sem_ctx_t ctx = lp->ctx;
     hipStream_t st = ctx->stream;
-    int rc = refresh_bf16(lp);
-    if (rc) return rc;
+    int rc;
     const int kOut = lp->no, kInPad = lp->nip;     // this network's sizes
     const int64_t n3 = (int64_t)B * kOut;
     const bool lin = lp->linear;
@@ -1834,7 +1834,6 @@ extern "C" int sem_lp_adam(sem_lp_t lp, double lr, double beta1, double beta2, d
                                                              (float)beta2, (float)(1.0 - beta2), (float)eps,
                                                              (float)c1, (float)c2);
     SEM_LAUNCH_CHECK(ctx);
-    lp->dirty = false;                          // every weight's bf16 copy has just been written
     lp->fold_dirty = true;
     return SEM_OK;
 }
@@ -2066,8 +2065,6 @@ extern "C" int sem_lp_set_block(sem_lp_t lp, const float* W, int64_t count) {
     if (!W || count != (int64_t)lp->no * lp->no)
         return sem::fail(lp->ctx, SEM_EINVAL, "sem_lp_set_block: need %d x %d values", lp->no, lp->no);
     rc = sem_lp_set_linear(lp, 1);
-    if (rc) return rc;
-    rc = refresh_bf16(lp);
     if (rc) return rc;
     SEM_HIP(lp->ctx, hipStreamSynchronize(lp->ctx->stream));
     SEM_HIP(lp->ctx, hipMemcpy(lp->Wf32, W, 4 * (size_t)count, hipMemcpyHostToDevice));
