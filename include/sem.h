@@ -179,12 +179,9 @@ int sem_ax_helmholtz(sem_ctx_t ctx, void* w, const void* u,
 /* Kernel variants of the float64 operator (sem_ax and sem_ax_helmholtz with
  * field dtype SEM_F64), all computing the same sums (results agree to
  * rounding):
- *   SEM_AX_COLUMN     the built-in kernel: one thread per (i, j) column, u's
- *                     column in registers, the element's slices and fluxes in
- *                     LDS (Sec. 4.2, the per-(i, j) thread mapping with a k
- *                     loop); at lx = 12, and at lx = 5 and 6 for large arrays,
- *                     if all of them lie on 16 bytes: whole elements with
- *                     the derivatives on matrix cores;
+ *   SEM_AX_COLUMN     one thread per (i, j) column, u's column in registers, the
+ *                     element's slices and fluxes in LDS (Sec. 4.2, the
+ *                     per-(i, j) thread mapping with a k loop);
  *   SEM_AX_COLUMN_PF  the column mapping with the opposite choice of fetching
  *                     the next slice's factors one slice ahead;
  *   SEM_AX_SLICE      the column mapping with the element passing through LDS
@@ -195,8 +192,11 @@ int sem_ax_helmholtz(sem_ctx_t ctx, void* w, const void* u,
  *                     16, 32 or 64 lanes of one wave (lx = 3, 5, 6, 7), so an
  *                     element never spans two waves and needs no workgroup
  *                     barrier (as the column mapping has at lx = 2, 4, 8).
- * SEM_AX_DEFAULT (-1) is the built-in choice: SEM_AX_COLUMN.  The paper picks among kernel variants by timing them at run
- * time (Sec. 4); sem_ax_tune does that for one lx and element count. */
+ * SEM_AX_DEFAULT (-1) is the built-in choice: SEM_AX_COLUMN, but for lx = 12,
+ * and lx = 5 and 6 with large arrays, if all of them lie on 16 bytes: whole
+ * elements as they lie in memory, the derivatives on matrix cores.  The paper
+ * picks among kernel variants by timing them at run time (Sec. 4);
+ * sem_ax_tune does that for one lx and element count. */
 enum { SEM_AX_DEFAULT = -1, SEM_AX_COLUMN = 0, SEM_AX_COLUMN_PF = 1, SEM_AX_SLICE = 2, SEM_AX_3D = 3,
        SEM_AX_WAVE = 4 };
 #define SEM_AX_VARIANTS 5
@@ -211,7 +211,10 @@ int sem_ax_get_variant(sem_ctx_t ctx, int lx, int* variant);
  * penalise the variant timed first), select the fastest for lx on this
  * context and return it in *best.  us (host, SEM_AX_VARIANTS entries, may be
  * NULL) receives the average launch time of each variant in microseconds, -1
- * where a variant does not exist.  Synchronous. */
+ * where a variant does not exist.  Where the built-in choice is whole elements
+ * it is timed too; if it beats the column mapping, the entry of SEM_AX_COLUMN
+ * is its time, and SEM_AX_COLUMN selected here (not by sem_ax_set_variant)
+ * stands for the built-in choice.  Synchronous. */
 int sem_ax_tune(sem_ctx_t ctx, int lx, int64_t nel, int reps, double* us, int* best);
 /* The same timing on the caller's own float64 operands (the arguments of
  * sem_ax, h1 may be NULL; w is overwritten, no allocation), as the paper's

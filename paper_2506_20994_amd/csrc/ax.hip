@@ -934,6 +934,13 @@ bool flat_aligned(const void* w, const void* u, const void* h1, const void* cons
     return bits % (V * sizeof(TS)) == 0 && (uintptr_t)w % (V * sizeof(TW)) == 0;
 }
 
+// whether the built-in kernel of the public form takes whole elements for this call
+template <int LX, typename TS, typename TW, bool HB>
+bool takes_flat(const void* w, const void* u, const void* h1, const void* const* G, int64_t nel, const void* hb) {
+    if constexpr (!kFlat<LX, TS>) return false;
+    else return nel <= 0x7fffffff && flat_pays<LX, TS, HB>(nel) && flat_aligned<LX, TS, TW>(w, u, h1, G, hb);
+}
+
 template <int LX, typename TU, typename TS, typename TC, typename TW, bool FUSE, bool GATHER, bool HB>
 void launch_flat(sem_ctx_t ctx, void* w, const void* u, const void* const* D, const void* h1, const void* const* G,
                  int64_t nel, const int* skip, double* dot, const int32_t* lid, const void* hb) {
@@ -1010,8 +1017,7 @@ int launch_form(sem_ctx_t ctx, void* w, const void* u, const void* const* D, con
         }
     }
     if constexpr (kFlat<LX, TS> && std::is_same<TU, TS>::value) {
-        if (!lid && (variant == SEM_AX_DEFAULT || variant == SEM_AX_COLUMN) && nel <= 0x7fffffff &&
-            flat_pays<LX, TS, HB>(nel) && flat_aligned<LX, TS, TW>(w, u, h1, G, hb)) {
+        if (!lid && variant == SEM_AX_DEFAULT && takes_flat<LX, TS, TW, HB>(w, u, h1, G, nel, hb)) {
             launch_flat<LX, TU, TS, TC, TW, false, false, HB>(ctx, w, u, D, h1, G, nel, skip, nullptr, nullptr, hb);
             SEM_LAUNCH_CHECK(ctx);
             return SEM_OK;
@@ -1109,7 +1115,8 @@ int ax_public(sem_ctx_t ctx, void* w, const void* u, const void* dx, const void*
     if (alias) return sem::fail(ctx, SEM_EINVAL, "sem_ax: output overlaps an input");
     if (f64)
         return dispatch<double, double, double, double>(ctx, lx, w, u, D, h1, G, nel, nullptr, nullptr, nullptr,
-                                                        nullptr, hb, ctx->ax_variant[lx]);
+                                                        nullptr, hb,
+                                                        ctx->ax_builtin[lx] ? SEM_AX_DEFAULT : ctx->ax_variant[lx]);
     if (field_dtype == SEM_F32)
         return dispatch<float, float, float, float>(ctx, lx, w, u, D, h1, G, nel, nullptr, nullptr, nullptr,
                                                     nullptr, hb);
@@ -1215,6 +1222,7 @@ extern "C" int sem_ax_set_variant(sem_ctx_t ctx, int lx, int variant) {
     if (variant != SEM_AX_DEFAULT && !variant_exists(lx, variant))
         return sem::fail(ctx, SEM_EINVAL, "sem_ax_set_variant: variant %d does not exist at lx=%d", variant, lx);
     ctx->ax_variant[lx] = variant;
+    ctx->ax_builtin[lx] = false;
     return SEM_OK;
 }
 
@@ -1232,7 +1240,9 @@ namespace {
 // launches after two warm-ups, HIP events on the context's stream) in two
 // rounds, keeping each variant's faster round: the clocks of a GPU that was
 // idle rise during the first launches, which would otherwise penalise the
-// variant timed first.  The fastest is selected on the context.
+// variant timed first.  The fastest is selected on the context.  Where the
+// built-in kernel takes whole elements here it is timed after the variants; if it
+// beats the column mapping it takes that one's place.
 int time_variants(sem_ctx_t ctx, int lx, void* w, const void* u, const void* const* D, const void* h1,
                   const void* const* G, int64_t nel, int reps, double* us, int* best) {
     hipStream_t st = ctx->stream;
@@ -1240,16 +1250,25 @@ int time_variants(sem_ctx_t ctx, int lx, void* w, const void* u, const void* con
     SEM_HIP(ctx, hipEventCreate(&e0));
     hipError_t he = hipEventCreate(&e1);
     if (he != hipSuccess) { (void)hipEventDestroy(e0); return sem::check_hip(ctx, he, "hipEventCreate"); }
-    double t_best[SEM_AX_VARIANTS];
-    for (int v = 0; v < SEM_AX_VARIANTS; ++v) t_best[v] = -1.0;
+    constexpr int kBuiltin = SEM_AX_VARIANTS;  // its place behind the variants
+    bool flat = false;
+    switch (lx) {
+#define SEM_AX_FLAT(L) case L: flat = takes_flat<L, double, double, false>(w, u, h1, G, nel, nullptr); break;
+        SEM_AX_FLAT(5) SEM_AX_FLAT(6) SEM_AX_FLAT(12)
+#undef SEM_AX_FLAT
+        default: break;
+    }
+    double t_best[SEM_AX_VARIANTS + 1];
+    for (int v = 0; v <= SEM_AX_VARIANTS; ++v) t_best[v] = -1.0;
     int rc = SEM_OK;
     for (int round = 0; round < 2 && rc == SEM_OK; ++round)
-        for (int v = 0; v < SEM_AX_VARIANTS && rc == SEM_OK; ++v) {
-            if (!variant_exists(lx, v)) continue;
+        for (int v = 0; v <= SEM_AX_VARIANTS && rc == SEM_OK; ++v) {
+            if (v == kBuiltin ? !flat : !variant_exists(lx, v)) continue;
             for (int q = 0; q < 2 + reps && rc == SEM_OK; ++q) {
                 if (q == 2) (void)hipEventRecord(e0, st);
                 rc = dispatch<double, double, double, double>(ctx, lx, w, u, D, h1, G, nel, nullptr, nullptr,
-                                                              nullptr, nullptr, nullptr, v);
+                                                              nullptr, nullptr, nullptr,
+                                                              v == kBuiltin ? SEM_AX_DEFAULT : v);
             }
             if (rc) break;
             (void)hipEventRecord(e1, st);
@@ -1262,12 +1281,15 @@ int time_variants(sem_ctx_t ctx, int lx, void* w, const void* u, const void* con
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
+    const bool builtin = t_best[kBuiltin] >= 0.0 && t_best[kBuiltin] < t_best[SEM_AX_COLUMN];
+    if (builtin) t_best[SEM_AX_COLUMN] = t_best[kBuiltin];
     int best_v = SEM_AX_COLUMN;
     for (int v = 0; v < SEM_AX_VARIANTS; ++v) {
         if (us) us[v] = t_best[v];
         if (t_best[v] >= 0.0 && (t_best[best_v] < 0.0 || t_best[v] < t_best[best_v])) best_v = v;
     }
     ctx->ax_variant[lx] = best_v;
+    ctx->ax_builtin[lx] = builtin && best_v == SEM_AX_COLUMN;
     *best = best_v;
     return SEM_OK;
 }

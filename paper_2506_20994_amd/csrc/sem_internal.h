@@ -21,6 +21,8 @@ struct sem_ctx_s {
     int ax_variant[SEM_LX_MAX + 1] = {SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT,
                                       SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT,
                                       SEM_AX_DEFAULT, SEM_AX_DEFAULT, SEM_AX_DEFAULT};
+    // SEM_AX_COLUMN above stands for the built-in kernel: sem_ax_tune found that faster
+    bool ax_builtin[SEM_LX_MAX + 1] = {};
 };
 
 struct sem_gs_s {
