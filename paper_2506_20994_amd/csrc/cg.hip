@@ -802,13 +802,18 @@ int pcg_vectors(sem_cg_t cg, Level& lv, int nb, int seq) {
     } else {
         const unsigned g = kPcgBlocks / 2;
         pcg_update_kernel<T, 1024><<<g, 1024, 0, st>>>(r, wl, minv, cp, n, cg->S, seq, cg->part, nb, cg->part_vec);
-        // What an iteration touches (six factors, lid and w per local node, five
-        // vectors) against the 256 MB last-level cache: above it the streams of this
-        // kernel go past the caches (32^3, lx = 8: 399 -> 378 us an iteration in
-        // float64, 210 -> 207 in float32), below it they find their lines there (16^3:
-        // 58.2 against 60.4 and 40.8 against 41.8 us).
-        const double touched = (double)cg->n * (7 * sizeof(T) + 4) + 5.0 * sizeof(T) * n;
-        if (touched > 256e6)
+        // What an iteration leaves in the 256 MB last-level cache: lid and w per local
+        // node, five vectors; the factors are read past it.  From about 340 MB on the
+        // streams of this kernel do best to go past it too, below they find their lines
+        // there.  Cached / past the caches, us an iteration, lx 8: float64 25^3 (310 MB)
+        // 182 / 186, 26^3 (349) 206 / 206, 27^3 (391) 229 / 225, 32^3 (651) 399 / 378;
+        // float32 30^3 (296) 167 / 169, 31^3 (326) 189 / 188, 34^3 (431) 246 / 241;
+        // bfloat16, whose vectors are float32, 29^3 (267) 134 / 137, 31^3 166 / 167,
+        // 34^3 210 / 209.  Other orders turn there as well: float64 lx 5 at 346 MB
+        // 246 / 246, lx 12 at 363 212 / 214, float32 lx 10 at 312 183 / 186 and at 397
+        // 230 / 229, bfloat16 lx 5 at 285 175 / 178 and at 359 221 / 219.
+        const double kept = (double)cg->n * (sizeof(T) + 4) + 5.0 * sizeof(T) * n;
+        if (kept > 340e6)
             pcg_p_kernel<T, 1024, true><<<g, 1024, 0, st>>>(x, p, r, minv, n, cg->S, seq, cg->part_vec, (int)g);
         else
             pcg_p_kernel<T, 1024, false><<<g, 1024, 0, st>>>(x, p, r, minv, n, cg->S, seq, cg->part_vec, (int)g);
