@@ -367,11 +367,10 @@ ax_kernel(TW* __restrict__ w, const TU* __restrict__ u,
 // What bounded the column mapping: at lx = 12 its 6 lx LDS reads per node (557 us
 // of 775 at 32768 elements), elsewhere slices that are no whole lines (lx 5, 6, 7,
 // 9, 10, 11) and loads of 2 and 4 bytes a lane.  Per 16.8M nodes with h1, column
-// mapping against this kernel: float64 lx 5 230 / 220, lx 6 224 / 200, lx 12
-// 232 / 207 us (6.0, 5.9 TB/s); float32 lx 4 115 / 101, 5 131 / 109, 6 124 / 103,
-// 7 121 / 111, 10 125 / 109, 12 127 / 107; bfloat16 lx 4 86 / 61,
-// 5 99 / 78, 6 97 / 75, 7 108 / 80, 8 97 / 61, 9 123 / 86, 10 134 / 75, 11 146 / 84,
-// 12 164 / 74.
+// mapping against this kernel: float64 lx 5 231 / 205, lx 6 225 / 191, lx 12
+// 232 / 203 us (6.0 TB/s); float32 lx 4 120 / 103, 5 134 / 105, 6 126 / 98,
+// 7 124 / 106, 10 126 / 105, 12 130 / 104; bfloat16 lx 4 87 / 59, 5 96 / 77, 6 97 / 69,
+// 7 109 / 74, 8 100 / 59, 9 123 / 86, 10 138 / 71, 11 147 / 83, 12 165 / 73.
 typedef double mvec4d __attribute__((ext_vector_type(4)));
 typedef float mvec4f __attribute__((ext_vector_type(4)));
 template <typename TC> struct Mfma;
@@ -389,26 +388,40 @@ template <> struct Mfma<float> {
 };
 
 // Where it is the built-in kernel.  The column mapping stays where it measured no
-// slower: float64 lx 4 (194 against 195 us), 7 (224 / 242), 8 (187 / 196),
-// 9 (224 / 242), 10 (221 / 223), 11 (224 / 273); float32 lx 8 (98 / 100),
-// 9 (131 / 123, but 13.0 / 15.4 us at 1500 elements) and 11 (128 / 132).  The matrix
-// blocks pad lx to a multiple of 4, which is what the odd orders pay for.
+// slower throughout: float64 lx 4 (194 against 195 us), 7 (224 / 242), 8 (187 / 188),
+// 9 (224 / 242), 10 (223 / 211, but 21.9 / 22.5 us at 1500 elements), 11 (224 / 273);
+// float32 lx 8 (100 / 101), 9 (131 / 123, but 11.0 / 12.9 at 1500 elements) and 11
+// (127 / 126, 16.6 / 18.4).  The matrix blocks pad lx to a multiple of 4, which is what
+// the odd orders pay for.
 template <int LX, typename TS>
 constexpr bool kFlat = std::is_same<TS, double>::value ? (LX == 5 || LX == 6 || LX == 12)
                      : std::is_same<TS, float>::value ? (LX >= 4 && LX != 8 && LX != 9 && LX != 11) : LX >= 4;
 
 // Where it is that at every size; the others of kFlat take it for large arrays
-// (flat_pays).
+// (flat_pays).  On the same arrays again and again, column / whole elements, us:
+// float64 lx 12 at 64 elements 10.7 / 5.9, 512 17.1 / 12.5, 1000 25.1 / 24.8, 4000 106 / 89;
+// float32 lx 10 at 64 7.0 / 6.3, 65 7.0 / 6.4, 1000 11.8 / 10.1, 3375 30.2 / 24.6; lx 12 at
+// 64 8.5 / 5.9, 3375 47 / 39; bfloat16 lx 8 at 64 6.2 / 4.3, 67 6.2 / 4.7, 1001 7.0 / 4.6,
+// 3375 10.7 / 9.0; lx 9 at 64 8.8 / 7.3, 67 8.8 / 8.4, 3375 20.6 / 19.1; lx 10 to 12 further
+// apart.
 template <int LX, typename TS>
 constexpr bool kFlatAlways = kFlat<LX, TS> && LX > 7;
 
 // Where the solver form takes it: not at lx = 4, 5 and float32 lx = 7, where the gather
-// hides what the accesses gain.  One conjugate-gradient iteration, column / whole
-// elements, us: float64 lx 5 26.8 / 30.0 at 16^3 elements and 66.1 / 68.3 at 26^3, lx 6
-// 18.2 / 17.1 at 6^3, 24.7 / 25.6 at 12^3, 54.1 / 52.7 at 20^3 and 101.9 / 102.1 at
-// 26^3; float32 lx 5 47.1 / 49.5 at 26^3, lx 6 25.5 / 24.0 at 12^3, 38.5 / 39.6 at 20^3
-// and 65.8 / 65.1 at 26^3, lx 7 36.9 / 39.1 at 16^3 and 97.3 / 96.2 at 26^3; bfloat16
-// lx 5 42.1 / 46.8 and lx 6 61.1 / 58.5 at 26^3.
+// hides what the accesses gain (one conjugate-gradient iteration, column / whole
+// elements, us: float64 lx 5 26.8 / 30.0 at 16^3 elements, float32 lx 5 47.1 / 49.5 at
+// 26^3, lx 7 36.9 / 39.1 at 16^3, bfloat16 lx 5 42.1 / 46.8 at 26^3).  By the order alone,
+// which the layout of its factors follows: at lx = 6 and bfloat16 lx = 7 it leads below
+// and above a stretch of some 2000 to 9000 elements, in which its fewer and larger
+// workgroups fill the chip in the coarser steps.  Float64 lx 6 17.6 / 15.6 at 6^3,
+// 23.2 / 22.6 at 12^3, 32.3 / 33.9 at 15^3, 44.7 / 47.6 at 19^3 (the worst), 52.8 / 49.6
+// at 20^3, 77.2 / 77.3 at 24^3, 160 / 154 at 32^3; float32 lx 6 21.3 / 19.6 at 12^3,
+// 27.7 / 27.6 at 15^3, 42.5 / 43.9 at 22^3, 54.5 / 51.9 at 24^3, 98.1 / 93.1 at 32^3;
+// bfloat16 lx 6 29.5 / 27.9 at 16^3, 37.9 / 39.2 at 21^3, 52.5 / 47.4 at 24^3, lx 7
+// 29.5 / 26.3 at 12^3, 41.4 / 43.6 at 19^3, 56.0 / 51.2 at 21^3.  The orders above lead
+// nearly everywhere: float64 lx 12 46.7 / 42.2 at 9^3, 120 / 102 at 13^3; float32 lx 10
+// 32.6 / 28.3 at 9^3, 73.7 / 66.3 at 16^3; bfloat16 lx 8 24.2 / 18.3 at 9^3, 55.7 / 55.4 at
+// 20^3, lx 9 48.0 / 47.4 at 15^3, 81.1 / 73.9 at 19^3, lx 12 78.2 / 59.5 at 13^3.
 template <int LX, typename TS>
 constexpr bool kFlatSolver = kFlat<LX, TS> && (LX > 7 || LX == 6 || (LX == 7 && std::is_same<TS, uint16_t>::value));
 
@@ -428,6 +441,12 @@ template <int LX> struct ShapeF<LX, false> {
     static constexpr int V = LX == 11 ? 2 : 4;
 };
 
+// The waves per SIMD that its registers have to leave room for.  bfloat16 lx 9 and 12 run
+// workgroups of eight waves, of which 81 registers leave room for two a CU and 80 for
+// three: 139 and 243 us without this at 32768 elements, 120 and 234 with it.
+template <int LX, typename TS, bool HB>
+constexpr int min_waves = !std::is_same<TS, uint16_t>::value || LX == 4 ? 4 : (LX == 9 || LX == 12) && !HB ? 6 : 5;
+
 template <bool WP>
 __device__ __forceinline__ void element_sync() {
     if (WP) wave_sync();
@@ -436,7 +455,7 @@ __device__ __forceinline__ void element_sync() {
 
 template <int LX, int EPB, int NW, int V, typename TU, typename TS, typename TC, typename TW, bool FUSE, bool GATHER,
           bool HB>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 8)))
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(min_waves<LX, TS, HB>, 8)))
 ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
                const TC* __restrict__ dx, const TC* __restrict__ dy, const TC* __restrict__ dz,
                const TC* __restrict__ dxt, const TC* __restrict__ dyt, const TC* __restrict__ dzt,
@@ -482,29 +501,31 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
     // this thread's vector q starts at node at_node(q)
     auto at_node = [&](int q) { return V * (WP ? (wv * NQ + q) * 64 + lane : q * T + tid); };
     const bool full = nn == N;                 // uniform: all but the mesh's last workgroup
-    // nodes o .. o + V - 1 of a streamed array.  A whole workgroup reads without a
-    // branch (threads past its last vector read that one); the last one reads node by
-    // node, zero past the end.
-    auto load_whole = [&](const TS* __restrict__ p, int o) {
-        const vec_s* q = reinterpret_cast<const vec_s*>(p + b0 + min(o, N - V));
-        return __builtin_nontemporal_load(q);
+    // Nodes o .. o + V - 1 of an array, without a branch: a vector past the last of the
+    // workgroup's nn nodes reads that one, which in the mesh's last workgroup need not
+    // start where the thread's does.  place() then moves value i + d to value i, `none`
+    // past the end, once every load is under way.  (Loads there under a branch for each
+    // value were a chain of waits that a ragged call ended with: bfloat16 lx 8 at 65
+    // elements 8.6 us, this 4.6; 64 elements 4.3.)  The type promises the alignment of one
+    // value only, which is also all that the solver's float64 h1 and h2 B, the caller's
+    // arrays, have; the instruction is the same.
+    auto load = [&](const auto* __restrict__ p, int o) {
+        typedef std::remove_const_t<std::remove_reference_t<decltype(*p)>> T1;
+        typedef T1 vec_1 __attribute__((ext_vector_type(V)));
+        typedef T1 vec_any __attribute__((ext_vector_type(V), aligned(sizeof(T1))));
+        const vec_1 x = __builtin_nontemporal_load(reinterpret_cast<const vec_any*>(p + b0 + min(o, nn - V)));
+        return x;
     };
-    // the coefficients h1 and h2 B, which the float64 solver form reads from the
-    // caller's arrays: those promise the alignment of one value only (the type says so;
-    // the load is the same instruction)
-    typedef TS vec_caller __attribute__((ext_vector_type(V), aligned(sizeof(TS))));
-    auto load_coef = [&](const TS* __restrict__ p, int o) -> vec_s {
-        if constexpr (GATHER && std::is_same<TS, double>::value)
-            return __builtin_nontemporal_load(reinterpret_cast<const vec_caller*>(p + b0 + min(o, N - V)));
-        else
-            return load_whole(p, o);
-    };
-    auto load_part = [&](const TS* __restrict__ p, int o) {
-        vec_s v = 0;
+    auto place = [&](auto& v, int o, auto none) {
+        const int d = o - min(o, nn - V);
+        const auto x = v;
 #pragma unroll
-        for (int i = 0; i < V; ++i)
-            if (o + i < nn) v[i] = p[b0 + o + i];
-        return v;
+        for (int i = 0; i < V; ++i) {
+            v[i] = none;
+#pragma unroll
+            for (int k = i; k < V; ++k)
+                if (k == i + d) v[i] = x[k];
+        }
     };
     auto to_c = [](const vec_s& v) {
         vec_c c;
@@ -517,43 +538,43 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
     };
     vec_c uv[NQ];
     vec_s us[NQ], f11[NQ], f22[NQ], f33[NQ], f12[NQ], f13[NQ], f23[NQ], fh[NQ];
-    auto load_all = [&](auto load, auto load_h1) {
-        if constexpr (!GATHER)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) us[q] = load(u, at_node(q));
-        if (h1)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) fh[q] = load_h1(h1, at_node(q));
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int o = at_node(q);
-            f11[q] = load(g11, o); f22[q] = load(g22, o); f33[q] = load(g33, o);
-            f12[q] = load(g12, o); f13[q] = load(g13, o); f23[q] = load(g23, o);
-        }
-    };
     typedef int32_t vec_i __attribute__((ext_vector_type(V)));
     vec_i id[NQ];
-    if constexpr (GATHER) {                    // the numbering ahead of the factors, its nodes of u after them
+    if constexpr (GATHER)                      // the numbering ahead of the factors, its nodes of u after them
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int o = at_node(q);
-            if (full) {
-                id[q] = __builtin_nontemporal_load(reinterpret_cast<const vec_i*>(lid + b0 + min(o, N - V)));
-            } else {
+        for (int q = 0; q < NQ; ++q) id[q] = load(lid, at_node(q));
+    else
 #pragma unroll
-                for (int i = 0; i < V; ++i) id[q][i] = o + i < nn ? lid[b0 + o + i] : -1;
-            }
-        }
+        for (int q = 0; q < NQ; ++q) us[q] = load(u, at_node(q));
+    if (h1)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) fh[q] = load(h1, at_node(q));
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int o = at_node(q);
+        f11[q] = load(g11, o); f22[q] = load(g22, o); f33[q] = load(g33, o);
+        f12[q] = load(g12, o); f13[q] = load(g13, o); f23[q] = load(g23, o);
     }
-    if (full) load_all(load_whole, load_coef);
-    else load_all(load_part, load_part);
     if constexpr (GATHER) {
+        if (!full)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) place(id[q], at_node(q), -1);
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
             for (int i = 0; i < V; ++i) uv[q][i] = id[q][i] >= 0 ? (TC)u[id[q][i]] : TC(0);
     }
     __builtin_amdgcn_sched_barrier(0);         // every load is in flight before anything waits
+    if (!full) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int o = at_node(q);
+            if constexpr (!GATHER) place(us[q], o, 0);
+            if (h1) place(fh[q], o, 0);
+            place(f11[q], o, 0); place(f22[q], o, 0); place(f33[q], o, 0);
+            place(f12[q], o, 0); place(f13[q], o, 0); place(f23[q], o, 0);
+        }
+    }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         if constexpr (!GATHER) uv[q] = to_c(us[q]);
@@ -650,7 +671,9 @@ ax_flat_kernel(TW* __restrict__ w, const TU* __restrict__ u,
         vec_c v = *reinterpret_cast<const vec_c*>(s_t + o) + *reinterpret_cast<const vec_c*>(s_r + o) +
                   *reinterpret_cast<const vec_c*>(s_s + o);
         if constexpr (HB) {                    // Helmholtz: + h2 B u
-            const vec_c m = to_c(full ? load_coef(hb, o) : load_part(hb, o)) * uv[q];
+            vec_s b = load(hb, o);
+            if (!full) place(b, o, 0);
+            const vec_c m = to_c(b) * uv[q];
             if constexpr (FUSE)
 #pragma unroll
                 for (int i = 0; i < V; ++i) pw += (double)m[i] * (double)uv[q][i];
@@ -905,17 +928,16 @@ void launch_3d(sem_ctx_t ctx, void* w, const void* u, const void* const* D, cons
 // last-level cache.  Within it a call on arrays just used finds them there, and the
 // column mapping, whose smaller workgroups then set the pace and whose accesses go
 // through the caches at these orders, is the faster.  Column / whole elements, us, on
-// the same arrays again and again: float64 lx 5 at 16000 elements (144 MB) 25.5 / 31.7,
-// at 32768 (295 MB) 50.9 / 57.4, at 65536 114.6 / 106.1; lx 6 at 16000 (249 MB) 40.3 /
-// 46.0, at 32768 (510 MB) 98.4 / 86.9; float32 lx 4 at 65536 (151 MB) 24.1 / 28.7; lx 5
-// at 32768 (147 MB) 26.6 / 31.2, at 65536 (295 MB) 58.6 / 54.9; lx 6 at 32768 (255 MB)
-// 41.3 / 46.0, at 65536 105.0 / 85.5; lx 7 at 16000 (198 MB) 33.4 / 40.3, at 32768
-// (405 MB) 81.3 / 74.9; bfloat16 lx 5 at 65536 (147 MB) 37.2 / 40.5.  On arrays from
+// the same arrays again and again: float64 lx 5 at 16000 elements (144 MB) 25.2 / 28.2,
+// at 32768 (295 MB) 52.9 / 54.2, at 40000 (360 MB) 70.3 / 65.2; lx 6 at 16000 (249 MB)
+// 38.7 / 42.0, at 24000 (373 MB) 74.6 / 62.4; float32 lx 4 at 65536 (151 MB) 23.7 / 26.1;
+// lx 5 at 32768 (147 MB) 26.6 / 29.2, at 65536 (295 MB) 61.4 / 53.8; lx 6 at 32768 (255 MB)
+// 42.6 / 44.9, at 40000 (311 MB) 63.7 / 54.0; lx 7 at 16000 (198 MB) 33.9 / 37.5, at 24000
+// (296 MB) 57.7 / 54.5; bfloat16 lx 5 at 65536 (147 MB) 37.8 / 40.3.  On arrays from
 // memory whole elements lead from about 110 MB on (float64 lx 6 at 8000, 124 MB: 29.9 /
 // 27.2), but by less.  bfloat16 lx 6 and 7 turn at about 40 MB (lx 6: 8000 elements,
-// 31 MB, 11.4 / 12.7, 13000, 51 MB, 17.6 / 17.0, 32768 34.2 / 33.2, from memory 32000
-// 44.2 / 33.0; lx 7: 3000, 19 MB, 10.4 / 11.5, 8000, 49 MB, 20.3 / 17.8).  The long
-// orders lead at every size that is not bound by the launch.
+// 31 MB, 10.8 / 11.3, 13000, 51 MB, 17.5 / 15.8; lx 7: 3000, 19 MB, 9.9 / 10.2, 8000,
+// 49 MB, 20.1 / 16.6), lx 4 too (32768, 38 MB, 10.7 / 9.8), where the line is as for lx 5.
 template <int LX, typename TS, bool HB>
 bool flat_pays(int64_t nel) {
     constexpr int64_t kLeast = (int64_t)(std::is_same<TS, uint16_t>::value && LX >= 6 ? 40 : 320) << 20;
@@ -925,7 +947,7 @@ bool flat_pays(int64_t nel) {
 // whole elements also need alignment: accesses are V values wide, so every array it
 // streams has to lie on that (any array of torch or hipMalloc does; a view into one
 // may not, and takes the column mapping).  The solver form has no such rule: its arrays
-// are the library's own but for float64 h1 and h2 B (load_coef).
+// are the library's own but for float64 h1 and h2 B.
 template <int LX, typename TS, typename TW>
 bool flat_aligned(const void* w, const void* u, const void* h1, const void* const* G, const void* hb) {
     constexpr int V = ShapeF<LX, std::is_same<TS, double>::value>::V;
