@@ -94,38 +94,30 @@ __global__ void link_kernel(int2* __restrict__ link, int4* __restrict__ more, un
     }
 }
 
-// slink[g] = link of the g-th shared id, whose first copy is idx[off[g]]
-__global__ void slink_kernel(int2* __restrict__ slink, const int2* __restrict__ link, const int32_t* __restrict__ lid,
-                             const int32_t* __restrict__ off, const int32_t* __restrict__ idx, int64_t n_shared) {
+// slink[g] = link of the g-th shared id, unique node su[g]
+__global__ void slink_kernel(int2* __restrict__ slink, const int2* __restrict__ link, const int32_t* __restrict__ su,
+                             int64_t n_shared) {
     const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (g < n_shared) slink[g] = link[lid[idx[off[g]]]];
+    if (g < n_shared) slink[g] = link[su[g]];
 }
 
-__global__ void mult_kernel(double* __restrict__ mult, const int32_t* __restrict__ off,
-                            const int32_t* __restrict__ idx, int64_t n_shared) {
-    const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (g >= n_shared) return;
-    const int32_t b = off[g], e = off[g + 1];
-    for (int32_t q = b; q < e; ++q) mult[idx[q]] = (double)(e - b);
-}
-
-__global__ void owner_kernel(double* __restrict__ owner, const int32_t* __restrict__ off,
-                             const int32_t* __restrict__ idx, int64_t n_shared) {
-    const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (g >= n_shared) return;
-    const int32_t b = off[g], e = off[g + 1];
-    for (int32_t q = b + 1; q < e; ++q) owner[idx[q]] = 0.0;   // idx is ascending: idx[b] owns
-}
-
-__global__ void zero_at_kernel(double* __restrict__ a, const int32_t* __restrict__ idx, int64_t n) {
-    const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (g < n) a[idx[g]] = 0.0;
-}
-
-__global__ void fill_kernel(double* __restrict__ p, double v, int64_t n) {
-    for (int64_t L = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; L < n;
-         L += (int64_t)gridDim.x * blockDim.x)
-        p[L] = v;
+// multiplicity and owner weight of every local node: threads [0, nu) the copies of a
+// unique node (ascending: the first owns), threads [nu, nu + n_masked) a Dirichlet node
+__global__ void weights_kernel(double* __restrict__ mult, double* __restrict__ owner, const int32_t* __restrict__ uoff,
+                               const int32_t* __restrict__ uidx, int64_t nu, int64_t n_masked) {
+    const int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (u < nu) {
+        const int32_t b = uoff[u], e = uoff[u + 1];
+        for (int32_t q = b; q < e; ++q) {
+            const int32_t L = uidx[q];
+            mult[L] = (double)(e - b);
+            owner[L] = q == b ? 1.0 : 0.0;
+        }
+    } else if (u < nu + n_masked) {
+        const int32_t L = uidx[uoff[nu] + (u - nu)];
+        mult[L] = 1.0;
+        owner[L] = 0.0;
+    }
 }
 
 }  // namespace
@@ -170,28 +162,11 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
         n_unique += (c > 0);
         n_more += more_entries(c);
     }
-    // shared ids in order of first appearance; slot[id] = shared index or -1
-    std::vector<int32_t> slot((size_t)(idmax + 1), -1);
-    std::vector<int32_t> off(1, 0);
-    int64_t n_shared = 0;
-    for (int64_t L = 0; L < n_local; ++L) {
-        const int64_t g = key[L];
-        if (g >= 0 && count[(size_t)g] > 1 && slot[(size_t)g] < 0) {
-            slot[(size_t)g] = (int32_t)n_shared++;
-            off.push_back(off.back() + count[(size_t)g]);
-        }
-    }
-    std::vector<int32_t> idx((size_t)off.back());
-    std::vector<int32_t> fillpos(off.begin(), off.end() - 1);
-    for (int64_t L = 0; L < n_local; ++L) {
-        if (key[L] < 0) continue;
-        const int32_t s = slot[(size_t)key[L]];
-        if (s >= 0) idx[(size_t)fillpos[(size_t)s]++] = (int32_t)L;
-    }
-    std::vector<int32_t>().swap(fillpos);
     // dense unique numbering in order of first appearance and the CSR of the
-    // local copies of every unique node (reuses `slot` as id -> unique index)
-    std::fill(slot.begin(), slot.end(), -1);
+    // local copies of every unique node, slot[id] = unique index or -1; the shared ids
+    // are the unique nodes of several copies, listed behind the counter of link_kernel
+    std::vector<int32_t> slot((size_t)(idmax + 1), -1);
+    std::vector<int32_t> shared(1, 0);
     std::vector<int32_t> lid((size_t)n_local);
     std::vector<int32_t> uoff(1, 0);
     uoff.reserve((size_t)n_unique + 1);
@@ -203,6 +178,7 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
             continue;
         }
         if (slot[(size_t)g] < 0) {
+            if (count[(size_t)g] > 1) shared.push_back(nu);
             slot[(size_t)g] = nu++;
             uoff.push_back(uoff.back() + count[(size_t)g]);
         }
@@ -223,63 +199,59 @@ extern "C" int sem_gs_setup(sem_ctx_t ctx, const int64_t* ids, int64_t n_local, 
     std::vector<int32_t>().swap(count);
     std::vector<int32_t>().swap(slot);
 
+    const int64_t n_shared = (int64_t)shared.size() - 1;
     auto* gs = new sem_gs_s();
     gs->ctx = ctx;
     gs->n_local = n_local;
     gs->n_unique = n_unique;
     gs->n_shared = n_shared;
     gs->n_masked = n_masked;
-    // the shared ids' lists, needed here only, and one block for the plan's copies
-    int32_t* d_tmp = nullptr;
-    hipError_t e = hipMalloc(&d_tmp, sizeof(int32_t) * (off.size() + idx.size() + 1));
-    int32_t *d_off = d_tmp, *d_idx = d_tmp + off.size();
-    unsigned* d_next = reinterpret_cast<unsigned*>(d_idx + idx.size());
-    if (e == hipSuccess) e = hipMemset(d_next, 0, sizeof(unsigned));
-    if (e == hipSuccess && n_unique > 0)
-        e = hipMalloc(&gs->more, sizeof(int4) * n_more + sizeof(int2) * (n_unique + n_shared));
+    hipError_t e = hipSuccess;
+    auto alloc = [&](auto** p, size_t bytes) {
+        if (e == hipSuccess && bytes) e = hipMalloc(p, bytes);
+    };
+    auto upload = [&](int32_t* p, const std::vector<int32_t>& v) {
+        if (e == hipSuccess && !v.empty())
+            e = hipMemcpy(p, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice);
+    };
+    if (n_unique > 0) alloc(&gs->more, sizeof(int4) * n_more + sizeof(int2) * (n_unique + n_shared));
     if (e == hipSuccess && n_unique > 0) {
         gs->link = reinterpret_cast<int2*>(gs->more + n_more);
         gs->slink = gs->link + n_unique;
     }
-    if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->mult, sizeof(double) * n_local);
-    if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->owner, sizeof(double) * n_local);
-    if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->lid, sizeof(int32_t) * n_local);
-    if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->uidx, sizeof(int32_t) * n_local);
-    if (e == hipSuccess && n_local > 0) e = hipMalloc(&gs->upos, sizeof(int32_t) * n_local);
-    if (e == hipSuccess && n_local > 0)
-        e = hipMemcpy(gs->upos, upos.data(), sizeof(int32_t) * n_local, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc(&gs->uoff, sizeof(int32_t) * uoff.size());
-    if (e == hipSuccess && n_local > 0)
-        e = hipMemcpy(gs->lid, lid.data(), sizeof(int32_t) * n_local, hipMemcpyHostToDevice);
-    if (e == hipSuccess && n_local > 0)
-        e = hipMemcpy(gs->uidx, uidx.data(), sizeof(int32_t) * n_local, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(gs->uoff, uoff.data(), sizeof(int32_t) * uoff.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !idx.empty())
-        e = hipMemcpy(d_idx, idx.data(), sizeof(int32_t) * idx.size(), hipMemcpyHostToDevice);
+    alloc(&gs->mult, sizeof(double) * n_local);
+    alloc(&gs->owner, sizeof(double) * n_local);
+    alloc(&gs->lid, sizeof(int32_t) * n_local);
+    alloc(&gs->uidx, sizeof(int32_t) * n_local);
+    alloc(&gs->upos, sizeof(int32_t) * n_local);
+    alloc(&gs->uoff, sizeof(int32_t) * uoff.size());
+    upload(gs->upos, upos);
+    upload(gs->lid, lid);
+    upload(gs->uidx, uidx);
+    upload(gs->uoff, uoff);
+    // the shared ids and their counter lie where the multiplicities go once the links
+    // are made (at most n_local / 2 of them): no memory of their own to free
+    int32_t* d_shared = reinterpret_cast<int32_t*>(gs->mult);
+    if (n_unique > 0) upload(d_shared, shared);
     if (e == hipSuccess && n_local > 0) {
-        fill_kernel<<<1024, kBlock, 0, ctx->stream>>>(gs->mult, 1.0, n_local);
-        fill_kernel<<<1024, kBlock, 0, ctx->stream>>>(gs->owner, 1.0, n_local);
-        e = hipGetLastError();
-        if (e == hipSuccess && n_unique > 0) {
-            link_kernel<<<4096, kBlock, 0, ctx->stream>>>(gs->link, gs->more, d_next, gs->uoff, gs->uidx, n_unique);
+        hipStream_t st = ctx->stream;
+        auto blocks = [](int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); };
+        if (n_unique > 0) {
+            link_kernel<<<std::min(blocks(n_unique), 4096u), kBlock, 0, st>>>(
+                gs->link, gs->more, reinterpret_cast<unsigned*>(d_shared), gs->uoff, gs->uidx, n_unique);
             e = hipGetLastError();
         }
         if (e == hipSuccess && n_shared > 0) {
-            const unsigned gr = (unsigned)((n_shared + kBlock - 1) / kBlock);
-            mult_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->mult, d_off, d_idx, n_shared);
-            owner_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->owner, d_off, d_idx, n_shared);
-            slink_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->slink, gs->link, gs->lid, d_off, d_idx, n_shared);
+            slink_kernel<<<blocks(n_shared), kBlock, 0, st>>>(gs->slink, gs->link, d_shared + 1, n_shared);
             e = hipGetLastError();
         }
-        if (e == hipSuccess && n_masked > 0) {
-            const unsigned gr = (unsigned)((n_masked + kBlock - 1) / kBlock);
-            zero_at_kernel<<<gr, kBlock, 0, ctx->stream>>>(gs->owner, gs->uidx + (n_local - n_masked), n_masked);
+        if (e == hipSuccess) {
+            weights_kernel<<<blocks(n_unique + n_masked), kBlock, 0, st>>>(gs->mult, gs->owner, gs->uoff, gs->uidx,
+                                                                           n_unique, n_masked);
             e = hipGetLastError();
         }
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
     }
-    if (d_tmp) (void)hipFree(d_tmp);
     if (e != hipSuccess) {
         sem_gs_destroy(gs);
         return sem::check_hip(ctx, e, "sem_gs_setup");
