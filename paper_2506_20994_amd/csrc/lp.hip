@@ -397,6 +397,14 @@ __global__ void __launch_bounds__(256) wave_gemm(WaveGemm g0, WaveGemm g1, WaveA
     else loss_final(aux, s_red);
 }
 
+// one product of a forward pass of few rows
+template <int TM, int TN>
+__global__ void __launch_bounds__(256) wave_product(WaveGemm g, const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    __shared__ double s_red[4];
+    wave_gemm_block<TM, TN>(g, blockIdx.x, s_red);
+}
+
 // ---- the network's forward pass in one kernel --------------------------------
 // 16 MT rows a workgroup: their features go to LDS as packed fragments, the eight
 // waves share the columns of a layer in pairs of tiles (weights as packed
@@ -1014,6 +1022,7 @@ struct sem_lp_s {
     bool fold_dirty = true;   // folded matrix of the linear form out of date
     float* colpart = nullptr; // column-sum partials (bias gradients)
     // activations / work for up to max_rows rows
+    u16 *F1 = nullptr, *F2 = nullptr;   // hidden layers of a forward pass by products
     u16 *X = nullptr, *Y1 = nullptr, *Y2 = nullptr, *d3b = nullptr, *d2b = nullptr;
     float *Y3 = nullptr, *d3f = nullptr, *d2f = nullptr, *d1f = nullptr, *scale = nullptr;
     // transposes of a minibatch (k-contiguous operands of the weight gradients)
@@ -1152,10 +1161,51 @@ size_t mlp_lds(const sem_lp_s* lp, int mt) {
 }
 constexpr size_t kLdsMax = 160 * 1024;      // per workgroup on gfx950
 
+// Rows up to which a forward pass is the training step's three products instead of
+// mlp_kernel, whose workgroups read all the weights each, at some 100 GB/s: few rows of
+// a large network took the products of 128 x 128 tiles 74 us (lx 12, 1024 hidden, 16
+// rows), that kernel 98 and these 16.  From 1 MB of bf16 weights on they lead up to about
+// 1000 rows: lx 10, 256 hidden (1.2 MB) 17.8 / 12.3 us at 16 rows, 18.4 / 15.2 at 512,
+// 18.9 / 18.5 at 1000, 20.1 / 23.6 at 2000; lx 12, 256 hidden (1.9 MB) 28.6 / 22.5 at
+// 1000, 31.9 / 38.0 at 2000; lx 8, 1024 hidden (4.2 MB) 43.9 / 28.7 at 1000, 47.5 / 67.9
+// at 4096.  Below it they do not: lx 8, 256 hidden (0.7 MB) 11.5 / 11.7 at 16 rows,
+// 12.2 / 14.3 at 1000.
+int64_t product_rows(const sem_lp_s* lp) {
+    const int64_t weights = (int64_t)lp->nh * (lp->nip + lp->nh + lp->no);
+    return 2 * weights < (1 << 20) ? 0 : std::min<int64_t>(lp->max_rows, 1024);
+}
+
 // forward of M rows of X (on 16 bytes) into Y (float32)
 int forward(sem_lp_t lp, const u16* X, int64_t M, float* Y) {
     if (M > 0x7fffffff) return sem::fail(lp->ctx, SEM_EINVAL, "sem_lp: too many rows");
     hipStream_t st = lp->ctx->stream;
+    if (M <= product_rows(lp)) {
+        const int hid = lp->linear ? 0 : EPI_BIAS | EPI_RELU, out = lp->linear ? 0 : EPI_BIAS;
+        WaveGemm g;
+        g.M = (int)M; g.N = lp->nh; g.K = lp->nip;
+        g.A = X; g.lda = lp->nip; g.B = lp->W1b;
+        g.bias = lp->b[0]; g.epi = hid;
+        g.Cb = lp->F1;
+        auto product = [&]() {                 // tiles as in wave_products, 6912 at most
+            const bool one = ((g.M + 15) / 16) * ((g.N + 15) / 16) <= 2048;
+            const unsigned blocks = (unsigned)(one ? wave_blocks<1, 1>(g) : wave_blocks<2, 2>(g));
+            if (one) wave_product<1, 1><<<blocks, 256, 0, st>>>(g, lp->skip);
+            else wave_product<2, 2><<<blocks, 256, 0, st>>>(g, lp->skip);
+        };
+        product();
+        g.K = lp->nh;
+        g.A = lp->F1; g.lda = 0; g.B = lp->W2b;
+        g.bias = lp->b[1];
+        g.Cb = lp->F2;
+        product();
+        g.N = lp->no;
+        g.A = lp->F2; g.B = lp->W3b;
+        g.bias = lp->b[2]; g.epi = out;
+        g.Cb = nullptr; g.Cf = Y; g.ldc = lp->no;
+        product();
+        SEM_LAUNCH_CHECK(lp->ctx);
+        return SEM_OK;
+    }
 #define LP_MLP(MT) mlp_kernel<MT><<<(unsigned)((M + 16 * MT - 1) / (16 * MT)), 64 * kMlpWaves, mlp_lds(lp, MT), st>>>( \
         Y, X, lp->nip, M, lp->W1b, lp->b[0], lp->W2b, lp->b[1], lp->W3b, lp->b[2], lp->nh, lp->no, lp->linear, lp->skip)
     // 32 rows a workgroup read the weights half as often, 16 rows make twice the
@@ -1234,6 +1284,10 @@ extern "C" int sem_lp_create_lx(sem_ctx_t ctx, int lx, int hidden, int64_t max_r
     LP_ALLOC(lp->Y3, 4 * R * no);
     LP_ALLOC(lp->scale, 4 * R);
     LP_ALLOC(lp->loss, 4);
+    if (const size_t rows = (size_t)product_rows(lp)) {
+        LP_ALLOC(lp->F1, 2 * packed_size(rows, kHid));
+        LP_ALLOC(lp->F2, 2 * packed_size(rows, kHid));
+    }
 #undef LP_ALLOC
     SEM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     *out = lp;
