@@ -36,7 +36,8 @@ constexpr int kBlock = 256;
 constexpr int kGrid = 8192;
 constexpr int kGrid32 = 2048;
 constexpr int kFinal = 1024;          // threads of the single-block finalisers
-constexpr int kPcgBlocks = 1024;      // most workgroups of the Jacobi-PCG vector kernels
+constexpr int kPcgBlocks = 1536;      // most workgroups of the Jacobi-PCG vector kernels,
+constexpr int kPcgWide = 512;         // and those of 1024 threads
 
 struct Scal {
     double rz, pAp, alpha, beta, rr, bb, tol2, mean, pw_prev;
@@ -220,8 +221,8 @@ __global__ void pcg_init_final(Scal* __restrict__ S, const double* __restrict__ 
 // order, instead of a single-workgroup kernel in between (2.3 + 3.2 us of the 24
 // us of an iteration on a 6^3 lx = 6 box, 8 of 42 on a 16^3 lx = 8 box in float32),
 // with the first node's loads issued ahead of the sum.  Workgroup 0 writes the
-// scalars.  At most 1024 workgroups of 256 threads, or 512 of 1024 (the whole
-// chip), so that the sums stay short.
+// scalars.  At most kPcgBlocks workgroups of 256 threads, or kPcgWide of 1024 (the
+// whole chip), so that the sums stay short.
 //
 // pAp from the operator's partials, alpha = r.z / pAp; r -= alpha w with w_u the
 // assembled w_L; partials (r.Minv.r, r.r)
@@ -786,8 +787,12 @@ template <typename T>
 unsigned vec_grid_t(int64_t n) { return vec_grid(n, sizeof(T) == 8 ? kGrid : kGrid32); }
 
 // the vector kernels of one Jacobi-PCG iteration, after the operator wrote wl and
-// its nb partials: 256-thread workgroups up to 1024 of them (one node a thread),
-// above that the chip filled once with 1024-thread ones
+// its nb partials: 256-thread workgroups up to 1536 of them (one node a thread),
+// above that the chip filled once with 1024-thread ones, which leave CUs idle below
+// 400000 unknowns and take two nodes a thread beyond 524288.  us an iteration with the
+// line at 1024 / 1536 / 2048 workgroups: float64 lx 7 11^3 (287496 unknowns) 31.0 / 27.3 /
+// 27.3, lx 6 14^3 (343000) 31.5 / 29.9 / 29.8, 16^3 (512000) 33.9 / 34.0 / 36.3; float32
+// lx 6 13^3 (274625) 26.3 / 23.1 / 23.0, 16^3 29.0 / 28.8 / 30.0
 template <typename T>
 int pcg_vectors(sem_cg_t cg, Level& lv, int nb, int seq) {
     hipStream_t st = cg->ctx->stream;
@@ -800,7 +805,7 @@ int pcg_vectors(sem_cg_t cg, Level& lv, int nb, int seq) {
         pcg_update_kernel<T, 256><<<g, 256, 0, st>>>(r, wl, minv, cp, n, cg->S, seq, cg->part, nb, cg->part_vec);
         pcg_p_kernel<T, 256, false><<<g, 256, 0, st>>>(x, p, r, minv, n, cg->S, seq, cg->part_vec, (int)g);
     } else {
-        const unsigned g = kPcgBlocks / 2;
+        const unsigned g = kPcgWide;
         pcg_update_kernel<T, 1024><<<g, 1024, 0, st>>>(r, wl, minv, cp, n, cg->S, seq, cg->part, nb, cg->part_vec);
         // What an iteration leaves in the 256 MB last-level cache: lid and w per local
         // node, five vectors; the factors are read past it.  From about 340 MB on the

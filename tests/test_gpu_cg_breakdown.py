@@ -46,7 +46,7 @@ def _until_breakdown(ref, b):
     raise AssertionError("no breakdown")
 
 
-@pytest.mark.parametrize("n,lx,h2,its", [(3, 6, -200.0, 9), (10, 8, -3000.0, 2)])
+@pytest.mark.parametrize("n,lx,h2,its", [(3, 6, -200.0, 9), (10, 8, -3000.0, 2), (11, 8, -3000.0, 2)])
 def test_breakdown(sem_ctx, n, lx, h2, its):
     op = BoxOperator(sem_ctx, n, lx, 0.1)
     ref = BoxProblem(n, lx, 0.1, h2=h2)

@@ -1,9 +1,9 @@
 """Krylov solves of the forms that the solver's whole-element operator (lx 6, 10, 12) has
 beside the plain Poisson one: the mass term, which enters p^T A p by itself, Dirichlet
 nodes, which its wide index loads read as -1, and the mass term beside a coefficient h1,
-on 27 elements (a ragged last workgroup wherever one holds several).  And one box of 343000
-unknowns, whose vector kernels run 1024 threads a workgroup with their vectors in the
-last-level cache.
+on 27 elements (a ragged last workgroup wherever one holds several).  And boxes on either
+side of the line from which the vector kernels run 1024 threads a workgroup, with their
+vectors in the last-level cache.
 
 Against the oracle's operator and solution, bounds as in test_gpu_solve.py."""
 import numpy as np
@@ -72,6 +72,8 @@ def test_whole_element_forms_with_h1(sem_ctx, lx, prec):
     _check(sem_ctx, 3, lx, prec, False, 20.0, True, (0,) if prec == "f64" else (1,))
 
 
-@pytest.mark.parametrize("prec,modes", [("f64", (0,)), ("f32", (0, 1)), ("bf16", (0, 1))])
-def test_wide_workgroups_with_cached_vectors(sem_ctx, prec, modes):
-    _check(sem_ctx, 10, 8, prec, False, 1e4, False, modes)
+@pytest.mark.parametrize("n,prec,modes", [(10, "f64", (0,)), (10, "f32", (0, 1)), (10, "bf16", (0, 1)),
+                                          (11, "f64", (0,)), (11, "f32", (1,)), (11, "bf16", (0,))])
+def test_wide_workgroups_with_cached_vectors(sem_ctx, n, prec, modes):
+    """343000 unknowns, 1340 workgroups of 256 threads, and 456533 in 512 of 1024"""
+    _check(sem_ctx, n, 8, prec, False, 1e4, False, modes)
