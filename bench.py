@@ -858,10 +858,13 @@ def main():
     achieved = alg_bytes / (ax_ms * 1e-3) / 1e9
     traffic = load_traffic(n_local)
     _, n_shared = P.sem_gs_info(op.gs)
-    # gather-scatter: per shared local entry its index (4 B), one read and one
-    # write (8 B each); per shared id its CSR offset (4 B)
+    # gather-scatter: per shared local entry one read and one write (8 B each); per
+    # shared id its link (8 B) and, from three copies on, the entries that hold the
+    # copies after the first (16 B: three of them, or four from the second on)
     n_entries = int((op.mult > 1).sum())
-    gs_bytes = 20 * n_entries + 4 * n_shared
+    n_more = sum(int((op.mult == m).sum()) // m * (1 + (m - 1) // 4 * (m > 4))
+                 for m in range(3, int(op.mult.max()) + 1))
+    gs_bytes = 16 * n_entries + 8 * n_shared + 16 * n_more
     out = {
         "metric": "Ax GDOF/s (unique dofs E*(lx-1)^3 per second), FP64, lx=8",
         "value": round(value, 3),

@@ -201,7 +201,7 @@ __device__ __forceinline__ void block_dot(double v, double* __restrict__ dot) {
 // through the caches, since neighbouring elements share nodes; lid < 0 marks
 // a Dirichlet node, read as 0).  The output stays in the local layout
 // (coalesced nontemporal stores); the solver sums the copies of each unique
-// node through the plan's CSR lists.
+// node through the plan's links.
 // TPE: threads per element (lx^2, or a power of two above it that divides 64,
 // so that every element sits inside one wave; the extra lanes idle)
 template <int LX, int EPB, typename TU, typename TS, typename TC, typename TW, bool FUSE, bool GATHER, bool HB,
@@ -938,16 +938,20 @@ void launch_3d(sem_ctx_t ctx, void* w, const void* u, const void* const* D, cons
 // 27.2), but by less.  bfloat16 lx 6 and 7 turn at about 40 MB (lx 6: 8000 elements,
 // 31 MB, 10.8 / 11.3, 13000, 51 MB, 17.5 / 15.8; lx 7: 3000, 19 MB, 9.9 / 10.2, 8000,
 // 49 MB, 20.1 / 16.6), lx 4 too (32768, 38 MB, 10.7 / 9.8), where the line is as for lx 5.
+// With the mass term these two lead from 40 MB on for arrays from memory (lx 6 at 16000
+// 27.3 / 21.2, lx 7 43.7 / 33.3, at 65536 88 / 68 and 138 / 114), but trail by 3 to 6 % on
+// the same arrays up to 200 MB (lx 6 at 16000 19.7 / 20.4, at 40000 40.7 / 43.1, at 65536
+// 85 / 67; lx 7 at 28000 49.1 / 51.9, at 32768 63.3 / 59.8): the larger gain sets the line.
 template <int LX, typename TS, bool HB>
 bool flat_pays(int64_t nel) {
     constexpr int64_t kLeast = (int64_t)(std::is_same<TS, uint16_t>::value && LX >= 6 ? 40 : 320) << 20;
     return kFlatAlways<LX, TS> || nel * (LX * LX * LX) * (9 + HB) * (int64_t)sizeof(TS) >= kLeast;
 }
 
-// whole elements also need alignment: accesses are V values wide, so every array it
+// Whole elements also ask for alignment: accesses are V values wide, so every array it
 // streams has to lie on that (any array of torch or hipMalloc does; a view into one
 // may not, and takes the column mapping).  The solver form has no such rule: its arrays
-// are the library's own but for float64 h1 and h2 B.
+// are the library's own but for float64 h1 and h2 B, whose loads ask for one value's.
 template <int LX, typename TS, typename TW>
 bool flat_aligned(const void* w, const void* u, const void* h1, const void* const* G, const void* hb) {
     constexpr int V = ShapeF<LX, std::is_same<TS, double>::value>::V;

@@ -11,8 +11,8 @@
 // the gather-scatter plan: the operator reads p[lid[L]] for every local node L
 // and writes its element-local output w_L in the local layout (coalesced);
 // the update kernel assembles w_u = sum of the local copies of u, read
-// through the plan's CSR lists, on the fly, so no separate gather-scatter
-// pass and no duplicated vector traffic remain.
+// through the plan's links, on the fly, so no separate gather-scatter pass
+// and no duplicated vector traffic remain.
 // p^T A p is the element-local sum of p_L w_L taken in the operator's
 // epilogue.  Everything stays on the device: scalars (alpha, beta, r.z, ...)
 // live in a small device struct, a `done` flag turns every later kernel of a
@@ -29,8 +29,8 @@
 namespace {
 
 constexpr int kBlock = 256;
-// vector kernels run on a fixed grid (fixed partial count, deterministic
-// reductions): 8192 blocks for float64 vectors, 2048 for float32 ones, whose
+// vector kernels (those of Jacobi-PCG: kPcgBlocks) run on a fixed grid (fixed
+// partial count, deterministic reductions): 8192 blocks for float64 vectors, 2048 for float32 ones, whose
 // lighter per-node traffic is better served by more nodes per thread and
 // shorter single-block finalisers (measured at 32^3, lx = 8)
 constexpr int kGrid = 8192;
@@ -66,7 +66,8 @@ __device__ __forceinline__ double block_sum(double v, double* s_red) {
     return t;
 }
 
-// fixed-order sum of n partials (stride `stride`) by one 1024-thread block
+// fixed-order sum of n partials (stride `stride`) by one workgroup: a finaliser's
+// 1024 threads, or every workgroup of a Jacobi-PCG vector kernel (all the same sum)
 __device__ double final_sum(const double* __restrict__ part, int n, int stride, double* s_red) {
     double v = 0.0;
     for (int q = threadIdx.x; q < n; q += blockDim.x) v += part[(int64_t)q * stride];

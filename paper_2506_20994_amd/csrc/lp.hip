@@ -5,8 +5,9 @@
 // moments, the loss and the bias gradients are float32.
 //
 // GEMM form used throughout: C[M][N] = A[M][K] . B[N][K]^T with both operands
-// k-contiguous (row-major bf16); the other products of backpropagation are
-// brought to this form with explicit transposes.
+// k-contiguous (bf16, row-major or packed as MFMA fragments); the transposes that the
+// other products of backpropagation read are written by the epilogues of the products
+// before them.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

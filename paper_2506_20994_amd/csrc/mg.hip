@@ -33,7 +33,7 @@
 // Vectors are float32 on the unique nodes of each level (the layout the solver
 // iterates in).  The operators run in the solver form of ax_kernel (unique
 // input through lid, element-local output) and the smoothing kernels assemble
-// that output through the plan's CSR lists.  P and P^T act element by element
+// that output through the plan's links.  P and P^T act element by element
 // with the 1-D transfer matrices in LDS (sum factorisation).  Each fine unique
 // node is taken from its first local copy (its owner); that is exact because a
 // coarse basis function that is non-zero at a fine node belongs to every

@@ -10,8 +10,9 @@ count and lx: every point uses N_E elements of random symmetric positive
 definite factors, h1 ~ U[0.5, 2] and u ~ N(0, 1).
 
 With --tune every point first times each float64 kernel variant of the
-operator on its own fields (sem_ax_tune_on: the column mapping, the same with
-the other prefetch choice, the slice-pipelined column mapping, one thread per
+operator on its own fields (sem_ax_tune_on: the column mapping, or whole elements
+where the built-in choice is those and they are the faster, the column mapping
+with the other prefetch choice, the slice-pipelined column mapping, one thread per
 node, one element per wave), as the paper's run-time autotuning does (Sec. 4),
 and the timed run uses the fastest.
 
