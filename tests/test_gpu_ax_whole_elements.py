@@ -1,7 +1,9 @@
 """The whole-element kernel of the operator (matrix-core products of an element's
 lines) at its edges: element counts that leave the last workgroup ragged or
-make it the only one, every lx and storage type that runs it, the Helmholtz
-term, no h1; the size from which short orders take it; arrays that do not lie on
+make it the only one, the Helmholtz term, no h1, at the orders that run it at
+every size (the rows of the short orders at these counts run the column mapping;
+test_gpu_ax_whole_elements_large.py has their whole elements); the size from
+which short orders take it; arrays that do not lie on
 its access width (a view into a buffer
 takes the column mapping); non-finite values, which stay in their element; and
 the solver's form with its plane layout of the factors.
